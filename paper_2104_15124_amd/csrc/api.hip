@@ -24,6 +24,20 @@ const char* const kProfNames[KVB_PROF_SLOTS] = {
 
 using namespace kvbh;
 
+static void fixed_buffers(kvb_ctx ctx, Carve& dev, Carve& host)
+{
+    ctx->tune_dev = dev.take<kvb::TuneResult>(1);
+    ctx->build_dev = dev.take<BuildDev>(1);
+    ctx->fb_count_dev = dev.take<int>(1);
+    ctx->pairs_dev = dev.take<unsigned long long>(1);
+    ctx->tune_host = host.take<kvb::TuneResult>(1);
+    ctx->build_host = host.take<BuildDev>(1);
+    ctx->fb_count_host = host.take<int>(1);
+    ctx->pairs_host = host.take<unsigned long long>(1);
+    ctx->union_host = host.take<unsigned long long>(2);
+    ctx->spec_host = host.take<double>(2 * SPEC_MAX);
+}
+
 extern "C" {
 
 int kvb_create(kvb_ctx* out, void* hip_stream)
@@ -38,23 +52,17 @@ int kvb_create(kvb_ctx* out, void* hip_stream)
     kvb_ctx ctx = new kvb_ctx_s();
     ctx->stream = static_cast<hipStream_t>(hip_stream);
     ctx->device = dev;
-    if (hipMalloc(reinterpret_cast<void**>(&ctx->tune_dev), sizeof(kvb::TuneResult)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->tune_host), sizeof(kvb::TuneResult), hipHostMallocDefault) !=
-            hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&ctx->build_dev), sizeof(BuildDev)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->build_host), sizeof(BuildDev), hipHostMallocDefault) !=
-            hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&ctx->fb_count_dev), sizeof(int)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&ctx->pairs_dev), sizeof(unsigned long long)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->pairs_host), sizeof(unsigned long long),
-                      hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->fb_count_host), sizeof(int), hipHostMallocDefault) !=
-            hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->union_host), 2 * sizeof(unsigned long long),
-                      hipHostMallocDefault) != hipSuccess) {
+    // the context's small fixed buffers: one device and one pinned allocation
+    // (each pinned allocation takes some 200 us)
+    Carve dsz(nullptr), hsz(nullptr);
+    fixed_buffers(ctx, dsz, hsz);
+    if (hipMalloc(&ctx->fixed_dev, dsz.off) != hipSuccess ||
+        hipHostMalloc(&ctx->fixed_host, hsz.off, hipHostMallocDefault) != hipSuccess) {
         kvb_destroy(ctx);
         return KVB_E_NOMEM;
     }
+    Carve dcv(ctx->fixed_dev), hcv(ctx->fixed_host);
+    fixed_buffers(ctx, dcv, hcv);
     if (noalloc_scratch_init(dev) != KVB_OK) {
         kvb_destroy(ctx);
         return KVB_E_HIP;
@@ -87,16 +95,9 @@ void kvb_destroy(kvb_ctx ctx)
         (void)hipEventDestroy(p.b);
     }
     if (ctx->scratch) (void)hipFree(ctx->scratch);
-    if (ctx->tune_dev) (void)hipFree(ctx->tune_dev);
-    if (ctx->tune_host) (void)hipHostFree(ctx->tune_host);
-    if (ctx->fb_count_dev) (void)hipFree(ctx->fb_count_dev);
-    if (ctx->fb_count_host) (void)hipHostFree(ctx->fb_count_host);
-    if (ctx->build_dev) (void)hipFree(ctx->build_dev);
-    if (ctx->build_host) (void)hipHostFree(ctx->build_host);
+    if (ctx->fixed_dev) (void)hipFree(ctx->fixed_dev);
+    if (ctx->fixed_host) (void)hipHostFree(ctx->fixed_host);
     if (ctx->loss_dev) (void)hipFree(ctx->loss_dev);
-    if (ctx->pairs_dev) (void)hipFree(ctx->pairs_dev);
-    if (ctx->pairs_host) (void)hipHostFree(ctx->pairs_host);
-    if (ctx->union_host) (void)hipHostFree(ctx->union_host);
     part_free(ctx);
     delete ctx;
 }

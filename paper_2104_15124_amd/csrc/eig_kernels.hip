@@ -48,25 +48,10 @@ __global__ __launch_bounds__(256) void k_spmv(const int64_t* __restrict__ rowptr
     if (lane == 0) y[i] = s;
 }
 
-// h[c] = V[c] . w, one workgroup per column: the threads stride over the
-// rows, then a fixed-order reduction (wavefront butterflies, then the four
-// wavefronts in order)
-__global__ __launch_bounds__(256) void k_project(const double* __restrict__ V, int64_t ldv,
-                                                 const double* __restrict__ w, int n, double* __restrict__ h)
-{
-    __shared__ double red[4];
-    const double* vc = V + static_cast<size_t>(blockIdx.x) * ldv;
-    double s = 0.0;
-    for (int r = threadIdx.x; r < n; r += 256) s += vc[r] * w[r];
-    s = wave_sum_f64(s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) h[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
 // part[s * ldp + c] = V[c][rows of chunk s] . w[same rows]: grid (ncol, chunks),
-// so that a few columns still spread over the whole chip; the same fixed-order
-// reduction within each workgroup as k_project
+// so that a few columns still spread over the whole chip; fixed-order
+// reduction within each workgroup (wavefront butterflies, then the four
+// wavefronts in order)
 __global__ __launch_bounds__(256) void k_project_part(const double* __restrict__ V, int64_t ldv,
                                                       const double* __restrict__ w, int n, int chunk, int ldp,
                                                       double* __restrict__ part)
@@ -159,11 +144,104 @@ __global__ __launch_bounds__(256) void k_ritz(const double* __restrict__ V, int6
 // Spectral solution of the Kolmogorov problem (Section 3.1): with unit
 // eigenvectors y_j of Lhat and S = P D^{1/2},
 //   t = S g;  c_j = y_j . t;  f = S^{-1} sum_j y_j c_j / lambda_j;  g_l = S^{-1} sum_j y_j c_j.
-__global__ __launch_bounds__(256) void k_weight(const double* __restrict__ P, const double* __restrict__ D,
-                                                const double* __restrict__ g, int n, double* __restrict__ t)
+
+// part[(q nvec + j) nchunk + s] = y_j . (S x_q) over the rows of chunk s (without
+// WEIGHT: y_j . x_q), for RHS vectors x_0, x_1. Bound by reading Y once. A
+// workgroup takes SP_VECS basis vectors and one row chunk, so the weights and
+// the right sides are formed once per SP_VECS vectors, both right sides share
+// one read of Y, and nvec / SP_VECS x nchunk workgroups (nchunk up to 64)
+// cover the chip; one workgroup per vector over all rows left 36 of 256 CUs
+// busy at 36 vectors (106 us per projection at n = 100k,
+// 10 now for one right side and 12 for two).
+// Fixed order: the threads' strided sums, wavefront butterflies, the four
+// wavefronts, then the chunks (project_total).
+constexpr int SP_VECS = 4;
+template <int RHS, bool WEIGHT>
+__global__ __launch_bounds__(256) void k_project_chunk(const double* __restrict__ Y, int nvec,
+                                                       const double* __restrict__ x0, const double* __restrict__ x1,
+                                                       const double* __restrict__ P, const double* __restrict__ D,
+                                                       int n, int chunk, double* __restrict__ part)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n) t[r] = P[r] * sqrt(D[r]) * g[r];
+    __shared__ double red[4][RHS * SP_VECS];
+    const int j0 = blockIdx.x * SP_VECS;
+    const int r0 = blockIdx.y * chunk, r1 = min(n, r0 + chunk);
+    const double* y[SP_VECS];
+#pragma unroll
+    for (int v = 0; v < SP_VECS; ++v) y[v] = Y + static_cast<size_t>(min(j0 + v, nvec - 1)) * n;
+    double acc[RHS][SP_VECS] = {};
+#pragma unroll 2
+    for (int r = r0 + threadIdx.x; r < r1; r += 256) {
+        const double s = WEIGHT ? P[r] * sqrt(D[r]) : 1.0;
+        const double w0 = WEIGHT ? s * x0[r] : x0[r];
+        const double w1 = RHS > 1 ? (WEIGHT ? s * x1[r] : x1[r]) : 0.0;
+#pragma unroll
+        for (int v = 0; v < SP_VECS; ++v) {
+            const double t = y[v][r];
+            acc[0][v] += t * w0;
+            if (RHS > 1) acc[RHS - 1][v] += t * w1;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < RHS; ++q)
+#pragma unroll
+        for (int v = 0; v < SP_VECS; ++v) {
+            const double t = wave_sum_f64(acc[q][v]);
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q * SP_VECS + v] = t;
+        }
+    __syncthreads();
+    if (threadIdx.x < RHS * SP_VECS) {
+        const int q = threadIdx.x / SP_VECS, j = j0 + threadIdx.x % SP_VECS, e = threadIdx.x;
+        if (j < nvec)
+            part[(static_cast<size_t>(q) * nvec + j) * gridDim.y + blockIdx.y] =
+                (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+    }
+}
+
+// y_j . (S x_q) from its chunks (at most 64), one wavefront per (q, j).
+__device__ __forceinline__ double project_total(const double* __restrict__ part, int nchunk, int qj)
+{
+    const int lane = lane_id();
+    return wave_sum_f64(lane < nchunk ? part[static_cast<size_t>(qj) * nchunk + lane] : 0.0);
+}
+
+// cg_j = c_j, cf_j = c_j / lambda_j, and c_j to the host (lam, c_host: pinned)
+__global__ __launch_bounds__(256) void k_solve_coef(const double* __restrict__ part, int nchunk, int nvec,
+                                                    const double* __restrict__ lam, double* __restrict__ cf,
+                                                    double* __restrict__ cg, double* __restrict__ c_host)
+{
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= nvec) return;
+    const double c = project_total(part, nchunk, j);
+    if (lane_id() == 0) {
+        cg[j] = c;
+        cf[j] = c / lam[j];
+        c_host[j] = c;
+    }
+}
+
+// coef = p, lambda p, q, lambda q (nvec each) from the projections p, q of two right sides
+__global__ __launch_bounds__(256) void k_cdc_coef(const double* __restrict__ part, int nchunk, int nvec,
+                                                  const double* __restrict__ lam, double* __restrict__ coef)
+{
+    const int qj = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (qj >= 2 * nvec) return;
+    const double c = project_total(part, nchunk, qj);
+    const int q = qj / nvec, j = qj % nvec;
+    if (lane_id() == 0) {
+        coef[(2 * q) * nvec + j] = c;
+        coef[(2 * q + 1) * nvec + j] = lam[j] * c;
+    }
+}
+
+// expansion coefficient of phi_l in grad u . grad v, in the y basis: (lambda_l a_l - b_l) / 2
+__global__ __launch_bounds__(256) void k_cdc_grad_coef(const double* __restrict__ part, int nchunk, int nvec,
+                                                       const double* __restrict__ lam, double* __restrict__ coef)
+{
+    const int l = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (l >= nvec) return;
+    const double a = project_total(part, nchunk, l);
+    const double b = project_total(part, nchunk, nvec + l);
+    if (lane_id() == 0) coef[l] = 0.5 * (lam[l] * a - b);
 }
 
 __global__ __launch_bounds__(256) void k_expand(const double* __restrict__ Y, int nvec, const double* __restrict__ cf,
@@ -174,6 +252,7 @@ __global__ __launch_bounds__(256) void k_expand(const double* __restrict__ Y, in
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
     double sf = 0.0, sg = 0.0;
+#pragma unroll 8
     for (int j = 0; j < nvec; ++j) {
         const double y = Y[static_cast<size_t>(j) * n + r];
         sf += y * cf[j];
@@ -196,6 +275,7 @@ __global__ __launch_bounds__(256) void k_cdc_products(const double* __restrict__
     if (r >= n) return;
     // coef: p, lambda p, q, lambda q (nvec each)
     double U = 0.0, LU = 0.0, V = 0.0, LV = 0.0;
+#pragma unroll 8
     for (int j = 0; j < nvec; ++j) {
         const double y = Y[static_cast<size_t>(j) * n + r];
         U += coef[j] * y;
@@ -274,6 +354,20 @@ __global__ __launch_bounds__(256) void k_advect(const float* __restrict__ X, int
 }  // namespace kvb
 
 namespace {
+
+// Row chunks of the spectral projections: at least 512 rows each, at most 64
+// (one wavefront adds them), and few enough that nvec sums per chunk fit in
+// the n doubles a right side would take; one chunk writes its sums in place.
+struct RowChunks {
+    int rows, count;
+};
+
+RowChunks row_chunks(int n, int nvec)
+{
+    const int want = std::max(1, std::min({64, n / 512, n / nvec}));
+    const int rows = (n + want - 1) / want;
+    return {rows, (n + rows - 1) / rows};
+}
 
 // split of the Lanczos projections over rows: chunks of at least 8192 rows,
 // at most 64 chunks
@@ -575,22 +669,21 @@ int kvb_kolmogorov_solve(kvb_ctx ctx, const double* evecs, const double* evals_h
     int rc = ensure_scratch(ctx, round256(size_t(nn) * sizeof(double)) + 3 * round256(size_t(l) * sizeof(double)) + 1024);
     if (rc) return rc;
     Carve cv(ctx->scratch);
-    double* t = cv.take<double>(nn);
+    double* part = cv.take<double>(nn);
     double* c = cv.take<double>(l);
     double* cf = cv.take<double>(l);
     double* cg = cv.take<double>(l);
     hipStream_t st = ctx->stream;
     const double* Y = evecs + size_t(skip) * nn;
     const dim3 blk(256), rows_grid((nn + 255) / 256);
-    hipLaunchKernelGGL(kvb::k_weight, rows_grid, blk, 0, st, P, D, g, nn, t);
-    hipLaunchKernelGGL(kvb::k_project, dim3(l), blk, 0, st, Y, static_cast<int64_t>(nn), t, nn, c);
-    KVB_HIP(ctx, hipGetLastError());
-    std::vector<double> ch(l), fh(l);
-    KVB_HIP(ctx, hipMemcpyAsync(ch.data(), c, sizeof(double) * l, hipMemcpyDeviceToHost, st));
-    KVB_HIP(ctx, hipStreamSynchronize(st));
-    for (int j = 0; j < l; ++j) fh[j] = ch[j] / evals_host[skip + j];
-    KVB_HIP(ctx, hipMemcpyAsync(cf, fh.data(), sizeof(double) * l, hipMemcpyHostToDevice, st));
-    KVB_HIP(ctx, hipMemcpyAsync(cg, ch.data(), sizeof(double) * l, hipMemcpyHostToDevice, st));
+    double* lam = ctx->spec_host;
+    double* ch = ctx->spec_host + SPEC_MAX;
+    for (int j = 0; j < l; ++j) lam[j] = evals_host[skip + j];
+    const RowChunks rk = row_chunks(nn, l);
+    double* pt = rk.count > 1 ? part : c;
+    hipLaunchKernelGGL((kvb::k_project_chunk<1, true>), dim3((l + kvb::SP_VECS - 1) / kvb::SP_VECS, rk.count), blk, 0,
+                       st, Y, l, g, g, P, D, nn, rk.rows, pt);
+    hipLaunchKernelGGL(kvb::k_solve_coef, dim3((l + 3) / 4), blk, 0, st, pt, rk.count, l, lam, cf, cg, ch);
     hipLaunchKernelGGL(kvb::k_expand, rows_grid, blk, 0, st, Y, l, cf, cg, P, D, nn, f, g_proj);
     KVB_HIP(ctx, hipGetLastError());
     KVB_HIP(ctx, hipStreamSynchronize(st));
@@ -619,41 +712,27 @@ int kvb_carre_du_champ(kvb_ctx ctx, const double* evecs, const double* evals_hos
                                      2 * round256(size_t(npairs) * sizeof(int)) + 2048);
     if (rc) return rc;
     Carve cv(ctx->scratch);
-    double* su = cv.take<double>(nn);
-    double* sv = cv.take<double>(nn);
+    double* part = cv.take<double>(2 * size_t(nn));
     double* t1 = cv.take<double>(nn);
     double* t2 = cv.take<double>(nn);
     double* pq = cv.take<double>(2 * size_t(nvec));
     double* coef = cv.take<double>(4 * size_t(nvec));
-    double* ab = cv.take<double>(2 * size_t(nvec));
     int* pj = cv.take<int>(npairs);
     int* pk = cv.take<int>(npairs);
     hipStream_t st = ctx->stream;
-    const dim3 blk(256), rows_grid((nn + 255) / 256);
-    hipLaunchKernelGGL(kvb::k_weight, rows_grid, blk, 0, st, P, D, u, nn, su);
-    hipLaunchKernelGGL(kvb::k_weight, rows_grid, blk, 0, st, P, D, v, nn, sv);
-    hipLaunchKernelGGL(kvb::k_project, dim3(nvec), blk, 0, st, evecs, static_cast<int64_t>(nn), su, nn, pq);
-    hipLaunchKernelGGL(kvb::k_project, dim3(nvec), blk, 0, st, evecs, static_cast<int64_t>(nn), sv, nn, pq + nvec);
-    KVB_HIP(ctx, hipGetLastError());
-    std::vector<double> h(2 * size_t(nvec)), c4(4 * size_t(nvec));
-    KVB_HIP(ctx, hipMemcpyAsync(h.data(), pq, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
-    KVB_HIP(ctx, hipStreamSynchronize(st));
-    for (int j = 0; j < nvec; ++j) {
-        c4[j] = h[j];
-        c4[nvec + j] = evals_host[j] * h[j];
-        c4[2 * nvec + j] = h[nvec + j];
-        c4[3 * nvec + j] = evals_host[j] * h[nvec + j];
-    }
-    KVB_HIP(ctx, hipMemcpyAsync(coef, c4.data(), sizeof(double) * c4.size(), hipMemcpyHostToDevice, st));
+    const dim3 blk(256), rows_grid((nn + 255) / 256), coef_grid((nvec + 3) / 4);
+    double* lam = ctx->spec_host;
+    for (int j = 0; j < nvec; ++j) lam[j] = evals_host[j];
+    const RowChunks rk = row_chunks(nn, nvec);
+    const dim3 proj_grid((nvec + kvb::SP_VECS - 1) / kvb::SP_VECS, rk.count);
+    double* pt = rk.count > 1 ? part : pq;
+    hipLaunchKernelGGL((kvb::k_project_chunk<2, true>), proj_grid, blk, 0, st, evecs, nvec, u, v, P, D, nn,
+                       rk.rows, pt);
+    hipLaunchKernelGGL(kvb::k_cdc_coef, dim3((2 * nvec + 3) / 4), blk, 0, st, pt, rk.count, nvec, lam, coef);
     hipLaunchKernelGGL(kvb::k_cdc_products, rows_grid, blk, 0, st, evecs, nvec, coef, P, D, nn, t1, t2);
-    hipLaunchKernelGGL(kvb::k_project, dim3(nvec), blk, 0, st, evecs, static_cast<int64_t>(nn), t1, nn, ab);
-    hipLaunchKernelGGL(kvb::k_project, dim3(nvec), blk, 0, st, evecs, static_cast<int64_t>(nn), t2, nn, ab + nvec);
-    KVB_HIP(ctx, hipGetLastError());
-    KVB_HIP(ctx, hipMemcpyAsync(h.data(), ab, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
-    KVB_HIP(ctx, hipStreamSynchronize(st));
-    // expansion coefficient of phi_l in grad u . grad v, in the y basis: (lambda_l a_l - b_l) / 2
-    for (int l = 0; l < nvec; ++l) c4[l] = 0.5 * (evals_host[l] * h[l] - h[nvec + l]);
-    KVB_HIP(ctx, hipMemcpyAsync(coef, c4.data(), sizeof(double) * nvec, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL((kvb::k_project_chunk<2, false>), proj_grid, blk, 0, st, evecs, nvec, t1, t2, P, D, nn,
+                       rk.rows, pt);
+    hipLaunchKernelGGL(kvb::k_cdc_grad_coef, coef_grid, blk, 0, st, pt, rk.count, nvec, lam, coef);
     hipLaunchKernelGGL(kvb::k_expand, rows_grid, blk, 0, st, evecs, nvec, coef, coef, P, D, nn, grad,
                        static_cast<double*>(nullptr));
     KVB_HIP(ctx, hipGetLastError());

@@ -39,6 +39,9 @@ struct PartState {
     int64_t nparams() const { return int64_t(h1) * m + h1 + int64_t(h2) * h1 + h2 + int64_t(nb) * h2 + nb; }
 };
 
+// eigenpairs of a spectral call (kvb_kolmogorov_solve, kvb_carre_du_champ)
+constexpr int SPEC_MAX = 1024;
+
 // Tuning results of both stages and the grid scale, kept on the device
 // between the steps of kvb_build.
 struct BuildDev {
@@ -63,6 +66,8 @@ struct kvb_ctx_s {
     int pattern = KVB_PATTERN_KNN;   // pattern of kvb_build's matrix
     double delta = 0.0;              // sparsity tolerance of kvb_build (0: keep every entry)
     int build_G = 0;   // grid size of the last kvb_build (0: none yet)
+    void* fixed_dev = nullptr;    // the small buffers below: one device and one pinned allocation
+    void* fixed_host = nullptr;
     kvb::TuneResult* tune_dev = nullptr;
     kvb::TuneResult* tune_host = nullptr;   // pinned
     kvbh::BuildDev* build_dev = nullptr;    // device-resident tuning results of kvb_build
@@ -72,6 +77,7 @@ struct kvb_ctx_s {
     unsigned long long* pairs_dev = nullptr;   // candidate pairs scored by the last kvb_knn
     unsigned long long* pairs_host = nullptr;  // pinned
     unsigned long long* union_host = nullptr;  // pinned [2]: reverse entries / check flags, invalid-input flag
+    double* spec_host = nullptr;            // pinned [2 * SPEC_MAX]: eigenvalues in, coefficients out (spectral calls)
     double* loss_dev = nullptr;             // per-epoch losses of kvb_part_train (device)
     int loss_cap = 0;
     kvbh::PartState part;
