@@ -175,16 +175,45 @@ hipError_t launch_gather_samples(const int32_t* pos, int n, const float* a_c, fl
                                  const float* c_c, float* c, hipStream_t st);
 
 // learned partitioner: MLP (mlp_kernels.hip)
-hipError_t launch_gemm_nt(const uint16_t* A, int lda, const uint16_t* B, int ldb, int M, int N, int K,
-                          const float* bias, int relu, const float* mask_ref, int ldm, float* Cf, int ldcf,
-                          uint16_t* Cb, int ldcb, hipStream_t st);
-hipError_t launch_transpose_bf16(const uint16_t* src, int rows, int cols, uint16_t* dst, hipStream_t st);
+struct GemmJob {   // C[M, N] = A[M, K] . B[N, K]^T and its epilogue
+    const uint16_t* A;
+    int lda;
+    const uint16_t* B;
+    int ldb;
+    int M, N, K;
+    const float* bias;       // [N] or null
+    int relu;
+    const float* mask_ref;   // [M, ldm] or null
+    int ldm;
+    float* Cf;               // float32 [M, ldcf] or null
+    int ldcf;
+    uint16_t* Cb;            // BF16 [M, ldcb] or null
+    int ldcb;
+    uint16_t* Ct;            // BF16 C^T [N, M] or null
+};
+hipError_t launch_gemm_nt(const GemmJob& g, hipStream_t st);
+hipError_t launch_gemm_nt_split(const GemmJob& j0, const GemmJob* j1, hipStream_t st);   // split contraction; j1 or null
+struct TransposeJob {
+    const uint16_t* src;
+    int rows, cols;
+    uint16_t* dst;
+};
+hipError_t launch_transpose_bf16(const TransposeJob& j0, const TransposeJob* j1, hipStream_t st);   // j1 or null
 hipError_t launch_cast_rows_bf16(const float* src, int cols, const int32_t* idx, int valid, int rows, int ldd,
                                  uint16_t* dst, hipStream_t st);
 hipError_t launch_cast_bf16(const float* src, int64_t cnt, uint16_t* dst, hipStream_t st);
-hipError_t launch_colsum(const float* src, int rows, int cols, float* out, hipStream_t st);
+struct ColSumJob {
+    const float* src;   // [rows, cols]
+    int cols;           // a multiple of 32
+    float* out;
+};
+struct ColSumJobs {
+    ColSumJob job[3];
+};
+hipError_t launch_colsums(const ColSumJobs& jobs, const double* row_loss, int rows, double* loss, int add,
+                          hipStream_t st);
 hipError_t launch_softmax_xent(const float* Z, int B, int NB, const int32_t* lab, int ks, float* dZ, uint16_t* dZb,
-                               double* row_loss, double* loss_out, int add, hipStream_t st);
+                               double* row_loss, hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m1, float* m2, int64_t cnt, float lr, float b1, float b2,
                        float eps, float c1, float c2, uint16_t* pb, hipStream_t st);
 hipError_t launch_route_topp(const float* Z, int rows, int NB, int P, int32_t* home, int32_t* probe, hipStream_t st);

@@ -95,14 +95,21 @@ int part_alloc(kvb_ctx ctx, int m, int h1, int h2, int nb, int np)
     return KVB_OK;
 }
 
+// BF16 W2^T and W3^T, used by the backward GEMMs.
+int transpose_weights(kvb_ctx ctx)
+{
+    PartState& P = ctx->part;
+    const kvb::TransposeJob w2{P.pb + P.off[2], P.h2, P.h1, P.w2t}, w3{P.pb + P.off[4], P.nb, P.h2, P.w3t};
+    KVB_HIP(ctx, kvb::launch_transpose_bf16(w3, &w2, ctx->stream));
+    return KVB_OK;
+}
+
 // BF16 copy of the parameters and the transposed weights used by the backward GEMMs.
 int refresh_bf16(kvb_ctx ctx)
 {
     PartState& P = ctx->part;
     KVB_HIP(ctx, kvb::launch_cast_bf16(P.p, P.total, P.pb, ctx->stream));
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(P.pb + P.off[2], P.h2, P.h1, P.w2t, ctx->stream));
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(P.pb + P.off[4], P.nb, P.h2, P.w3t, ctx->stream));
-    return KVB_OK;
+    return transpose_weights(ctx);
 }
 
 // Padded flat layout <-> the exported compact order W1 [h1, m], b1, W2, b2, W3, b3.
@@ -111,7 +118,9 @@ int copy_params(kvb_ctx ctx, const float* src, float* dst, bool to_compact)
     PartState& P = ctx->part;
     const size_t m = P.m, mp = P.mpad;
     const int64_t rest = P.off[5] + P.nb - P.off[1];
-    if (to_compact) {
+    if (m == mp) {   // no padding: one order
+        KVB_HIP(ctx, hipMemcpyAsync(dst, src, (P.off[1] + rest) * 4, hipMemcpyDeviceToDevice, ctx->stream));
+    } else if (to_compact) {
         KVB_HIP(ctx, hipMemcpy2DAsync(dst, m * 4, src, mp * 4, m * 4, P.h1, hipMemcpyDeviceToDevice, ctx->stream));
         KVB_HIP(ctx, hipMemcpyAsync(dst + int64_t(P.h1) * P.m, src + P.off[1], rest * 4, hipMemcpyDeviceToDevice,
                                     ctx->stream));
@@ -129,7 +138,7 @@ struct Acts {
     float *H1f, *H2f, *Z;
     // backward only
     float *dZ, *dH2f, *dH1f;
-    uint16_t *dZb, *dZT, *H2T, *dH2b, *dH2T, *H1T, *dH1b, *dH1T, *XbT;
+    uint16_t *dZb, *dZT, *H2T, *dH2b, *dH2T, *H1T, *dH1T, *XbT;
     double* row_loss;
     int32_t *bidx, *nbrlab;
 };
@@ -142,7 +151,7 @@ size_t acts_bytes(const PartState& P, int B, int ks, bool train)
         s += round256(size_t(B) * P.h1 * 4) + round256(size_t(B) * P.h2 * 4);
         s += round256(size_t(B) * P.nb * 4) + round256(size_t(B) * P.h2 * 4) + round256(size_t(B) * P.h1 * 4);
         s += 2 * round256(size_t(B) * P.nb * 2) + 3 * round256(size_t(B) * P.h2 * 2) +
-             3 * round256(size_t(B) * P.h1 * 2) + round256(size_t(B) * P.mpad * 2);
+             2 * round256(size_t(B) * P.h1 * 2) + round256(size_t(B) * P.mpad * 2);
         s += round256(size_t(B) * 8) + round256(size_t(B) * 4) + round256(size_t(B) * ks * 4);
     }
     return s + 256;
@@ -167,7 +176,6 @@ Acts carve_acts(Carve& cv, const PartState& P, int B, int ks, bool train)
         a.dH2b = cv.take<uint16_t>(size_t(B) * P.h2);
         a.dH2T = cv.take<uint16_t>(size_t(B) * P.h2);
         a.H1T = cv.take<uint16_t>(size_t(B) * P.h1);
-        a.dH1b = cv.take<uint16_t>(size_t(B) * P.h1);
         a.dH1T = cv.take<uint16_t>(size_t(B) * P.h1);
         a.XbT = cv.take<uint16_t>(size_t(B) * P.mpad);
         a.row_loss = cv.take<double>(B);
@@ -178,19 +186,32 @@ Acts carve_acts(Carve& cv, const PartState& P, int B, int ks, bool train)
 }
 
 // Forward pass over `valid` rows of X (gathered through idx if non-null),
-// padded with zero rows to B: logits in a.Z. With train, float32 copies of
-// the hidden activations are kept for the ReLU masks of the backward pass.
+// padded with zero rows to B: logits in a.Z. With train, float32 and
+// transposed BF16 copies of the hidden activations are kept for the backward
+// pass (the ReLU masks and the weight gradients).
 int mlp_forward(kvb_ctx ctx, const float* X, const int32_t* idx, int valid, int B, Acts& a, bool train)
 {
     PartState& P = ctx->part;
     hipStream_t st = ctx->stream;
     KVB_HIP(ctx, kvb::launch_cast_rows_bf16(X, P.m, idx, valid, B, P.mpad, a.Xb, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.Xb, P.mpad, P.pb + P.off[0], P.mpad, B, P.h1, P.mpad, P.p + P.off[1], 1,
-                                     nullptr, 0, train ? a.H1f : nullptr, P.h1, a.H1b, P.h1, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.H1b, P.h1, P.pb + P.off[2], P.h1, B, P.h2, P.h1, P.p + P.off[3], 1, nullptr,
-                                     0, train ? a.H2f : nullptr, P.h2, a.H2b, P.h2, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.H2b, P.h2, P.pb + P.off[4], P.h2, B, P.nb, P.h2, P.p + P.off[5], 0, nullptr,
-                                     0, a.Z, P.nb, nullptr, 0, st));
+    kvb::GemmJob g1{a.Xb, P.mpad, P.pb + P.off[0], P.mpad, B, P.h1, P.mpad, P.p + P.off[1], 1};
+    g1.Cb = a.H1b;
+    kvb::GemmJob g2{a.H1b, P.h1, P.pb + P.off[2], P.h1, B, P.h2, P.h1, P.p + P.off[3], 1};
+    g2.Cb = a.H2b;
+    kvb::GemmJob g3{a.H2b, P.h2, P.pb + P.off[4], P.h2, B, P.nb, P.h2, P.p + P.off[5], 0};
+    g3.Cf = a.Z;
+    g1.ldcf = g1.ldcb = P.h1;
+    g2.ldcf = g2.ldcb = P.h2;
+    g3.ldcf = P.nb;
+    if (train) {
+        g1.Cf = a.H1f;
+        g1.Ct = a.H1T;
+        g2.Cf = a.H2f;
+        g2.Ct = a.H2T;
+    }
+    KVB_HIP(ctx, kvb::launch_gemm_nt(g1, st));
+    KVB_HIP(ctx, kvb::launch_gemm_nt(g2, st));
+    KVB_HIP(ctx, kvb::launch_gemm_nt(g3, st));
     return KVB_OK;
 }
 
@@ -201,29 +222,38 @@ int mlp_backward(kvb_ctx ctx, int B, const int32_t* nbrlab, int ks, Acts& a, dou
 {
     PartState& P = ctx->part;
     hipStream_t st = ctx->stream;
-    KVB_HIP(ctx, kvb::launch_softmax_xent(a.Z, B, P.nb, nbrlab, ks, a.dZ, a.dZb, a.row_loss, loss_dev, add, st));
-    // layer 3: dW3 = dZ^T H2, db3 = colsum dZ, dH2 = (dZ W3) * [H2 > 0]
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.dZb, B, P.nb, a.dZT, st));
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.H2b, B, P.h2, a.H2T, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.dZT, B, a.H2T, B, P.nb, P.h2, B, nullptr, 0, nullptr, 0, P.g + P.off[4], P.h2,
-                                     nullptr, 0, st));
-    KVB_HIP(ctx, kvb::launch_colsum(a.dZ, B, P.nb, P.g + P.off[5], st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.dZb, P.nb, P.w3t, P.nb, B, P.h2, P.nb, nullptr, 0, a.H2f, P.h2, a.dH2f, P.h2,
-                                     a.dH2b, P.h2, st));
+    KVB_HIP(ctx, kvb::launch_softmax_xent(a.Z, B, P.nb, nbrlab, ks, a.dZ, a.dZb, a.row_loss, st));
+    const kvb::TransposeJob tz{a.dZb, B, P.nb, a.dZT}, tx{a.Xb, B, P.mpad, a.XbT};
+    KVB_HIP(ctx, kvb::launch_transpose_bf16(tz, &tx, st));
+    // layer 3: dW3 = dZ^T H2, dH2 = (dZ W3) * [H2 > 0]
+    kvb::GemmJob dw3{a.dZT, B, a.H2T, B, P.nb, P.h2, B};
+    dw3.Cf = P.g + P.off[4];
+    dw3.ldcf = P.h2;
+    kvb::GemmJob dh2{a.dZb, P.nb, P.w3t, P.nb, B, P.h2, P.nb};
+    dh2.mask_ref = a.H2f;
+    dh2.Cf = a.dH2f;
+    dh2.Cb = a.dH2b;
+    dh2.ldm = dh2.ldcf = dh2.ldcb = P.h2;
+    dh2.Ct = a.dH2T;
+    KVB_HIP(ctx, kvb::launch_gemm_nt_split(dh2, &dw3, st));
     // layer 2
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.dH2b, B, P.h2, a.dH2T, st));
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.H1b, B, P.h1, a.H1T, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.dH2T, B, a.H1T, B, P.h2, P.h1, B, nullptr, 0, nullptr, 0, P.g + P.off[2], P.h1,
-                                     nullptr, 0, st));
-    KVB_HIP(ctx, kvb::launch_colsum(a.dH2f, B, P.h2, P.g + P.off[3], st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.dH2b, P.h2, P.w2t, P.h2, B, P.h1, P.h2, nullptr, 0, a.H1f, P.h1, a.dH1f, P.h1,
-                                     a.dH1b, P.h1, st));
+    kvb::GemmJob dw2{a.dH2T, B, a.H1T, B, P.h2, P.h1, B};
+    dw2.Cf = P.g + P.off[2];
+    dw2.ldcf = P.h1;
+    kvb::GemmJob dh1{a.dH2b, P.h2, P.w2t, P.h2, B, P.h1, P.h2};
+    dh1.mask_ref = a.H1f;
+    dh1.Cf = a.dH1f;
+    dh1.ldm = dh1.ldcf = P.h1;
+    dh1.Ct = a.dH1T;
+    KVB_HIP(ctx, kvb::launch_gemm_nt_split(dh1, &dw2, st));
     // layer 1
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.dH1b, B, P.h1, a.dH1T, st));
-    KVB_HIP(ctx, kvb::launch_transpose_bf16(a.Xb, B, P.mpad, a.XbT, st));
-    KVB_HIP(ctx, kvb::launch_gemm_nt(a.dH1T, B, a.XbT, B, P.h1, P.mpad, B, nullptr, 0, nullptr, 0, P.g + P.off[0],
-                                     P.mpad, nullptr, 0, st));
-    KVB_HIP(ctx, kvb::launch_colsum(a.dH1f, B, P.h1, P.g + P.off[1], st));
+    kvb::GemmJob dw1{a.dH1T, B, a.XbT, B, P.h1, P.mpad, B};
+    dw1.Cf = P.g + P.off[0];
+    dw1.ldcf = P.mpad;
+    KVB_HIP(ctx, kvb::launch_gemm_nt_split(dw1, nullptr, st));
+    // bias gradients: the column sums of dZ, dH2, dH1; and the loss
+    const kvb::ColSumJobs cs{{{a.dZ, P.nb, P.g + P.off[5]}, {a.dH2f, P.h2, P.g + P.off[3]}, {a.dH1f, P.h1, P.g + P.off[1]}}};
+    KVB_HIP(ctx, kvb::launch_colsums(cs, a.row_loss, B, loss_dev, add, st));
     return KVB_OK;
 }
 
@@ -490,8 +520,7 @@ int kvb_part_train(kvb_ctx ctx, const float* Xs, int64_t ns, int32_t m, const in
             const float c2 = 1.f - std::pow(kAdamB2, float(P.step));
             KVB_HIP(ctx, kvb::launch_adam(P.p, P.g, P.m1, P.m2, P.total, lr, kAdamB1, kAdamB2, kAdamEps, c1, c2, P.pb,
                                           st));
-            KVB_HIP(ctx, kvb::launch_transpose_bf16(P.pb + P.off[2], P.h2, P.h1, P.w2t, st));
-            KVB_HIP(ctx, kvb::launch_transpose_bf16(P.pb + P.off[4], P.nb, P.h2, P.w3t, st));
+            KVB_TRY(transpose_weights(ctx));
         }
     }
     std::vector<double> lh(epochs);

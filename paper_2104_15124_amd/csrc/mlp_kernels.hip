@@ -3,9 +3,11 @@
 // top-P routing and a counter-based generator for seeded parameters.
 //
 // Every GEMM here is C[M, N] = A[M, K] . B[N, K]^T with A and B row-major BF16
-// (K contiguous), FP32 accumulation on v_mfma_f32_32x32x16_bf16; one
-// wavefront computes one 32 x 32 output tile. M, N are multiples of 32 and K a
+// (K contiguous), FP32 accumulation on v_mfma_f32_32x32x16_bf16, 32 x 32
+// output tiles. M, N are multiples of 32 and K a
 // multiple of 16 (the caller pads).
+#include <algorithm>
+
 #include "kvb_device.h"
 #include "kvb_kernels.h"
 
@@ -23,57 +25,148 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 
 // Epilogue: v = acc (+ bias[col]); relu: v = max(v, 0); mask: v = 0 where
-// mask_ref[row, col] <= 0; then optional float32 and BF16 stores.
-__global__ __launch_bounds__(256) void k_gemm_nt(const uint16_t* __restrict__ A, int lda,
-                                                 const uint16_t* __restrict__ B, int ldb, int M, int N, int K,
-                                                 const float* __restrict__ bias, int relu,
-                                                 const float* __restrict__ mask_ref, int ldm,
-                                                 float* __restrict__ Cf, int ldcf, uint16_t* __restrict__ Cb,
-                                                 int ldcb)
+// mask_ref[row, col] <= 0; then optional float32, BF16 and transposed BF16
+// (Ct [N, M]) stores. The four accumulator registers of a group hold four
+// consecutive rows of one column, so the transposed copy takes one 8-byte
+// store per group and the backward products need no transpose pass.
+__device__ __forceinline__ void gemm_store4(const GemmJob& g, int row0, int col, float bcol, float (&v)[4])
 {
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int tiles_n = N / 32;
-    const int tile = blockIdx.x * 4 + wave;
-    if (tile >= (M / 32) * tiles_n) return;
-    const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
-    const int half = lane >> 5;
-    const uint16_t* ap = A + static_cast<size_t>(m0 + (lane & 31)) * lda + half * 8;
-    const uint16_t* bp = B + static_cast<size_t>(n0 + (lane & 31)) * ldb + half * 8;
-    f32x16 acc = {};
-    for (int k = 0; k < K; k += 16) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(ap + k);
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(bp + k);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-    }
-    const int col = n0 + (lane & 31);
-    const float bcol = bias ? bias[col] : 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = m0 + 8 * (r / 4) + 4 * half + (r % 4);
-        float v = acc[r] + bcol;
-        if (relu) v = fmaxf(v, 0.f);
-        if (mask_ref && mask_ref[static_cast<size_t>(row) * ldm + col] <= 0.f) v = 0.f;
-        if (Cf) Cf[static_cast<size_t>(row) * ldcf + col] = v;
-        if (Cb) Cb[static_cast<size_t>(row) * ldcb + col] = f2bf(v);
+    for (int u = 0; u < 4; ++u) {
+        v[u] += bcol;
+        if (g.relu) v[u] = fmaxf(v[u], 0.f);
+        if (g.mask_ref && g.mask_ref[static_cast<size_t>(row0 + u) * g.ldm + col] <= 0.f) v[u] = 0.f;
+        if (g.Cf) g.Cf[static_cast<size_t>(row0 + u) * g.ldcf + col] = v[u];
+        if (g.Cb) g.Cb[static_cast<size_t>(row0 + u) * g.ldcb + col] = f2bf(v[u]);
+    }
+    if (g.Ct) {
+        uint2 t;
+        t.x = f2bf(v[0]) | (static_cast<uint32_t>(f2bf(v[1])) << 16);
+        t.y = f2bf(v[2]) | (static_cast<uint32_t>(f2bf(v[3])) << 16);
+        *reinterpret_cast<uint2*>(g.Ct + static_cast<size_t>(col) * g.M + row0) = t;
     }
 }
 
-// dst[c, r] = src[r, c] for a rows x cols BF16 matrix (32 x 32 LDS tiles).
-__global__ __launch_bounds__(256) void k_transpose_bf16(const uint16_t* __restrict__ src, int rows, int cols,
-                                                        uint16_t* __restrict__ dst)
+// acc + A tile . B tile^T over the k-steps s0 .. s1 - 1 (16 each), in order;
+// the operands of eight steps are loaded together, so a short batch waits for
+// memory once per eight steps instead of once per step.
+__device__ __forceinline__ f32x16 gemm_steps(const uint16_t* ap, const uint16_t* bp, int s0, int s1, f32x16 acc)
+{
+    constexpr int U = 8;
+    int s = s0;
+    for (; s + U <= s1; s += U) {
+        bf16x8 a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = *reinterpret_cast<const bf16x8*>(ap + (s + u) * 16);
+            b[u] = *reinterpret_cast<const bf16x8*>(bp + (s + u) * 16);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+    }
+    for (; s < s1; ++s)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(ap + s * 16),
+                                                      *reinterpret_cast<const bf16x8*>(bp + s * 16), acc, 0, 0, 0);
+    return acc;
+}
+
+// One wavefront per output tile, the k-steps in order (the forward products:
+// the order of a logit's sum is part of the routing).
+__global__ __launch_bounds__(256) void k_gemm_nt(GemmJob g)
+{
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int tiles_n = g.N / 32;
+    const int tile = blockIdx.x * 4 + wave;
+    if (tile >= (g.M / 32) * tiles_n) return;
+    const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
+    const int half = lane >> 5;
+    const uint16_t* ap = g.A + static_cast<size_t>(m0 + (lane & 31)) * g.lda + half * 8;
+    const uint16_t* bp = g.B + static_cast<size_t>(n0 + (lane & 31)) * g.ldb + half * 8;
+    const f32x16 zero = {};
+    const f32x16 acc = gemm_steps(ap, bp, 0, g.K / 16, zero);
+    const int col = n0 + (lane & 31);
+    const float bcol = g.bias ? g.bias[col] : 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        gemm_store4(g, m0 + 8 * q + 4 * half, col, bcol, v);
+    }
+}
+
+// One workgroup per output tile, the k-steps in four consecutive quarters, one
+// per wavefront: the backward products of a training batch have few tiles (32
+// to 256) and a long contraction, so their time is the chain of loads. All
+// four wavefronts load their quarter at once; the accumulator then passes
+// from wavefront to wavefront through LDS, so every sum keeps the order of
+// k_gemm_nt. Two independent products share one launch (job 0: workgroups
+// below tiles0). The backward products of a 512-row batch (128-256-256-1024):
+// 53 us in five launches with one tile per wavefront and one load per step,
+// 25 us in three launches now.
+__global__ __launch_bounds__(256) void k_gemm_nt_split(GemmJob j0, GemmJob j1, int tiles0)
+{
+    constexpr int PRE = 16;   // steps a wavefront loads ahead of its turn
+    __shared__ float s_acc[16][WAVE];
+    const bool second = static_cast<int>(blockIdx.x) >= tiles0;
+    const GemmJob& g = second ? j1 : j0;
+    const int tile = blockIdx.x - (second ? tiles0 : 0);
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int tiles_n = g.N / 32;
+    const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
+    const int half = lane >> 5;
+    const uint16_t* ap = g.A + static_cast<size_t>(m0 + (lane & 31)) * g.lda + half * 8;
+    const uint16_t* bp = g.B + static_cast<size_t>(n0 + (lane & 31)) * g.ldb + half * 8;
+    const int steps = g.K / 16;
+    const int s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+    bf16x8 a[PRE], b[PRE];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u)
+        if (s0 + u < s1) {
+            a[u] = *reinterpret_cast<const bf16x8*>(ap + (s0 + u) * 16);
+            b[u] = *reinterpret_cast<const bf16x8*>(bp + (s0 + u) * 16);
+        }
+    for (int turn = 0; turn < 4; ++turn) {
+        if (wave == turn) {
+            f32x16 acc = {};
+            if (turn > 0)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = s_acc[r][lane];
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (s0 + u < s1) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+            if (s0 + PRE < s1) acc = gemm_steps(ap, bp, s0 + PRE, s1, acc);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s_acc[r][lane] = acc[r];
+        }
+        __syncthreads();
+    }
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = s_acc[4 * wave + u][lane];
+    const int col = n0 + (lane & 31);
+    gemm_store4(g, m0 + 8 * wave + 4 * half, col, g.bias ? g.bias[col] : 0.f, v);
+}
+
+// dst[c, r] = src[r, c] for a rows x cols BF16 matrix (32 x 32 LDS tiles), for
+// one or two matrices (blockIdx.z) in one launch.
+__global__ __launch_bounds__(256) void k_transpose_bf16(TransposeJob j0, TransposeJob j1)
 {
     __shared__ uint16_t t[32][33];
+    const TransposeJob& j = blockIdx.z ? j1 : j0;
+    const uint16_t* __restrict__ src = j.src;
+    uint16_t* __restrict__ dst = j.dst;
+    const int rows = j.rows, cols = j.cols;
     const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-    for (int j = ty; j < 32; j += 8) {
-        const int r = by + j, c = bx + tx;
-        t[j][tx] = (r < rows && c < cols) ? src[static_cast<size_t>(r) * cols + c] : static_cast<uint16_t>(0);
+    for (int q = ty; q < 32; q += 8) {
+        const int r = by + q, c = bx + tx;
+        t[q][tx] = (r < rows && c < cols) ? src[static_cast<size_t>(r) * cols + c] : static_cast<uint16_t>(0);
     }
     __syncthreads();
-    for (int j = ty; j < 32; j += 8) {
-        const int c = bx + j, r = by + tx;
-        if (c < cols && r < rows) dst[static_cast<size_t>(c) * rows + r] = t[tx][j];
+    for (int q = ty; q < 32; q += 8) {
+        const int c = bx + q, r = by + tx;
+        if (c < cols && r < rows) dst[static_cast<size_t>(c) * rows + r] = t[tx][q];
     }
 }
 
@@ -101,68 +194,98 @@ __global__ __launch_bounds__(256) void k_cast_bf16(const float* __restrict__ src
     if (t < cnt) dst[t] = f2bf(src[t]);
 }
 
-// out[c] = sum_r src[r, c] in a fixed order (float64 accumulation).
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ src, int rows, int cols,
-                                                float* __restrict__ out)
+// Bias gradients out[c] = sum_r src[r, c] (float64 accumulation) of up to three
+// matrices, and the batch's mean loss, in one launch: job blockIdx.y, 16
+// columns per workgroup and 16 row lanes per column (lane l adds rows l, l + 16,
+// ...), then the lanes in order. One thread per column, 512 dependent loads
+// each, took 122 us per matrix of a 512-row batch; all three and the loss take 3.7 us.
+__global__ __launch_bounds__(256) void k_colsums(ColSumJobs jobs, const double* __restrict__ row_loss, int rows,
+                                                 double scale, double* __restrict__ loss, int add)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
+    __shared__ double s_part[16][17];
+    if (blockIdx.y == 3) {
+        if (blockIdx.x > 0) return;
+        double s = 0.0;
+        for (int r = threadIdx.x; r < rows; r += 256) s += row_loss[r];
+        s = wave_sum_f64(s);
+        if ((threadIdx.x & 63) == 0) s_part[0][threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const double t = (s_part[0][0] + s_part[0][1]) + (s_part[0][2] + s_part[0][3]);
+            loss[0] = (add ? loss[0] : 0.0) + t * scale;
+        }
+        return;
+    }
+    const ColSumJob j = jobs.job[blockIdx.y];
+    const int c0 = blockIdx.x * 16;
+    if (c0 >= j.cols) return;   // whole workgroup; cols is a multiple of 32
+    const int c = threadIdx.x & 15, l = threadIdx.x >> 4;
     double s = 0.0;
-    for (int r = 0; r < rows; ++r) s += static_cast<double>(src[static_cast<size_t>(r) * cols + c]);
-    out[c] = static_cast<float>(s);
+#pragma unroll 8
+    for (int r = l; r < rows; r += 16) s += static_cast<double>(j.src[static_cast<size_t>(r) * j.cols + c0 + c]);
+    s_part[l][c] = s;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t += s_part[q][threadIdx.x];
+        j.out[c0 + threadIdx.x] = static_cast<float>(t);
+    }
 }
 
-// Soft-target cross-entropy, one wavefront per row of logits Z [B, NB]:
+// Soft-target cross-entropy, one workgroup per row of logits Z [B, NB] (one
+// wavefront per row left a 512-row batch on 128 of 256 CUs: 16.5 -> 8.6 us):
 // target t_b = (1/ks) #{r : lab[i, r] == b} (a histogram built in LDS);
 // loss_i = logsumexp(z) - sum_b t_b z_b; dZ = (softmax(z) - t) / B (float32 and
-// BF16 copies); row losses to row_loss. Dynamic LDS: 4 * NB ints.
+// BF16 copies); row losses to row_loss. Dynamic LDS: NB ints.
 __global__ __launch_bounds__(256) void k_softmax_xent(const float* __restrict__ Z, int B, int NB,
                                                       const int32_t* __restrict__ lab, int ks,
                                                       float* __restrict__ dZ, uint16_t* __restrict__ dZb,
                                                       double* __restrict__ row_loss)
 {
-    extern __shared__ int s_hist[];
-    const int lane = lane_id();
+    extern __shared__ int hist[];
+    __shared__ float s_mx[4];
+    __shared__ double s_se[4], s_tz[4];
     const int wave = threadIdx.x >> 6;
-    const int i = blockIdx.x * 4 + wave;
-    if (i >= B) return;
-    int* hist = s_hist + wave * NB;
-    for (int b = lane; b < NB; b += WAVE) hist[b] = 0;
-    wave_lds_sync();
+    const bool lead = (threadIdx.x & 63) == 0;
+    const int i = blockIdx.x;
+    for (int b = threadIdx.x; b < NB; b += 256) hist[b] = 0;
+    __syncthreads();
     const int32_t* li = lab + static_cast<size_t>(i) * ks;
-    for (int r = lane; r < ks; r += WAVE) {
+    for (int r = threadIdx.x; r < ks; r += 256) {
         const int b = li[r];
         if (b >= 0 && b < NB) atomicAdd(&hist[b], 1);
     }
-    wave_lds_sync();
     const float* z = Z + static_cast<size_t>(i) * NB;
     float mx = -INFINITY;
-    for (int b = lane; b < NB; b += WAVE) mx = fmaxf(mx, z[b]);
+    for (int b = threadIdx.x; b < NB; b += 256) mx = fmaxf(mx, z[b]);
     mx = wave_max_f32(mx);
+    if (lead) s_mx[wave] = mx;
+    __syncthreads();   // the histogram and the wavefronts' maxima
+    mx = fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3]));
     double se = 0.0, tz = 0.0;
-    for (int b = lane; b < NB; b += WAVE) {
+    for (int b = threadIdx.x; b < NB; b += 256) {
         se += exp(static_cast<double>(z[b]) - static_cast<double>(mx));
         tz += static_cast<double>(hist[b]) * static_cast<double>(z[b]);
     }
     se = wave_sum_f64(se);
-    tz = wave_sum_f64(tz) / ks;
+    tz = wave_sum_f64(tz);
+    if (lead) {
+        s_se[wave] = se;
+        s_tz[wave] = tz;
+    }
+    __syncthreads();
+    se = (s_se[0] + s_se[1]) + (s_se[2] + s_se[3]);
+    tz = ((s_tz[0] + s_tz[1]) + (s_tz[2] + s_tz[3])) / ks;
     const double lse = static_cast<double>(mx) + log(se);
     const double invB = 1.0 / B;
-    for (int b = lane; b < NB; b += WAVE) {
+    for (int b = threadIdx.x; b < NB; b += 256) {
         const double p = exp(static_cast<double>(z[b]) - lse);
         const float g = static_cast<float>((p - static_cast<double>(hist[b]) / ks) * invB);
         dZ[static_cast<size_t>(i) * NB + b] = g;
         dZb[static_cast<size_t>(i) * NB + b] = f2bf(g);
     }
-    if (lane == 0) row_loss[i] = lse - tz;
-}
-
-__global__ void k_sum_f64(const double* __restrict__ v, int cnt, double scale, double* __restrict__ out, int add)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int t = 0; t < cnt; ++t) s += v[t];
-    out[0] = (add ? out[0] : 0.0) + s * scale;
+    if (threadIdx.x == 0) row_loss[i] = lse - tz;
 }
 
 // Adam on float32 master parameters with a BF16 shadow (bias-corrected moments).
@@ -253,21 +376,29 @@ __global__ __launch_bounds__(256) void k_fill_normal(float* __restrict__ p, int6
 }
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_gemm_nt(const uint16_t* A, int lda, const uint16_t* B, int ldb, int M, int N, int K,
-                          const float* bias, int relu, const float* mask_ref, int ldm, float* Cf, int ldcf,
-                          uint16_t* Cb, int ldcb, hipStream_t st)
+static bool gemm_ok(const GemmJob& g) { return g.M % 32 == 0 && g.N % 32 == 0 && g.K % 16 == 0; }
+static int gemm_tiles(const GemmJob& g) { return (g.M / 32) * (g.N / 32); }
+
+hipError_t launch_gemm_nt(const GemmJob& g, hipStream_t st)
 {
-    if (M % 32 || N % 32 || K % 16) return hipErrorInvalidValue;
-    const int tiles = (M / 32) * (N / 32);
-    hipLaunchKernelGGL(k_gemm_nt, dim3((tiles + 3) / 4), dim3(256), 0, st, A, lda, B, ldb, M, N, K, bias, relu,
-                       mask_ref, ldm, Cf, ldcf, Cb, ldcb);
+    if (!gemm_ok(g)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gemm_nt, dim3((gemm_tiles(g) + 3) / 4), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 
-hipError_t launch_transpose_bf16(const uint16_t* src, int rows, int cols, uint16_t* dst, hipStream_t st)
+hipError_t launch_gemm_nt_split(const GemmJob& j0, const GemmJob* j1, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_transpose_bf16, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(256), 0, st, src, rows, cols,
-                       dst);
+    if (!gemm_ok(j0) || (j1 && !gemm_ok(*j1))) return hipErrorInvalidValue;
+    const int t0 = gemm_tiles(j0), t1 = j1 ? gemm_tiles(*j1) : 0;
+    hipLaunchKernelGGL(k_gemm_nt_split, dim3(t0 + t1), dim3(256), 0, st, j0, j1 ? *j1 : j0, t0);
+    return hipGetLastError();
+}
+
+hipError_t launch_transpose_bf16(const TransposeJob& j0, const TransposeJob* j1, hipStream_t st)
+{
+    const int rows = std::max(j0.rows, j1 ? j1->rows : 0), cols = std::max(j0.cols, j1 ? j1->cols : 0);
+    hipLaunchKernelGGL(k_transpose_bf16, dim3((cols + 31) / 32, (rows + 31) / 32, j1 ? 2 : 1), dim3(256), 0, st, j0,
+                       j1 ? *j1 : j0);
     return hipGetLastError();
 }
 
@@ -286,18 +417,22 @@ hipError_t launch_cast_bf16(const float* src, int64_t cnt, uint16_t* dst, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float* src, int rows, int cols, float* out, hipStream_t st)
+hipError_t launch_colsums(const ColSumJobs& jobs, const double* row_loss, int rows, double* loss, int add,
+                          hipStream_t st)
 {
-    hipLaunchKernelGGL(k_colsum, dim3((cols + 255) / 256), dim3(256), 0, st, src, rows, cols, out);
+    int cols = 0;
+    for (const ColSumJob& j : jobs.job) {
+        if (j.cols % 32) return hipErrorInvalidValue;
+        cols = std::max(cols, j.cols);
+    }
+    hipLaunchKernelGGL(k_colsums, dim3(cols / 16, 4), dim3(256), 0, st, jobs, row_loss, rows, 1.0 / rows, loss, add);
     return hipGetLastError();
 }
 
 hipError_t launch_softmax_xent(const float* Z, int B, int NB, const int32_t* lab, int ks, float* dZ, uint16_t* dZb,
-                               double* row_loss, double* loss_out, int add, hipStream_t st)
+                               double* row_loss, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_softmax_xent, dim3((B + 3) / 4), dim3(256), 4 * NB * sizeof(int), st, Z, B, NB, lab, ks, dZ,
-                       dZb, row_loss);
-    hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(64), 0, st, row_loss, B, 1.0 / B, loss_out, add);
+    hipLaunchKernelGGL(k_softmax_xent, dim3(B), dim3(256), NB * sizeof(int), st, Z, B, NB, lab, ks, dZ, dZb, row_loss);
     return hipGetLastError();
 }
 
