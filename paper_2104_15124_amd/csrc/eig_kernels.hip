@@ -19,9 +19,11 @@
 // wanted pairs only: eigenvalues by bisection on the Sturm count, eigenvectors
 // by inverse iteration (Golub and Van Loan, Sections 8.4 and 8.2).
 //
-// On the device: the matrix-vector product (one wavefront per row, FP64
+// On the device: the matrix-vector product (16 lanes per row, FP64
 // accumulation of float32 entries), the projections V^T w (one workgroup per
-// basis vector and row chunk, then a fixed-order sum over the chunks), w -= V h (one thread per row), norms and Ritz vectors. Every reduction has a fixed order, so results are reproducible.
+// four basis vectors and row chunk, then a fixed-order sum over the chunks),
+// w -= V h (one thread per row), norms and Ritz vectors. Every reduction has a
+// fixed order, so results are reproducible.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -32,61 +34,100 @@
 
 namespace kvb {
 
-// y = A x, one wavefront per row, lanes strided over the row, butterfly sum
+// y = A x, 16 lanes per row (four rows per wavefront): lane l takes entries l,
+// l + 16, l + 32 and l + 48 of every 64, each in a sum of its own, and the sums
+// are added in the order of a butterfly over 64 lanes. Bound by the gathers of
+// x from L2; a wavefront per row of some 70 entries left most of its second
+// pass idle (43 us at n = 100k and 6.9M entries, 39 us now).
 __global__ __launch_bounds__(256) void k_spmv(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
                                               const float* __restrict__ val, const double* __restrict__ x, int n,
                                               double* __restrict__ y)
 {
-    const int lane = lane_id();
-    const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (i >= n) return;
-    double s = 0.0;
-    for (int64_t p = rowptr[i] + lane; p < rowptr[i + 1]; p += WAVE)
-        s += static_cast<double>(val[p]) * x[col[p]];
+    constexpr int LPR = 16, Q = WAVE / LPR;
+    const int sub = threadIdx.x % LPR;
+    const int i = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+    double s[Q] = {};
+    if (i < n) {
+        const int64_t p1 = rowptr[i + 1];
+        for (int64_t p = rowptr[i] + sub; p < p1; p += WAVE) {
+            int c[Q];
+            float v[Q];
 #pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) s += shfl_xor_f64(s, o);
-    if (lane == 0) y[i] = s;
+            for (int q = 0; q < Q; ++q)
+                if (p + q * LPR < p1) {
+                    c[q] = col[p + q * LPR];
+                    v[q] = val[p + q * LPR];
+                }
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (p + q * LPR < p1) s[q] += static_cast<double>(v[q]) * x[c[q]];
+        }
+    }
+    double t = (s[0] + s[2]) + (s[1] + s[3]);
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) t += shfl_xor_f64(t, o);
+    if (i < n && sub == 0) y[i] = t;
 }
 
-// part[s * ldp + c] = V[c][rows of chunk s] . w[same rows]: grid (ncol, chunks),
-// so that a few columns still spread over the whole chip; fixed-order
-// reduction within each workgroup (wavefront butterflies, then the four
-// wavefronts in order)
-__global__ __launch_bounds__(256) void k_project_part(const double* __restrict__ V, int64_t ldv,
+// part[s * ldp + c] = V[c][rows of chunk s] . w[same rows], PP_VECS columns per
+// workgroup: they share the reads of w, and their loads overlap. Bound by
+// reading V from the Infinity Cache (mean over the sweeps and norms of 400
+// steps at n = 100k: 23.0 us with one column, 19.7 now). A few columns still
+// spread over the whole chip; fixed-order reduction within each workgroup
+// (wavefront butterflies, then the four wavefronts in order)
+constexpr int PP_VECS = 4;
+__global__ __launch_bounds__(256) void k_project_part(const double* __restrict__ V, int64_t ldv, int ncol,
                                                       const double* __restrict__ w, int n, int chunk, int ldp,
                                                       double* __restrict__ part)
 {
-    __shared__ double red[4];
-    const double* vc = V + static_cast<size_t>(blockIdx.x) * ldv;
+    __shared__ double red[4][PP_VECS];
+    const int c0 = blockIdx.x * PP_VECS;
+    const double* v[PP_VECS];
+#pragma unroll
+    for (int u = 0; u < PP_VECS; ++u) v[u] = V + static_cast<size_t>(min(c0 + u, ncol - 1)) * ldv;
     const int64_t r0 = static_cast<int64_t>(blockIdx.y) * chunk;
     const int64_t r1 = r0 + chunk < n ? r0 + chunk : n;
-    double s = 0.0;
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) s += vc[r] * w[r];
-    s = wave_sum_f64(s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    double s[PP_VECS] = {};
+#pragma unroll 4
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
+        const double wr = w[r];
+#pragma unroll
+        for (int u = 0; u < PP_VECS; ++u) s[u] += v[u][r] * wr;
+    }
+#pragma unroll
+    for (int u = 0; u < PP_VECS; ++u) {
+        s[u] = wave_sum_f64(s[u]);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][u] = s[u];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) part[static_cast<size_t>(blockIdx.y) * ldp + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    const int u = threadIdx.x;
+    if (u < PP_VECS && c0 + u < ncol)
+        part[static_cast<size_t>(blockIdx.y) * ldp + c0 + u] = (red[0][u] + red[1][u]) + (red[2][u] + red[3][u]);
 }
 
-// h[c] = sum over chunks s, in order, of part[s * ldp + c]
-__global__ __launch_bounds__(256) void k_project_sum(const double* __restrict__ part, int ncol, int nchunk,
-                                                     int ldp, double* __restrict__ h)
+// h[c] = sum over chunks s, in order, of part[s * ldp + c]; the last column's
+// is alpha_j on the first Gram-Schmidt pass and is added to it on the second
+__global__ __launch_bounds__(64) void k_project_sum(const double* __restrict__ part, int ncol, int nchunk, int ldp,
+                                                    double* __restrict__ h, int first, double* __restrict__ alpha)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncol) return;
     double s = 0.0;
+#pragma unroll 8
     for (int q = 0; q < nchunk; ++q) s += part[static_cast<size_t>(q) * ldp + c];
     h[c] = s;
+    if (c == ncol - 1) *alpha = first ? s : *alpha + s;
 }
 
-// w[r] -= sum_c V[c][r] h[c]
-__global__ __launch_bounds__(256) void k_subtract_span(const double* __restrict__ V, int64_t ldv, int ncol,
-                                                       const double* __restrict__ h, int n, double* __restrict__ w)
+// w[r] -= sum_c V[c][r] h[c]; one wavefront per workgroup, so that the last
+// round of workgroups does not leave compute units idle
+__global__ __launch_bounds__(64) void k_subtract_span(const double* __restrict__ V, int64_t ldv, int ncol,
+                                                      const double* __restrict__ h, int n, double* __restrict__ w)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
     double s = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int c = 0; c < ncol; ++c) s += V[static_cast<size_t>(c) * ldv + r] * h[c];
     w[r] -= s;
 }
@@ -99,17 +140,16 @@ __global__ __launch_bounds__(256) void k_scale(const double* __restrict__ x, dou
     if (r < n) out[r] = x[r] * scale;
 }
 
-// ab[0] = h[0] on the first Gram-Schmidt pass, ab[0] += h[0] on the second
-__global__ void k_alpha_add(const double* __restrict__ h, int first, double* __restrict__ ab)
+// b = sqrt(the sum over chunks, in order, of part[s * ldp]); out[r] = x[r] * (1 / b);
+// the first thread stores b
+__global__ __launch_bounds__(256) void k_scale_by_norm(const double* __restrict__ x, const double* __restrict__ part,
+                                                       int nchunk, int ldp, int n, double* __restrict__ out,
+                                                       double* __restrict__ b)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) ab[0] = first ? h[0] : ab[0] + h[0];
-}
-
-// b = sqrt(nrm2[0]); out[r] = x[r] * (1 / b); the first thread stores b
-__global__ __launch_bounds__(256) void k_scale_by_norm(const double* __restrict__ x, const double* __restrict__ nrm2,
-                                                       int n, double* __restrict__ out, double* __restrict__ b)
-{
-    const double bj = sqrt(nrm2[0]);
+    double nrm2 = 0.0;
+#pragma unroll 8
+    for (int q = 0; q < nchunk; ++q) nrm2 += part[static_cast<size_t>(q) * ldp];
+    const double bj = sqrt(nrm2);
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r == 0) b[0] = bj;
     if (r < n) out[r] = x[r] * (1.0 / bj);
@@ -128,17 +168,28 @@ __global__ __launch_bounds__(256) void k_start_vector(uint64_t seed, int n, doub
     v[r] = static_cast<double>(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
-// Y[i][r] = sum_c V[c][r] S[c][i] (Ritz vectors), S column-major [m][nev] as S[c * nev + i]
+// Y[i][r] = sum_c V[c][r] S[c][i] (Ritz vectors), S as S[c * nev + i]. A
+// workgroup forms RITZ_VECS vectors of its rows from one sweep of V (one vector
+// at a time read V nev times: 5.8 ms for 36 vectors at n = 100k and 400
+// columns, 0.31 ms now).
+constexpr int RITZ_VECS = 12;
 __global__ __launch_bounds__(256) void k_ritz(const double* __restrict__ V, int64_t ldv, int m,
                                               const double* __restrict__ S, int nev, int n, double* __restrict__ Y)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    for (int i = 0; i < nev; ++i) {
-        double s = 0.0;
-        for (int c = 0; c < m; ++c) s += V[static_cast<size_t>(c) * ldv + r] * S[static_cast<size_t>(c) * nev + i];
-        Y[static_cast<size_t>(i) * n + r] = s;
+    const int r = min(static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x), n - 1);
+    const int i0 = blockIdx.y * RITZ_VECS;
+    double s[RITZ_VECS] = {};
+#pragma unroll 4
+    for (int c = 0; c < m; ++c) {
+        const double v = V[static_cast<size_t>(c) * ldv + r];
+#pragma unroll
+        for (int u = 0; u < RITZ_VECS; ++u)
+            s[u] += v * S[static_cast<size_t>(c) * nev + min(i0 + u, nev - 1)];
     }
+    if (static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x) < n)
+#pragma unroll
+        for (int u = 0; u < RITZ_VECS; ++u)
+            if (i0 + u < nev) Y[static_cast<size_t>(i0 + u) * n + r] = s[u];
 }
 
 // Spectral solution of the Kolmogorov problem (Section 3.1): with unit
@@ -545,7 +596,7 @@ int kvb_eigsh(kvb_ctx ctx, const int64_t* rowptr, const int32_t* col, const floa
     const int nn = static_cast<int>(n);
     const int64_t ldv = (n + 63) / 64 * 64;
     const size_t need = round256(size_t(ncv + 1) * ldv * sizeof(double)) + round256(size_t(ldv) * sizeof(double)) +
-                        2 * round256(size_t(ncv + 1) * sizeof(double)) +
+                        round256(size_t(ncv + 1) * sizeof(double)) +
                         round256(size_t(ncv) * nev * sizeof(double)) +
                         round256(size_t(PROJ_MAX_CHUNKS) * (ncv + 1) * sizeof(double)) +
                         round256(2 * size_t(ncv) * sizeof(double)) + 2048;
@@ -555,12 +606,11 @@ int kvb_eigsh(kvb_ctx ctx, const int64_t* rowptr, const int32_t* col, const floa
     double* V = cv.take<double>(size_t(ncv + 1) * ldv);
     double* w = cv.take<double>(ldv);
     double* h = cv.take<double>(ncv + 1);
-    double* hsum = cv.take<double>(ncv + 1);
     double* S = cv.take<double>(size_t(ncv) * nev);
     const int ldp = ncv + 1;
     double* part = cv.take<double>(size_t(PROJ_MAX_CHUNKS) * ldp);
     hipStream_t st = ctx->stream;
-    const dim3 blk(256), rows_grid((nn + 255) / 256), spmv_grid((nn + 3) / 4);
+    const dim3 blk(256), rows_grid((nn + 255) / 256), spmv_grid((nn + 15) / 16);
     double* ab = cv.take<double>(2 * size_t(ncv));   // alpha_0..alpha_{ncv-1}, then beta_0..beta_{ncv-1}
     // row chunks of the projections: at least PROJ_MIN_CHUNK rows, a multiple
     // of 256, at most PROJ_MAX_CHUNKS of them
@@ -568,27 +618,19 @@ int kvb_eigsh(kvb_ctx ctx, const int64_t* rowptr, const int32_t* col, const floa
     chunk = (chunk + 255) / 256 * 256;
     const int nchunk = (nn + chunk - 1) / chunk;
 
-    // hd[0..ncol) = B[:, :ncol]^T x on the device, B's columns ldv apart
-    auto project_cols = [&](const double* B, const double* x, int ncol, double* hd) -> hipError_t {
-        hipLaunchKernelGGL(kvb::k_project_part, dim3(ncol, nchunk), blk, 0, st, B, ldv, x, nn, chunk, ldp, part);
-        hipLaunchKernelGGL(kvb::k_project_sum, dim3((ncol + 255) / 256), blk, 0, st, part, ncol, nchunk, ldp, hd);
-        return hipGetLastError();
-    };
-    auto project = [&](const double* x, int ncol, double* hd) -> hipError_t {
-        return project_cols(V, x, ncol, hd);
-    };
-    // ||x||
-    auto norm = [&](double* x, double* out) -> int {
-        KVB_HIP(ctx, project_cols(x, x, 1, h));
-        KVB_HIP(ctx, hipMemcpyAsync(out, h, sizeof(double), hipMemcpyDeviceToHost, st));
-        KVB_HIP(ctx, hipStreamSynchronize(st));
-        *out = std::sqrt(*out);
-        return KVB_OK;
+    // part = the chunk sums of B[:, :ncol]^T x
+    auto project = [&](const double* B, const double* x, int ncol) {
+        hipLaunchKernelGGL(kvb::k_project_part, dim3((ncol + kvb::PP_VECS - 1) / kvb::PP_VECS, nchunk), blk, 0, st, B,
+                           ldv, ncol, x, nn, chunk, ldp, part);
     };
 
     hipLaunchKernelGGL(kvb::k_start_vector, rows_grid, blk, 0, st, seed, nn, w);
     double b0 = 0.0;
-    KVB_TRY(norm(w, &b0));
+    project(w, w, 1);
+    hipLaunchKernelGGL(kvb::k_project_sum, dim3(1), dim3(64), 0, st, part, 1, nchunk, ldp, h, 1, ab);
+    KVB_HIP(ctx, hipMemcpyAsync(&b0, h, sizeof(double), hipMemcpyDeviceToHost, st));
+    KVB_HIP(ctx, hipStreamSynchronize(st));
+    b0 = std::sqrt(b0);
     KVB_REQUIRE(ctx, b0 > 0, "start vector vanished");
     hipLaunchKernelGGL(kvb::k_scale, rows_grid, blk, 0, st, w, 1.0 / b0, nn, V);
     // The steps run without a host round trip: alpha_j and beta_j stay on the
@@ -598,20 +640,19 @@ int kvb_eigsh(kvb_ctx ctx, const int64_t* rowptr, const int32_t* col, const floa
     double* alpha_d = ab;
     double* beta_d = ab + ncv;
     for (int j = 0; j < ncv; ++j) {
-        double* vj = V + size_t(j) * ldv;
-        hipLaunchKernelGGL(kvb::k_spmv, spmv_grid, blk, 0, st, rowptr, col, val, vj, nn, w);
+        hipLaunchKernelGGL(kvb::k_spmv, spmv_grid, blk, 0, st, rowptr, col, val, V + size_t(j) * ldv, nn, w);
         // two passes of classical Gram-Schmidt against v_0..v_j; alpha_j is
         // the first pass's coefficient on v_j plus the second's correction
         for (int pass = 0; pass < 2; ++pass) {
-            KVB_HIP(ctx, project(w, j + 1, hsum));
-            hipLaunchKernelGGL(kvb::k_subtract_span, rows_grid, blk, 0, st, V, ldv, j + 1, hsum, nn, w);
-            hipLaunchKernelGGL(kvb::k_alpha_add, dim3(1), dim3(64), 0, st, hsum + j, pass == 0 ? 1 : 0,
-                               alpha_d + j);
+            project(V, w, j + 1);
+            hipLaunchKernelGGL(kvb::k_project_sum, dim3((j + 64) / 64), dim3(64), 0, st, part, j + 1, nchunk, ldp, h,
+                               pass == 0 ? 1 : 0, alpha_d + j);
+            hipLaunchKernelGGL(kvb::k_subtract_span, dim3((nn + 63) / 64), dim3(64), 0, st, V, ldv, j + 1, h, nn, w);
         }
         // beta_j = ||w||, v_{j+1} = w / beta_j (V has room for v_ncv)
-        KVB_HIP(ctx, project_cols(w, w, 1, h));
-        hipLaunchKernelGGL(kvb::k_scale_by_norm, rows_grid, blk, 0, st, w, h, nn, V + size_t(j + 1) * ldv,
-                           beta_d + j);
+        project(w, w, 1);
+        hipLaunchKernelGGL(kvb::k_scale_by_norm, rows_grid, blk, 0, st, w, part, nchunk, ldp, nn,
+                           V + size_t(j + 1) * ldv, beta_d + j);
         KVB_HIP(ctx, hipGetLastError());
     }
     std::vector<double> abh(2 * size_t(ncv));
@@ -643,7 +684,7 @@ int kvb_eigsh(kvb_ctx ctx, const int64_t* rowptr, const int32_t* col, const floa
     }
     if (evecs) {
         KVB_HIP(ctx, hipMemcpyAsync(S, Ssel.data(), sizeof(double) * Ssel.size(), hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(kvb::k_ritz, rows_grid, blk, 0, st, V, ldv, m, S, nev, nn, evecs);
+        hipLaunchKernelGGL(kvb::k_ritz, dim3(rows_grid.x, (nev + kvb::RITZ_VECS - 1) / kvb::RITZ_VECS), blk, 0, st, V, ldv, m, S, nev, nn, evecs);
         KVB_HIP(ctx, hipGetLastError());
         KVB_HIP(ctx, hipStreamSynchronize(st));
     }
