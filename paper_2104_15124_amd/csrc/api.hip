@@ -292,7 +292,7 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                 float* tree = cv.take<float>(size_t(std::max(tl.nodes, 1)) * 2 * kvb::PR_DIMS);
                 float* sbox = cv.take<float>(size_t(csb) * 2 * kvb::PR_DIMS);
                 void* sort_tmp = cv.take<char>(csort);
-                KVB_HIP(ctx, kvb::launch_colmean(X, nn, m, colpart, colblocks, mu, ctx->stream));
+                KVB_HIP(ctx, kvb::launch_colmean(X, nn, m, colpart, colblocks, Aq, mu, ctx->stream));
                 KVB_HIP(ctx, kvb::launch_principal_basis(X, nn, m, mu, covpart, C, P, ctx->stream));
                 KVB_HIP(ctx, kvb::launch_curve_order(X, nn, m, mu, P, z, zpart, code, scode, vals, order, sort_tmp,
                                                      csort, pos, cid, zs, tbox, sbox, tree, ctx->curve_order == 2,

@@ -42,7 +42,10 @@ namespace kvb {
 // m <= 256 the block's threads form T = 256 / m row lanes of m columns: thread
 // (j, c) sums column c over rows r0 + j, r0 + j + T, ... (consecutive threads
 // read consecutive columns of a row), and the T partial sums of a column are
-// added in the order j = 0, 1, ... . Wider rows: one thread per column.
+// added in the order j = 0, 1, ... . Wider rows: one thread per column. Bound
+// by the chain of loads of a block's rows: eight are in flight, and a block
+// takes 128 rows up to 1024 blocks (4096 rows per block left 8 blocks at n =
+// 30k, 1.0 ms for m = 200, 0.02 now; 0.97 -> 0.38 ms at n = 4M, m = 128).
 __global__ __launch_bounds__(256) void k_colsum_partial(const float* __restrict__ X, int n, int m, int rows_per_block,
                                                         double* __restrict__ part)
 {
@@ -53,8 +56,10 @@ __global__ __launch_bounds__(256) void k_colsum_partial(const float* __restrict_
         const int T = 256 / m;
         const int j = threadIdx.x / m, c = threadIdx.x % m;
         double s = 0.0;
-        if (j < T)
+        if (j < T) {
+#pragma unroll 8
             for (int r = r0 + j; r < r1; r += T) s += static_cast<double>(X[static_cast<size_t>(r) * m + c]);
+        }
         s_part[threadIdx.x] = s;
         __syncthreads();
         if (threadIdx.x < m) {
@@ -66,38 +71,22 @@ __global__ __launch_bounds__(256) void k_colsum_partial(const float* __restrict_
     }
     for (int c = threadIdx.x; c < m; c += blockDim.x) {
         double s = 0.0;
+#pragma unroll 8
         for (int r = r0; r < r1; ++r) s += static_cast<double>(X[static_cast<size_t>(r) * m + c]);
         part[static_cast<size_t>(blockIdx.x) * m + c] = s;
     }
 }
 
-// The block partials of each column added in a fixed order: for m <= 256,
-// thread (j, c) sums the partials j, j + T, ... of column c, and the T sums
-// are added in the order j = 0, 1, ... .
-__global__ __launch_bounds__(256) void k_colsum_finish(const double* __restrict__ part, int nb, int m, int n,
-                                                       double* __restrict__ mu)
+// The block partials of each column added in a fixed order, one wavefront per column.
+__global__ __launch_bounds__(WAVE) void k_colsum_finish(const double* __restrict__ part, int nb, int m, int n,
+                                                        double* __restrict__ mu)
 {
-    __shared__ double s_part[256];
-    if (m <= 256) {
-        const int T = 256 / m;
-        const int j = threadIdx.x / m, c = threadIdx.x % m;
-        double s = 0.0;
-        if (j < T)
-            for (int b = j; b < nb; b += T) s += part[static_cast<size_t>(b) * m + c];
-        s_part[threadIdx.x] = s;
-        __syncthreads();
-        if (threadIdx.x < m) {
-            double t = 0.0;
-            for (int q = 0; q < T; ++q) t += s_part[q * m + threadIdx.x];
-            mu[threadIdx.x] = t / static_cast<double>(n);
-        }
-        return;
-    }
-    for (int c = threadIdx.x; c < m; c += blockDim.x) {
-        double s = 0.0;
-        for (int b = 0; b < nb; ++b) s += part[static_cast<size_t>(b) * m + c];
-        mu[c] = s / static_cast<double>(n);
-    }
+    const int c = blockIdx.x;
+    double s = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += WAVE) s += part[static_cast<size_t>(b) * m + c];
+    s = wave_sum_f64(s);
+    if (threadIdx.x == 0) mu[c] = s / static_cast<double>(n);
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
@@ -921,11 +910,17 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
 }
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_colmean(const float* X, int n, int m, double* colpart, int colblocks, double* mu, hipStream_t st)
+// The block partials go to colpart while they fit its colblocks rows, else (n >
+// 128) to `room`: the query operand's n rows of at least 2 m bytes, written
+// later, hold the ceil(n / 128) rows of 8 m bytes.
+hipError_t launch_colmean(const float* X, int n, int m, double* colpart, int colblocks, void* room, double* mu,
+                          hipStream_t st)
 {
-    const int rpb = (n + colblocks - 1) / colblocks;
-    hipLaunchKernelGGL(k_colsum_partial, dim3(colblocks), dim3(256), 0, st, X, n, m, rpb, colpart);
-    hipLaunchKernelGGL(k_colsum_finish, dim3(1), dim3(256), 0, st, colpart, colblocks, m, n, mu);
+    const int nb = std::max(1, std::min(1024, (n + 127) / 128));
+    const int rpb = (n + nb - 1) / nb;
+    double* part = nb > colblocks ? static_cast<double*>(room) : colpart;
+    hipLaunchKernelGGL(k_colsum_partial, dim3(nb), dim3(256), 0, st, X, n, m, rpb, part);
+    hipLaunchKernelGGL(k_colsum_finish, dim3(m), dim3(WAVE), 0, st, part, nb, m, n, mu);
     return hipGetLastError();
 }
 
@@ -963,11 +958,10 @@ hipError_t launch_prep(const float* X, int n, int m, int split, int kpad, double
                        double* mu, void* Aq, void* Bc, float* ynorm2, unsigned* rmax_bits, const int* brow,
                        const int* arow, hipStream_t st)
 {
-    const int rpb = (n + colblocks - 1) / colblocks;
     // with a row map the padding rows of the last tile are filled separately
     const int npad = brow ? n : (n + 31) / 32 * 32;
-    hipLaunchKernelGGL(k_colsum_partial, dim3(colblocks), dim3(256), 0, st, X, n, m, rpb, colpart);
-    hipLaunchKernelGGL(k_colsum_finish, dim3(1), dim3(256), 0, st, colpart, colblocks, m, n, mu);
+    const hipError_t e = launch_colmean(X, n, m, colpart, colblocks, Aq, mu, st);
+    if (e != hipSuccess) return e;
     launch_rows(X, n, npad, m, mu, split, kpad, Aq, Bc, ynorm2, rmax_bits, brow, arow, st);
     return hipGetLastError();
 }

@@ -107,7 +107,8 @@ hipError_t launch_exact_rows(const float* X, int n, int m, int k, const int* row
 hipError_t launch_prep(const float* X, int n, int m, int split, int kpad, double* colpart, int colblocks,
                        double* mu, void* Aq, void* Bc, float* ynorm2, unsigned* rmax_bits, const int* brow,
                        const int* arow, hipStream_t st);
-hipError_t launch_colmean(const float* X, int n, int m, double* colpart, int colblocks, double* mu, hipStream_t st);
+hipError_t launch_colmean(const float* X, int n, int m, double* colpart, int colblocks, void* room, double* mu,
+                          hipStream_t st);
 hipError_t launch_prep_rows(const float* X, int n, int m, const double* mu, int split, int kpad, void* Aq, void* Bc,
                             float* ynorm2, unsigned* rmax_bits, const int* brow, const int* arow, hipStream_t st);
 // the operands in curve order: operand row p from Xs[p], the curve-ordered copy

@@ -20,8 +20,6 @@
 
 namespace kvb {
 
-constexpr int COV_ROWS = 32;      // rows staged per step
-constexpr int COV_ENTRIES = 2048; // covariance entries per block (8 per thread)
 constexpr int COV_SAMPLE = 32768; // rows sampled for the covariance
 
 __device__ __forceinline__ void tri_index(int e, int m, int& a, int& b)
@@ -36,52 +34,79 @@ __device__ __forceinline__ void tri_index(int e, int m, int& a, int& b)
     b = a + rem;
 }
 
-// Partial sums of y y^T over the sampled rows (every `stride`-th row), y = x - mu,
-// for the entries chunk blockIdx.y of the upper triangle.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// Partial sums of y y^T over the sampled rows (every `stride`-th row), y = x - mu:
+// part[b] holds block b's sums over the upper triangle, row by row. One
+// workgroup per 32 x 32 tile of the triangle and row block; its wavefronts take
+// a quarter of the rows each, four rows per v_mfma_f64_16x16x4f64 (lane l: row
+// l / 16, coordinate l % 16 of each operand; result register r of lane l: row
+// 4 r + l / 16, column l % 16), and are added in order through LDS. Two LDS
+// reads per product on the vector ALUs took 0.41 ms for 30k rows of m = 200, 0.08
+// now (0.20 and 0.06 at m = 64).
+constexpr int COV_TILE = 32;
 __global__ __launch_bounds__(256) void k_cov_partial(const float* __restrict__ X, int n, int m,
                                                      const double* __restrict__ mu, int stride, int rows_per_block,
                                                      double* __restrict__ part)
 {
-    __shared__ float sy[COV_ROWS][256 + 1];
-    const int ntri = m * (m + 1) / 2;
-    const int e0 = blockIdx.y * COV_ENTRIES;
-    int ea[8], eb[8];
-    double acc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int e = e0 + threadIdx.x + 256 * u;
-        acc[u] = 0.0;
-        ea[u] = -1;
-        eb[u] = 0;
-        if (e < ntri) tri_index(e, m, ea[u], eb[u]);
-    }
-    const int s_begin = blockIdx.x * rows_per_block;
+    __shared__ double s_acc[3][COV_TILE * COV_TILE];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    // tile blockIdx.y of the upper triangle of tiles
+    int ti, tj;
+    tri_index(blockIdx.y, (m + COV_TILE - 1) / COV_TILE, ti, tj);
     const int nsample = (n + stride - 1) / stride;
-    const int s_end = min(nsample, s_begin + rows_per_block);
-    for (int s0 = s_begin; s0 < s_end; s0 += COV_ROWS) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < COV_ROWS * m; t += 256) {
-            const int r = t / m, c = t % m;
-            const int srow = s0 + r;
-            sy[r][c] = srow < s_end
-                           ? static_cast<float>(static_cast<double>(X[static_cast<size_t>(srow) * stride * m + c]) - mu[c])
-                           : 0.f;
-        }
-        __syncthreads();
+    const int b0 = blockIdx.x * rows_per_block, b1 = min(nsample, b0 + rows_per_block);
+    const int q = (max(0, b1 - b0) + 3) / 4;
+    const int r0 = b0 + wave * q, r1 = min(b1, r0 + q);
+    const int c = lane & 15, k = lane >> 4;
+    int ci[2], cj[2];
+    double mi[2], mj[2];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (ea[u] < 0) continue;
-            double a = 0.0;
-            for (int r = 0; r < COV_ROWS; ++r)
-                a += static_cast<double>(sy[r][ea[u]]) * static_cast<double>(sy[r][eb[u]]);
-            acc[u] += a;
-        }
+    for (int u = 0; u < 2; ++u) {
+        ci[u] = ti * COV_TILE + 16 * u + c;
+        cj[u] = tj * COV_TILE + 16 * u + c;
+        mi[u] = ci[u] < m ? mu[ci[u]] : 0.0;
+        mj[u] = cj[u] < m ? mu[cj[u]] : 0.0;
     }
+    f64x4 acc[2][2] = {};
+    for (int r = r0; r < r1; r += 4) {
+        const bool ok = r + k < r1;
+        const float* x = X + static_cast<size_t>(ok ? r + k : r) * stride * m;
+        double a[2], b[2];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int e = e0 + threadIdx.x + 256 * u;
-        if (e < ntri) part[static_cast<size_t>(blockIdx.x) * ntri + e] = acc[u];
+        for (int u = 0; u < 2; ++u) {
+            const float xi = ci[u] < m ? x[ci[u]] : 0.f, xj = cj[u] < m ? x[cj[u]] : 0.f;
+            a[u] = ok ? static_cast<double>(static_cast<float>(static_cast<double>(xi) - mi[u])) : 0.0;
+            b[u] = ok ? static_cast<double>(static_cast<float>(static_cast<double>(xj) - mj[u])) : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
     }
+    if (wave > 0)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    s_acc[wave - 1][(16 * u + 4 * r + k) * COV_TILE + 16 * v + c] = acc[u][v][r];
+    __syncthreads();
+    if (wave > 0) return;
+    const int ntri = m * (m + 1) / 2;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int li = 16 * u + 4 * r + k, lj = 16 * v + c;
+                const int i = ti * COV_TILE + li, j = tj * COV_TILE + lj, e = li * COV_TILE + lj;
+                if (i <= j && j < m)
+                    part[static_cast<size_t>(blockIdx.x) * ntri + static_cast<size_t>(i) * m - i * (i - 1) / 2 + (j - i)] =
+                        ((acc[u][v][r] + s_acc[0][e]) + s_acc[1][e]) + s_acc[2][e];
+            }
 }
 
 __global__ __launch_bounds__(256) void k_cov_reduce(const double* __restrict__ part, int nparts, int m,
@@ -91,6 +116,7 @@ __global__ __launch_bounds__(256) void k_cov_reduce(const double* __restrict__ p
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= ntri) return;
     double s = 0.0;
+#pragma unroll 8
     for (int b = 0; b < nparts; ++b) s += part[static_cast<size_t>(b) * ntri + e];
     int a, b;
     tri_index(e, m, a, b);
@@ -99,116 +125,192 @@ __global__ __launch_bounds__(256) void k_cov_reduce(const double* __restrict__ p
 }
 
 // Subspace iteration for the top PR eigenvectors of the covariance C (one
-// block): V <- orthonormalise(C V) from a fixed full-rank starting basis. The
-// product uses the whole block; modified Gram-Schmidt runs in the first
-// wavefront (float64, wavefront reductions in a fixed order). Columns of
-// negligible norm (a covariance of rank below PR) are set to zero, so the
-// nonzero columns of P stay orthonormal.
-__global__ __launch_bounds__(256) void k_subspace(const double* __restrict__ C, int m, int iters,
-                                                  float* __restrict__ P)
+// block): V <- orthonormalise(C V) from a fixed full-rank starting basis.
+// Bound by latency (one compute unit, iters dependent rounds), so each round
+// is wide: the product takes all threads, thread (g, a) the rows b = g, g + G,
+// ... of the symmetric C for output row a (consecutive threads read
+// consecutive columns), and the modified Gram-Schmidt gives each column a
+// wavefront that holds it in registers: one barrier per column, in which the
+// later columns drop their part along it. The last round orthogonalises twice
+// (rounding level); before it once is enough. Columns of negligible norm (a
+// covariance of rank below PR) are set to zero, so the nonzero columns of P
+// stay orthonormal. One wavefront orthogonalising all columns twice per round
+// and one thread forming the Gram matrix: 0.48 ms at m = 16, 0.89 at 64, 3.8 at
+// 200; 0.11, 0.13 and 0.35 now.
+constexpr int SUB_THREADS = WAVE * PR_DIMS;
+__global__ __launch_bounds__(SUB_THREADS) void k_subspace(const double* __restrict__ C, int m, int iters,
+                                                          float* __restrict__ P)
 {
+    constexpr int CV = 256 / WAVE;   // a column's values per lane
     __shared__ double V[256 * PR_DIMS];
-    __shared__ double W[256 * PR_DIMS];
-    for (int t = threadIdx.x; t < m * PR_DIMS; t += 256) {
-        const int a = t / PR_DIMS, j = t % PR_DIMS;
-        W[t] = (a % PR_DIMS == j ? 1.0 : 0.0) + 1e-3 * static_cast<double>((a * 7 + j * 13) % 17) / 17.0;
-    }
-    __syncthreads();
+    __shared__ double part[SUB_THREADS * PR_DIMS];   // [g][a][j]
+    __shared__ double s_q[2][256];
+    __shared__ double s_row[PR_DIMS];
+    const int tid = threadIdx.x, lane = lane_id(), j = __builtin_amdgcn_readfirstlane(tid >> 6);   // this wavefront's column
+    const int G = SUB_THREADS / m;
+    const int g = tid / m, a = tid % m;
     double trace = 0.0;
-    for (int a = 0; a < m; ++a) trace += C[static_cast<size_t>(a) * m + a];
+    for (int q = lane; q < m; q += WAVE) trace += C[static_cast<size_t>(q) * m + q];
+    trace = wave_sum_f64(trace);
     const double tiny = 1e-24 * (trace > 0.0 ? trace * trace : 1.0);
+    double w[CV];
+#pragma unroll
+    for (int u = 0; u < CV; ++u) {
+        const int r = lane + u * WAVE;
+        w[u] = r < m ? (r % PR_DIMS == j ? 1.0 : 0.0) + 1e-3 * static_cast<double>((r * 7 + j * 13) % 17) / 17.0 : 0.0;
+    }
     for (int it = 0; it <= iters; ++it) {
         if (it > 0) {
-            for (int t = threadIdx.x; t < m * PR_DIMS; t += 256) {
-                const int a = t / PR_DIMS, j = t % PR_DIMS;
-                double s = 0.0;
-                for (int b = 0; b < m; ++b) s += C[static_cast<size_t>(a) * m + b] * V[b * PR_DIMS + j];
-                W[t] = s;
+            if (g < G) {
+                double acc[PR_DIMS] = {};
+#pragma unroll 4
+                for (int b = g; b < m; b += G) {
+                    const double c = C[static_cast<size_t>(b) * m + a];
+#pragma unroll
+                    for (int q = 0; q < PR_DIMS; ++q) acc[q] += c * V[b * PR_DIMS + q];
+                }
+#pragma unroll
+                for (int q = 0; q < PR_DIMS; ++q) part[(g * m + a) * PR_DIMS + q] = acc[q];
             }
             __syncthreads();
-        }
-        if (threadIdx.x < WAVE) {
-            const int lane = threadIdx.x;
-            // Gram-Schmidt twice keeps the columns orthonormal to rounding level
-            for (int pass = 0; pass < 2; ++pass)
-            for (int j = 0; j < PR_DIMS; ++j) {
-                for (int l = 0; l < j; ++l) {
-                    double d = 0.0;
-                    for (int a = lane; a < m; a += WAVE) d += W[a * PR_DIMS + j] * W[a * PR_DIMS + l];
-                    d = wave_sum_f64(d);
-                    for (int a = lane; a < m; a += WAVE) W[a * PR_DIMS + j] -= d * W[a * PR_DIMS + l];
-                }
-                double nn = 0.0;
-                for (int a = lane; a < m; a += WAVE) nn += W[a * PR_DIMS + j] * W[a * PR_DIMS + j];
-                nn = wave_sum_f64(nn);
-                const double inv = (pass == 1 || nn > (it == 0 ? 1e-24 : tiny)) && nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
-                for (int a = lane; a < m; a += WAVE) W[a * PR_DIMS + j] *= inv;
+#pragma unroll
+            for (int u = 0; u < CV; ++u) {
+                const int r = lane + u * WAVE;
+                double s = 0.0;
+                if (r < m)
+                    for (int q = 0; q < G; ++q) s += part[(q * m + r) * PR_DIMS + j];
+                w[u] = s;
             }
         }
-        __syncthreads();
-        for (int t = threadIdx.x; t < m * PR_DIMS; t += 256) V[t] = W[t];
+        for (int pass = 0; pass < (it == iters ? 2 : 1); ++pass) {
+#pragma unroll
+            for (int c = 0; c < PR_DIMS; ++c) {
+                if (j == c) {
+                    double nn = 0.0;
+#pragma unroll
+                    for (int u = 0; u < CV; ++u) nn += w[u] * w[u];
+                    nn = wave_sum_f64(nn);
+                    const double inv = (pass == 1 || nn > (it == 0 ? 1e-24 : tiny)) && nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+#pragma unroll
+                    for (int u = 0; u < CV; ++u) {
+                        w[u] *= inv;
+                        s_q[c & 1][lane + u * WAVE] = w[u];
+                    }
+                }
+                __syncthreads();   // two buffers: the next column writes the other one
+                if (j > c) {
+                    double d = 0.0;
+#pragma unroll
+                    for (int u = 0; u < CV; ++u) d += w[u] * s_q[c & 1][lane + u * WAVE];
+                    d = wave_sum_f64(d);
+#pragma unroll
+                    for (int u = 0; u < CV; ++u) w[u] -= d * s_q[c & 1][lane + u * WAVE];
+                }
+            }
+        }
+        if (it == iters) {
+            // the float32 basis, also in LDS for its Gram matrix
+#pragma unroll
+            for (int u = 0; u < CV; ++u) {
+                const float f = static_cast<float>(w[u]);
+                w[u] = static_cast<double>(f);
+                if (lane + u * WAVE < m) P[(lane + u * WAVE) * PR_DIMS + j] = f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < CV; ++u) V[(lane + u * WAVE) * PR_DIMS + j] = w[u];
         __syncthreads();
     }
-    for (int t = threadIdx.x; t < m * PR_DIMS; t += 256) P[t] = static_cast<float>(V[t]);
-    __syncthreads();
     // |P^T v|^2 <= lambda_max(P P^T) |v|^2 = lambda_max(P^T P) |v|^2, and the
     // largest eigenvalue of the Gram matrix G = P^T P of the float32 basis is at
     // most its largest absolute row sum: pscale = 1 / sqrt(that), rounded down
-    if (threadIdx.x == 0) {
+    double row = 0.0;
+#pragma unroll
+    for (int l = 0; l < PR_DIMS; ++l) {
+        double d = 0.0;
+#pragma unroll
+        for (int u = 0; u < CV; ++u) d += w[u] * V[(lane + u * WAVE) * PR_DIMS + l];
+        row += fabs(wave_sum_f64(d));
+    }
+    if (lane == 0) s_row[j] = row;
+    __syncthreads();
+    if (tid == 0) {
         double rmax = 0.0;
-        for (int j = 0; j < PR_DIMS; ++j) {
-            double row = 0.0;
-            for (int l = 0; l < PR_DIMS; ++l) {
-                double g = 0.0;
-                for (int a = 0; a < m; ++a)
-                    g += static_cast<double>(P[a * PR_DIMS + j]) * static_cast<double>(P[a * PR_DIMS + l]);
-                row += fabs(g);
-            }
-            rmax = fmax(rmax, row);
-        }
+        for (int l = 0; l < PR_DIMS; ++l) rmax = fmax(rmax, s_row[l]);
         P[m * PR_DIMS] = rmax > 0.0 ? static_cast<float>((1.0 - 1e-6) / sqrt(rmax * (1.0 + 1e-9))) : 1.f;
     }
 }
 
-// z_i = P^T y_i (float32, y = x - mu as in the operands), one thread per row;
-// per-block minima / maxima of the first PCODE coordinates for the code range.
+// z_i = P^T y_i (float32, y = x - mu as in the operands) and the per-block
+// minima / maxima of the first PCODE coordinates for the code range. Bound by
+// reading X once: 16 lanes per row (64-byte pieces of it), lane l the
+// coordinates l, l + 16, ... (NJ of them) with their rows of P in registers
+// over the block's 256 rows; the 8 sums are added over the lanes by halving
+// (8 exchanges instead of 32). One thread per row read 64 rows m apart at a
+// time: 0.90 ms at n = 1M, m = 64 and 8.6 ms at n = 4M, m = 128; 0.14 and
+// 1.27 ms now.
+template <int NJ>
 __global__ __launch_bounds__(256) void k_project(const float* __restrict__ X, int n, int m,
                                                  const double* __restrict__ mu, const float* __restrict__ P,
                                                  float* __restrict__ z, float* __restrict__ zpart)
 {
-    __shared__ float slo[PCODE_DIMS][256], shi[PCODE_DIMS][256];
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    float zc[PR_DIMS];
+    static_assert(PR_DIMS == 8 && PCODE_DIMS == 4, "the exchanges below halve 8 sums");
+    __shared__ float s_lo[4][PCODE_DIMS], s_hi[4][PCODE_DIMS];
+    const int lane = lane_id(), sub = threadIdx.x % 16, grp = threadIdx.x / 16;
+    float p[NJ][PR_DIMS];
+    double mj[NJ];
 #pragma unroll
-    for (int c = 0; c < PR_DIMS; ++c) zc[c] = 0.f;
-    if (i < n) {
-        const float* x = X + static_cast<size_t>(i) * m;
-        for (int k = 0; k < m; ++k) {
-            const float y = static_cast<float>(static_cast<double>(x[k]) - mu[k]);
+    for (int q = 0; q < NJ; ++q) {
+        const int k = sub + 16 * q;
+        mj[q] = k < m ? mu[k] : 0.0;
 #pragma unroll
-            for (int c = 0; c < PR_DIMS; ++c) zc[c] = fmaf(y, P[k * PR_DIMS + c], zc[c]);
+        for (int c = 0; c < PR_DIMS; ++c) p[q][c] = k < m ? P[k * PR_DIMS + c] : 0.f;
+    }
+    const bool b3 = sub & 8, b0 = sub & 1, b1 = sub & 2;
+    const int cc = (b3 ? 4 : 0) + (b0 ? 2 : 0) + (b1 ? 1 : 0);   // the sum this lane ends with
+    float lo = __uint_as_float(0x7F800000u), hi = -lo;
+#pragma unroll 2
+    for (int t = 0; t < 16; ++t) {
+        const int i = blockIdx.x * 256 + grp + 16 * t;
+        const float* x = X + static_cast<size_t>(min(i, n - 1)) * m;
+        float xv[NJ];
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) xv[q] = sub + 16 * q < m ? x[sub + 16 * q] : 0.f;
+        float s[PR_DIMS] = {};
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {
+            const float y = static_cast<float>(static_cast<double>(xv[q]) - mj[q]);
+#pragma unroll
+            for (int c = 0; c < PR_DIMS; ++c) s[c] = fmaf(y, p[q][c], s[c]);
         }
+        float h[4], g[2], f;
 #pragma unroll
-        for (int c = 0; c < PR_DIMS; ++c) z[static_cast<size_t>(i) * PR_DIMS + c] = zc[c];
+        for (int c = 0; c < 4; ++c) h[c] = (b3 ? s[4 + c] : s[c]) + shfl_xor_f32(b3 ? s[c] : s[4 + c], 8);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) g[c] = (b0 ? h[2 + c] : h[c]) + shfl_xor_f32(b0 ? h[c] : h[2 + c], 1);
+        f = (b1 ? g[1] : g[0]) + shfl_xor_f32(b1 ? g[0] : g[1], 2);
+        f += shfl_xor_f32(f, 4);
+        if (i < n) {
+            if (!(sub & 4)) z[static_cast<size_t>(i) * PR_DIMS + cc] = f;
+            lo = fminf(lo, f);
+            hi = fmaxf(hi, f);
+        }
     }
 #pragma unroll
-    for (int c = 0; c < PCODE_DIMS; ++c) {
-        slo[c][threadIdx.x] = i < n ? zc[c] : __uint_as_float(0x7F800000u);
-        shi[c][threadIdx.x] = i < n ? zc[c] : -__uint_as_float(0x7F800000u);
+    for (int o = 16; o < WAVE; o <<= 1) {
+        lo = fminf(lo, shfl_xor_f32(lo, o));
+        hi = fmaxf(hi, shfl_xor_f32(hi, o));
+    }
+    if (lane < 16 && !(sub & 4) && cc < PCODE_DIMS) {
+        s_lo[threadIdx.x >> 6][cc] = lo;
+        s_hi[threadIdx.x >> 6][cc] = hi;
     }
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o)
-#pragma unroll
-            for (int c = 0; c < PCODE_DIMS; ++c) {
-                slo[c][threadIdx.x] = fminf(slo[c][threadIdx.x], slo[c][threadIdx.x + o]);
-                shi[c][threadIdx.x] = fmaxf(shi[c][threadIdx.x], shi[c][threadIdx.x + o]);
-            }
-        __syncthreads();
-    }
     if (threadIdx.x < PCODE_DIMS) {
-        zpart[static_cast<size_t>(blockIdx.x) * 2 * PCODE_DIMS + threadIdx.x] = slo[threadIdx.x][0];
-        zpart[static_cast<size_t>(blockIdx.x) * 2 * PCODE_DIMS + PCODE_DIMS + threadIdx.x] = shi[threadIdx.x][0];
+        const int c = threadIdx.x;
+        float* out = zpart + static_cast<size_t>(blockIdx.x) * 2 * PCODE_DIMS;
+        out[c] = fminf(fminf(s_lo[0][c], s_lo[1][c]), fminf(s_lo[2][c], s_lo[3][c]));
+        out[PCODE_DIMS + c] = fmaxf(fmaxf(s_hi[0][c], s_hi[1][c]), fmaxf(s_hi[2][c], s_hi[3][c]));
     }
 }
 
@@ -663,7 +765,6 @@ __global__ __launch_bounds__(KG_THREADS) void k_kd_group(const int32_t* __restri
 
 // ------------------------------------------------------------------ launchers
 int cov_partials() { return 32; }
-int cov_chunks(int m) { return (m * (m + 1) / 2 + COV_ENTRIES - 1) / COV_ENTRIES; }
 int project_blocks(int n) { return (n + 255) / 256; }
 
 hipError_t launch_principal_basis(const float* X, int n, int m, const double* mu, double* part, double* C, float* P,
@@ -674,10 +775,11 @@ hipError_t launch_principal_basis(const float* X, int n, int m, const double* mu
     const int nsample = (n + stride - 1) / stride;
     const int nb = cov_partials();
     const int rpb = (nsample + nb - 1) / nb;
-    hipLaunchKernelGGL(k_cov_partial, dim3(nb, cov_chunks(m)), dim3(256), 0, st, X, n, m, mu, stride, rpb, part);
+    const int ct = (m + COV_TILE - 1) / COV_TILE;
+    hipLaunchKernelGGL(k_cov_partial, dim3(nb, ct * (ct + 1) / 2), dim3(256), 0, st, X, n, m, mu, stride, rpb, part);
     const int ntri = m * (m + 1) / 2;
     hipLaunchKernelGGL(k_cov_reduce, dim3((ntri + 255) / 256), dim3(256), 0, st, part, nb, m, C);
-    hipLaunchKernelGGL(k_subspace, dim3(1), dim3(256), 0, st, C, m, 20, P);
+    hipLaunchKernelGGL(k_subspace, dim3(1), dim3(SUB_THREADS), 0, st, C, m, 20, P);
     return hipGetLastError();
 }
 
@@ -687,7 +789,13 @@ hipError_t launch_curve_order(const float* X, int n, int m, const double* mu, co
                               float* tree, bool median_splits, hipStream_t st)
 {
     const int nb = project_blocks(n);
-    hipLaunchKernelGGL(k_project, dim3(nb), dim3(256), 0, st, X, n, m, mu, P, z, zpart);
+    auto project = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, st, X, n, m, mu, P, z, zpart); };
+    if (m > 256) return hipErrorInvalidValue;
+    m <= 16    ? project(k_project<1>)
+    : m <= 32  ? project(k_project<2>)
+    : m <= 64  ? project(k_project<4>)
+    : m <= 128 ? project(k_project<8>)
+               : project(k_project<16>);
     float* zr = zpart + static_cast<size_t>(nb) * 2 * PCODE_DIMS;   // one more partial's room
     hipLaunchKernelGGL(k_zrange, dim3(1), dim3(256), 0, st, zpart, nb, zr);
     hipLaunchKernelGGL(k_zcodes, dim3(nb), dim3(256), 0, st, z, n, zr, code, vals);
