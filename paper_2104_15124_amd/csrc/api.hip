@@ -206,7 +206,6 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
     const bool curve = !direct && ctx->curve_order && m <= 256;
     const int npad32 = (nn + 31) / 32 * 32, ctiles = npad32 / 32;
     const kvb::TreeLayout tl = kvb::tree_layout(ctiles);
-    const int csb = (ctiles + kvb::SB_TILES_MFMA - 1) / kvb::SB_TILES_MFMA;
     const size_t ntri = size_t(m) * (m + 1) / 2;
     size_t csort = 0;
     if (curve) {
@@ -219,7 +218,7 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                 round256(size_t(npad32) * sizeof(int32_t)) + round256(size_t(npad32) * kvb::PR_DIMS * sizeof(float)) +
                 round256(size_t(ctiles) * 2 * kvb::PR_DIMS * sizeof(float)) +
                 round256(size_t(std::max(tl.nodes, 1)) * 2 * kvb::PR_DIMS * sizeof(float)) +
-                round256(size_t(csb) * 2 * kvb::PR_DIMS * sizeof(float)) + round256(csort) +
+                round256(csort) +
                 round256(size_t(nn) * m * sizeof(float)) + 512;
     }
     int rc = ensure_scratch(ctx, base + need);
@@ -290,13 +289,11 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                 float* zs = cv.take<float>(size_t(npad32) * kvb::PR_DIMS);
                 float* tbox = cv.take<float>(size_t(ctiles) * 2 * kvb::PR_DIMS);
                 float* tree = cv.take<float>(size_t(std::max(tl.nodes, 1)) * 2 * kvb::PR_DIMS);
-                float* sbox = cv.take<float>(size_t(csb) * 2 * kvb::PR_DIMS);
                 void* sort_tmp = cv.take<char>(csort);
                 KVB_HIP(ctx, kvb::launch_colmean(X, nn, m, colpart, colblocks, Aq, mu, ctx->stream));
                 KVB_HIP(ctx, kvb::launch_principal_basis(X, nn, m, mu, covpart, C, P, ctx->stream));
                 KVB_HIP(ctx, kvb::launch_curve_order(X, nn, m, mu, P, z, zpart, code, scode, vals, order, sort_tmp,
-                                                     csort, pos, cid, zs, tbox, sbox, tree, ctx->curve_order == 2,
-                                                     ctx->stream));
+                                                     csort, pos, cid, zs, tbox, tree, ctx->curve_order == 2, ctx->stream));
                 // curve-ordered copy of the samples for the refine step
                 Xs = cv.take<float>(size_t(nn) * m);
                 KVB_HIP(ctx, kvb::launch_gather_rows(X, nn, m, cid, Xs, ctx->stream));
@@ -311,7 +308,6 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                 crv.perm = cid;
                 crv.zs = zs;
                 crv.tbox = tbox;
-                crv.sbox = sbox;
                 crv.tree = tree;
                 crv.layout = tl;
                 crv.pscale = P + size_t(m) * kvb::PR_DIMS;
@@ -337,12 +333,12 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
         em.center = 1.01 * u;
         {
             Prof pr(ctx, KVB_PROF_KNN_SELECT);
-            if (curve && kvb::select_tree_fits(split, kpad))
+            if (curve)
                 KVB_HIP(ctx, kvb::launch_select_tree(split, Aq, Bc, nn, kpad, kp, ynorm2, rmax, em, keys, cap, slast,
                                                      crv, ctx->pairs_dev, ctx->stream));
             else
                 KVB_HIP(ctx, kvb::launch_select_mfma(split, Aq, Bc, nn, kpad, kp, ynorm2, rmax, em, keys, cap, slast,
-                                                     nullptr, 0, curve ? &crv : nullptr, ctx->pairs_dev, ctx->stream));
+                                                     nullptr, 0, ctx->pairs_dev, ctx->stream));
         }
         kstride = cap;
     }

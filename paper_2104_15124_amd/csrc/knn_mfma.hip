@@ -322,149 +322,6 @@ __global__ __launch_bounds__(256) void k_prep_rows_thread(const float* __restric
 }
 
 // ------------------------------------------------------------------ select
-// Curve-order scan: the own tile, then alternately outward to the right and
-// to the left, skipping what lies beyond the workgroup's current threshold.
-// Picking the next tile is a ballot over a window of 64 tiles whose bounds to
-// the workgroup's box (bw) and to this wavefront's box (ww) one load gave
-// every lane. Before a new tile window is loaded, a window of 64 superblock
-// bounds (SB_TILES_MFMA tiles each, also one load) moves the scan past the
-// superblocks beyond reach, so sparse scans do not load tile windows of
-// tiles that are all far away. The scan state is the same in every wavefront
-// of the workgroup.
-struct CurveScan {
-    int cur_r, cur_l;     // next candidate tile on each side
-    int rt0, lt0;         // tile windows: lane l is tile rt0 + l / lt0 - l
-    int rsb0, lsb0;       // superblock windows: lane l is superblock rsb0 + l / lsb0 - l
-    bool go_right;
-    float rbw, rww, lbw, lww;   // tile bounds
-    float rsbw, lsbw;           // superblock bounds (workgroup box)
-
-    __device__ __forceinline__ void init(int own_t)
-    {
-        cur_r = own_t;
-        cur_l = own_t - 1;
-        rt0 = lt0 = rsb0 = lsb0 = -4 * WAVE;
-        go_right = true;
-        rbw = rww = lbw = lww = rsbw = lsbw = 0.f;
-    }
-
-    __device__ __forceinline__ static void load_box(const float* __restrict__ src_f, float (&b)[2 * PR_DIMS])
-    {
-        const float4* src = reinterpret_cast<const float4*>(src_f);
-#pragma unroll
-        for (int v = 0; v < PR_DIMS / 2; ++v) {
-            const float4 q = src[v];
-            b[4 * v] = q.x;
-            b[4 * v + 1] = q.y;
-            b[4 * v + 2] = q.z;
-            b[4 * v + 3] = q.w;
-        }
-    }
-
-    // bounds of tile t (NaN: no such tile, never within reach; -inf: own tile)
-    __device__ __forceinline__ static void tile_window(int t, int own_t, int tend, const CurveArgs& crv,
-                                                       const float* qlo, const float* qhi, const float* wlo,
-                                                       const float* whi, const BoxBound& bb, float& bw, float& ww)
-    {
-        bw = __uint_as_float(0x7FC00000u);
-        ww = bw;
-        if (t < 0 || t >= tend) return;
-        if (t == own_t) {
-            bw = -__uint_as_float(0x7F800000u);
-            ww = bw;
-            return;
-        }
-        float b[2 * PR_DIMS];
-        load_box(crv.tbox + static_cast<size_t>(t) * 2 * PR_DIMS, b);
-        bw = box_bound(b, qlo, qhi, bb);
-        ww = box_bound(b, wlo, whi, bb);
-    }
-
-    // bound of superblock sb (NaN: none; -inf: the own tile's)
-    __device__ __forceinline__ static float sb_window(int sb, int own_sb, int nsb, const CurveArgs& crv,
-                                                      const float* qlo, const float* qhi, const BoxBound& bb)
-    {
-        if (sb < 0 || sb >= nsb) return __uint_as_float(0x7FC00000u);
-        if (sb == own_sb) return -__uint_as_float(0x7F800000u);
-        float b[2 * PR_DIMS];
-        load_box(crv.sbox + static_cast<size_t>(sb) * 2 * PR_DIMS, b);
-        return box_bound(b, qlo, qhi, bb);
-    }
-
-    // next tile whose workgroup bound is <= thr, or -1; wb: its wavefront bound
-    __device__ __forceinline__ int next(float thr, int own_t, int tend, const CurveArgs& crv, const float* qlo,
-                                        const float* qhi, const float* wlo, const float* whi, const BoxBound& bb,
-                                        float& wb)
-    {
-        constexpr int ST = SB_TILES_MFMA;
-        const int own_sb = own_t / ST, nsb = (tend + ST - 1) / ST;
-        const int lane = lane_id();
-        while (cur_r < tend || cur_l >= 0) {
-            if ((go_right && cur_r < tend) || cur_l < 0) {
-                go_right = false;
-                while (cur_r < tend) {
-                    if (cur_r >= rt0 + WAVE) {
-                        // first superblock within reach at or after cur_r's
-                        const int sb = cur_r / ST;
-                        if (sb >= rsb0 + WAVE || sb < rsb0) {
-                            rsb0 = sb;
-                            rsbw = sb_window(rsb0 + lane, own_sb, nsb, crv, qlo, qhi, bb);
-                        }
-                        const uint64_t ms = __ballot(rsbw <= thr) & (~0ull << (sb - rsb0));
-                        if (!ms) {
-                            cur_r = (rsb0 + WAVE) * ST;
-                            continue;
-                        }
-                        const int nsbr = rsb0 + __builtin_ctzll(ms);
-                        if (nsbr != sb) cur_r = nsbr * ST;
-                        if (cur_r >= tend) break;
-                        rt0 = cur_r;
-                        tile_window(rt0 + lane, own_t, tend, crv, qlo, qhi, wlo, whi, bb, rbw, rww);
-                    }
-                    const uint64_t m = __ballot(rbw <= thr) & (~0ull << (cur_r - rt0));
-                    if (m) {
-                        const int l = __builtin_ctzll(m);
-                        wb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rww), l));
-                        cur_r = rt0 + l + 1;
-                        return rt0 + l;
-                    }
-                    cur_r = rt0 + WAVE;
-                }
-            } else {
-                go_right = true;
-                while (cur_l >= 0) {
-                    if (cur_l <= lt0 - WAVE || cur_l > lt0) {
-                        // first superblock within reach at or before cur_l's
-                        const int sb = cur_l / ST;
-                        if (sb > lsb0 || sb <= lsb0 - WAVE) {
-                            lsb0 = sb;
-                            lsbw = sb_window(lsb0 - lane, own_sb, nsb, crv, qlo, qhi, bb);
-                        }
-                        const uint64_t ms = __ballot(lsbw <= thr) & (~0ull << (lsb0 - sb));
-                        if (!ms) {
-                            cur_l = (lsb0 - WAVE + 1) * ST - 1;
-                            continue;
-                        }
-                        const int nsbl = lsb0 - __builtin_ctzll(ms);
-                        if (nsbl != sb) cur_l = nsbl * ST + ST - 1;
-                        lt0 = cur_l;
-                        tile_window(lt0 - lane, own_t, tend, crv, qlo, qhi, wlo, whi, bb, lbw, lww);
-                    }
-                    const uint64_t m = __ballot(lbw <= thr) & (~0ull << (lt0 - cur_l));
-                    if (m) {
-                        const int l = __builtin_ctzll(m);
-                        wb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lww), l));
-                        cur_l = lt0 - l - 1;
-                        return lt0 - l;
-                    }
-                    cur_l = lt0 - WAVE;
-                }
-            }
-        }
-        return -1;
-    }
-};
-
 // WV wavefronts per workgroup share every candidate stage; each wavefront owns
 // 32 queries. The first CAP / 32 tiles of a scan that starts from empty
 // lists are written into the lists directly and sorted once; afterwards keys
@@ -480,53 +337,23 @@ struct CurveScan {
 // rows map to sample ids through cid (-1 for padding). Lists of queries are
 // created on the first probe pass and merged into on later ones (the list's
 // kp-th score is the starting threshold); no certificate is computed.
-//
-// MODE 2 (curve order): operands are laid out in the Morton order of the
-// samples' principal projections (spatial_mfma.hip); curve position p holds
-// sample crv.perm[p]. Queries, candidate keys, lists and bounds all refer to
-// curve positions (the refine step maps them to sample ids while it reads the
-// candidates from a curve-ordered copy of the samples). A workgroup's queries
-// are consecutive positions; it scans
-// tiles outward from its own along the curve and skips every tile (or, where
-// the scan enters one, every superblock of SB_TILES_MFMA tiles) whose
-// projected box is farther from the workgroup's query box than the largest
-// distance threshold of its queries (the bound and its rounding margins are
-// derived with the pruning test below). The thresholds are exchanged between
-// the wavefronts through a double-buffered LDS array at each stage barrier, so
-// all wavefronts take the same skipping decisions. The certificate epilogue
-// is that of MODE 0: a skipped candidate lies beyond the threshold at the
-// time of the skip, hence beyond every later one.
-// Curve scans run as two 4-wavefront workgroups per CU where both fit in LDS
-// (two candidate stages and 40-entry query buffers each): a wavefront's list
-// merge then holds up three others at the tile barrier instead of seven, and
-// the other workgroup keeps the CU busy meanwhile.
-constexpr int CURVE_PAIR_BUF = 40;
-template <class Tr, int KS>
-constexpr bool curve_pair()
-{
-    return 2 * (2 * KS * 64 * static_cast<int>(sizeof(typename Tr::frag)) + 4 * 32 * CURVE_PAIR_BUF * 8 + 2048) <=
-           160 * 1024;
-}
-
 template <class Tr, int KS, int WV, int E, int MODE>
-__global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS>()) ? 2 : 1) void k_select_mfma(
+__global__ __launch_bounds__(64 * WV) void k_select_mfma(
     const typename Tr::elem* __restrict__ Aq,
                                                           const typename Tr::elem* __restrict__ Bc, int n, int kp,
                                                           const float* __restrict__ ynorm2,
                                                           const unsigned* __restrict__ rmax_bits, ErrModel em,
                                                           uint64_t* __restrict__ lists, float* __restrict__ lb_out,
-                                                          BucketArgs ba, CurveArgs crv,
+                                                          BucketArgs ba,
                                                           unsigned long long* __restrict__ pair_count)
 {
     constexpr bool LEARNED = MODE == 1;
-    constexpr bool CURVE = MODE == 2;
     using elem = typename Tr::elem;
     using frag = typename Tr::frag;
     constexpr int CAP = WAVE * E;
     constexpr int kpad = KS * Tr::KSTEP;        // padded contraction length
     constexpr int NQ = 32;                      // queries per wavefront
-    // per-query LDS buffer entries (curve scans in pairs of 4-wavefront workgroups: 40)
-    constexpr int BUF = (MODE == 2 && WV == 4 && curve_pair<Tr, KS>()) ? CURVE_PAIR_BUF : WV == 8 ? 48 : 64;
+    constexpr int BUF = WV == 8 ? 48 : 64;   // per-query LDS buffer entries
     // two candidate stages, fragment-major: [stage][k-step][half][row] so that
     // lane l reads consecutive fragments (no bank conflicts). The next tile is
     // prefetched into registers while the current one is consumed.
@@ -552,10 +379,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
         tbeg = ba.tptr[wk.x];
         tend = ba.tptr[wk.x + 1];
         if (lane < NQ) s_qid[wave][lane] = q0 + lane < qend ? ba.qids[q0 + lane] : -1;
-    } else if constexpr (CURVE) {
-        q0 = (xcd_block() * WV + wave) * NQ;
-        tend = (n + 31) / 32;
-        if (lane < NQ) s_qid[wave][lane] = q0 + lane < n ? q0 + lane : -1;   // curve positions
     } else {
         q0 = (blockIdx.x * WV + wave) * NQ;
         tend = (n + 31) / 32;
@@ -565,8 +388,7 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
 
     frag qa[KS];
     {
-        // query operand row: curve position (MODE 2) or sample id
-        int row = CURVE ? min(q0 + (lane & 31), n - 1) : s_qid[wave][lane & 31];
+        int row = s_qid[wave][lane & 31];   // query operand row: the sample id
         if (row < 0) row = max(s_qid[wave][0], 0);
         const elem* src = Aq + static_cast<size_t>(row) * kpad + half * Tr::VEC;
 #pragma unroll
@@ -602,75 +424,10 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
 #pragma unroll
     for (int r = 0; r < 16; ++r) qrow[r] = s_qid[wave][acc_row(r, half)];
 
-    // MODE 2: the query boxes in projected space (s_qbox[w]: wavefront w's,
-    // s_qbox[WV]: the workgroup's), the squared norms of the queries
-    // (thresholds are kept as scores s = |y_j|^2 - 2 y_i.y_j, the distance
-    // threshold is s + |y_i|^2) and the scan cursor
-    __shared__ float s_qbox[WV + 1][2][PR_DIMS];
-    __shared__ float s_thr[2][WV];
-    const float* qlo = &s_qbox[WV][0][0];
-    const float* qhi = &s_qbox[WV][1][0];
-    const float* wlo = &s_qbox[wave][0][0];
-    const float* whi = &s_qbox[wave][1][0];
-    // |y_i|^2 of the queries for the distance thresholds: in registers, or in
-    // LDS for short contractions (measured faster there; the long ones are
-    // short of LDS instead)
-    constexpr bool YQ_LDS = KS <= 8;
-    __shared__ float s_yq[WV][NQ];
-    float yq[YQ_LDS ? 1 : 16];
-    CurveScan scan;
-    scan.init(0);
-    int own_t = 0;
-    BoxBound bb = {0.f, 1.f, 0.f};
-    if constexpr (CURVE) {
-        if constexpr (YQ_LDS) {
-            if (lane < NQ) s_yq[wave][lane] = s_qid[wave][lane] >= 0 ? ynorm2[s_qid[wave][lane]] : 0.f;
-        } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) yq[r] = qrow[r] >= 0 ? ynorm2[qrow[r]] : 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < PR_DIMS; ++c) {
-            const bool ok = lane < NQ && q0 + lane < n;
-            const float v = ok ? crv.zs[static_cast<size_t>(q0 + lane) * PR_DIMS + c] : 0.f;
-            float lo = ok ? v : __uint_as_float(0x7F800000u), hi = ok ? v : -__uint_as_float(0x7F800000u);
-#pragma unroll
-            for (int o = WAVE / 2; o > 0; o >>= 1) {
-                lo = fminf(lo, shfl_xor_f32(lo, o));
-                hi = fmaxf(hi, shfl_xor_f32(hi, o));
-            }
-            if (lane == 0) {
-                s_qbox[wave][0][c] = lo;
-                s_qbox[wave][1][c] = hi;
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < PR_DIMS) {
-            const int c = threadIdx.x;
-            float lo = s_qbox[0][0][c], hi = s_qbox[0][1][c];
-            for (int w = 1; w < WV; ++w) {
-                lo = fminf(lo, s_qbox[w][0][c]);
-                hi = fmaxf(hi, s_qbox[w][1][c]);
-            }
-            s_qbox[WV][0][c] = lo;
-            s_qbox[WV][1][c] = hi;
-        }
-        __syncthreads();
-        own_t = min(tend - 1, (xcd_block() * WV * NQ + WV * NQ / 2) / 32);
-        const float R = __uint_as_float(*rmax_bits);
-        bb.zerr = crv.zcoef * R;
-        bb.pscale = *crv.pscale;
-        bb.yerr = crv.ycoef * R;
-        scan.init(own_t);
-    }
     __builtin_amdgcn_s_waitcnt(0);
     u32x4 pf[PF];
     int cid_pf = -1;
-    int tile = -1;
-    float wb_pf = 0.f;   // MODE 2: bound of the prefetched tile to this wavefront's box
-    if (tbeg < tend)
-        tile = CURVE ? scan.next(__uint_as_float(0x7F800000u), own_t, tend, crv, qlo, qhi, wlo, whi, bb, wb_pf)
-                     : tbeg;
+    int tile = tbeg < tend ? tbeg : -1;
     if (tile >= 0) {
         const u32x4* g = reinterpret_cast<const u32x4*>(Bc + static_cast<size_t>(tile) * 32 * kpad);
 #pragma unroll
@@ -679,7 +436,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
             if (ch < CHUNKS) pf[u] = g[ch];
         }
         if constexpr (LEARNED) cid_pf = ba.cid[static_cast<size_t>(tile) * 32 + (lane & 31)];
-        if constexpr (CURVE) cid_pf = tile * 32 + (lane & 31) < n ? tile * 32 + (lane & 31) : -1;
     }
     // the buffers' fill, wave-uniform: query q's count in byte q % 4 of
     // cntw[q / 4] (every index below is a compile-time constant, so they stay
@@ -692,28 +448,8 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
     // lists that start empty are filled by the first tiles without merging
     bool filling = !LEARNED || ba.first;
     const int fill_tiles = CAP / 32;   // the whole list capacity: a tighter first threshold
-    // MODE 2: this wavefront's largest distance threshold, an upper bound of
-    // s + |y_i|^2 over its queries; recomputed only after thresholds change
-    float wthr = __uint_as_float(0x7F800000u);
-    bool thr_dirty = true;
     for (int it = 0; tile >= 0; ++it) {
         const int stage = it & 1;
-        if constexpr (CURVE) {
-            if (thr_dirty) {
-                float t = -__uint_as_float(0x7F800000u);
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (qrow[r] >= 0) {
-                        const float y2 = YQ_LDS ? s_yq[wave][acc_row(r, half)] : yq[YQ_LDS ? 0 : r];
-                        t = fmaxf(t, fmaxf(tauv[r] + y2, 0.f) * (1.f + 4.8e-7f));
-                    }
-                // read from one lane: the compiler then sees a wave-uniform
-                // value and keeps the branches on it (and the counts) scalar
-                wthr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wave_max_f32(t))));
-                thr_dirty = false;
-            }
-            if (lane == 0) s_thr[stage][wave] = wthr;
-        }
         {
             u32x4* d = reinterpret_cast<u32x4*>(&s_tile[stage][0][0][0]);
 #pragma unroll
@@ -723,19 +459,8 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
             }
         }
         const int cid_cur = cid_pf;
-        const float wb_cur = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wb_pf)));
         __syncthreads();                 // stage visible; the other stage's readers finished a tile ago
-        float thr = __uint_as_float(0x7F800000u);
-        if constexpr (CURVE) {
-            thr = s_thr[stage][0];
-#pragma unroll
-            for (int w = 1; w < WV; ++w) thr = fmaxf(thr, s_thr[stage][w]);
-        }
-        int next;
-        if constexpr (CURVE)
-            next = scan.next(thr, own_t, tend, crv, qlo, qhi, wlo, whi, bb, wb_pf);
-        else
-            next = tile + 1 < tend ? tile + 1 : -1;
+        const int next = tile + 1 < tend ? tile + 1 : -1;
         if (next >= 0) {
             const u32x4* g = reinterpret_cast<const u32x4*>(Bc + static_cast<size_t>(next) * 32 * kpad);
 #pragma unroll
@@ -744,15 +469,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
                 if (ch < CHUNKS) pf[u] = g[ch];
             }
             if constexpr (LEARNED) cid_pf = ba.cid[static_cast<size_t>(next) * 32 + (lane & 31)];
-            if constexpr (CURVE) cid_pf = next * 32 + (lane & 31) < n ? next * 32 + (lane & 31) : -1;
-        }
-        // MODE 2, after the fill: a tile the workgroup scans may still lie
-        // beyond this wavefront's own box and thresholds
-        if constexpr (CURVE) {
-            if (!filling && wb_cur > wthr) {
-                tile = next;
-                continue;
-            }
         }
         // all fragment reads are issued before the products (up to 16 at a
         // time), and even / odd K-steps go to two accumulators, so the chain of
@@ -809,7 +525,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         if (r == rr && half == hh) tauv[r] = nt;
-                    thr_dirty = true;
                 }
             }
             tile = next;
@@ -835,7 +550,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
                             nt = merge_query_list<E>(lists + static_cast<size_t>(qg) * CAP, &s_buf[wave][qa_][0], ca,
                                                      kp);
                         if (half == 0) tauv[r] = nt;
-                        thr_dirty = true;
                         ca = 0;
                         cntw[qa_ >> 2] &= ~(0xFFu << (8 * (qa_ & 3)));
                     }
@@ -846,7 +560,6 @@ __global__ __launch_bounds__(64 * WV, (MODE == 2 && WV == 4 && curve_pair<Tr, KS
                             nt = merge_query_list<E>(lists + static_cast<size_t>(qg) * CAP, &s_buf[wave][qb_][0], cb,
                                                      kp);
                         if (half == 1) tauv[r] = nt;
-                        thr_dirty = true;
                         cb = 0;
                         cntw[qb_ >> 2] &= ~(0xFFu << (8 * (qb_ & 3)));
                     }
@@ -969,7 +682,7 @@ hipError_t launch_prep(const float* X, int n, int m, int split, int kpad, double
 template <class Tr, int KS, int WV>
 static hipError_t launch_sel(const void* Aq, const void* Bc, int n, int kp, const float* ynorm2, const unsigned* rmax,
                              ErrModel em, uint64_t* lists, int cap, float* lb, const BucketArgs* ba, int max_work,
-                             const CurveArgs* crv, unsigned long long* pairs, hipStream_t st)
+                             unsigned long long* pairs, hipStream_t st)
 {
     using elem = typename Tr::elem;
     const int rows_per_block = WV * 32;
@@ -980,38 +693,24 @@ static hipError_t launch_sel(const void* Aq, const void* Bc, int n, int kp, cons
     if (kp > cap) return hipErrorInvalidValue;
     if (cap != 128 && cap != 256) return hipErrorInvalidValue;
     const BucketArgs nb = {};
-    const CurveArgs nc = {};
     if (ba) {
         if (max_work <= 0) return hipSuccess;
         const dim3 grid(max_work);
         if (cap == 128)
             hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 2, 1>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, *ba, nc, pairs);
+                               lists, lb, *ba, pairs);
         else
             hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 4, 1>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, *ba, nc, pairs);
+                               lists, lb, *ba, pairs);
         return hipGetLastError();
     }
     const dim3 grid((n + rows_per_block - 1) / rows_per_block);
-    if (crv) {
-        // curve-ordered workgroup scan (long contractions; the short ones walk
-        // the box tree in knn_tree.hip)
-        constexpr int WC = curve_pair<Tr, KS>() ? 4 : WV;
-        const dim3 gridc((n + WC * 32 - 1) / (WC * 32)), blockc(64 * WC);
-        if (cap == 128)
-            hipLaunchKernelGGL((k_select_mfma<Tr, KS, WC, 2, 2>), gridc, blockc, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, nb, *crv, pairs);
-        else
-            hipLaunchKernelGGL((k_select_mfma<Tr, KS, WC, 4, 2>), gridc, blockc, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, nb, *crv, pairs);
-        return hipGetLastError();
-    }
     if (cap == 128)
         hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 2, 0>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em, lists,
-                           lb, nb, nc, pairs);
+                           lb, nb, pairs);
     else
         hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 4, 0>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em, lists,
-                           lb, nb, nc, pairs);
+                           lb, nb, pairs);
     return hipGetLastError();
 }
 
@@ -1034,7 +733,7 @@ int mfma_pick_ksteps(int split, int needed)
 }
 
 #define KVB_SEL_CASE(TR, K, WV) \
-    case K: return launch_sel<TR, K, WV>(Aq, Bc, n, kp, ynorm2, rmax, em, lists, cap, lb, ba, max_work, crv, pairs, st);
+    case K: return launch_sel<TR, K, WV>(Aq, Bc, n, kp, ynorm2, rmax, em, lists, cap, lb, ba, max_work, pairs, st);
 
 int select_mfma_queries_per_block(int split, int kpad)
 {
@@ -1045,7 +744,7 @@ int select_mfma_queries_per_block(int split, int kpad)
 
 hipError_t launch_select_mfma(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
-                              const BucketArgs* ba, int max_work, const CurveArgs* crv, unsigned long long* pairs,
+                              const BucketArgs* ba, int max_work, unsigned long long* pairs,
                               hipStream_t st)
 {
     const int ks = kpad / mfma_kstep(split);

@@ -1,6 +1,6 @@
 // Pieces shared by the matrix-core selection kernels (knn_mfma.hip: the
-// all-tiles and learned-bucket scans; knn_tree.hip: the curve-ordered scan
-// over the tile-box tree): MFMA operand traits, the accumulator layout, the
+// all-tiles and learned-bucket scans; knn_tree.hip: the curve-ordered walk
+// of the tile-box tree): MFMA operand traits, the accumulator layout, the
 // per-query list merge and sort in global scratch, the projected-box distance
 // bound and the XCD-aware workgroup order.
 #pragma once
@@ -52,30 +52,6 @@ __device__ __noinline__ float merge_query_list(uint64_t* __restrict__ dst, const
 #pragma unroll
     for (int s = 0; s < E; ++s) L[s] = dst[s * WAVE + lane];
     merge_into_list<E>(L, b);
-#pragma unroll
-    for (int s = 0; s < E; ++s) dst[s * WAVE + lane] = L[s];
-    return key_dist(list_at<E>(L, kp - 1));
-}
-
-// The same for a buffer of at most 32 keys: they are placed in the upper half
-// of the wavefront and sorted there in descending order by the first five
-// passes of the bitonic network (15 stages instead of 21), which is already
-// the reversed ascending order of the 64-key buffer padded with KEY_INF.
-template <int E>
-__device__ __noinline__ float merge_query_list32(uint64_t* __restrict__ dst, const uint64_t* buf, int cnt, int kp)
-{
-    const int lane = lane_id();
-    uint64_t B[1] = {lane >= 32 && lane - 32 < cnt ? buf[lane - 32] : KEY_INF};
-    uint64_t L[E];
-#pragma unroll
-    for (int s = 0; s < E; ++s) L[s] = dst[s * WAVE + lane];
-#pragma unroll
-    for (int kb = 2; kb <= 32; kb <<= 1) {
-#pragma unroll
-        for (int j = kb >> 1; j > 0; j >>= 1) cx_lanes<1>(B, kb, j, lane);
-    }
-    L[E - 1] = umin64(L[E - 1], B[0]);
-    bitonic_merge_asc<E>(L);
 #pragma unroll
     for (int s = 0; s < E; ++s) dst[s * WAVE + lane] = L[s];
     return key_dist(list_at<E>(L, kp - 1));

@@ -28,12 +28,10 @@ struct BucketArgs {
     int first;           // 1: create the query lists, 0: merge into them
 };
 
-// Projected dimensions of the curve order (MODE 2 of the matrix-core select):
-// boxes use PR_DIMS principal coordinates, the Morton code the first
-// PCODE_DIMS of them; superblocks group SB_TILES_MFMA tiles of 32 samples.
+// Projected dimensions of the curve order: boxes use PR_DIMS principal
+// coordinates, the Morton code the first PCODE_DIMS of them.
 constexpr int PR_DIMS = 8;
 constexpr int PCODE_DIMS = 4;
-constexpr int SB_TILES_MFMA = 16;
 
 // Box tree over the curve-ordered tiles: level 0 holds the tiles' boxes,
 // node v of level l >= 1 the box of nodes 64 v .. 64 v + 63 of level l - 1;
@@ -52,7 +50,6 @@ struct CurveArgs {
     const int* perm;    // [tiles * 32] sample id at each curve position, -1 for padding
     const float* zs;    // [n, PR_DIMS] projected coordinates in curve order
     const float* tbox;  // [tiles, 2, PR_DIMS] boxes of 32-sample tiles
-    const float* sbox;  // [superblocks, 2, PR_DIMS] (workgroup scans of knn_mfma.hip)
     const float* tree;  // [layout.nodes, 2, PR_DIMS] boxes of the tree levels >= 1
     TreeLayout layout;
     const float* pscale;// |v| >= *pscale |P^T v| for every v (set with the basis)
@@ -121,11 +118,10 @@ int mfma_pick_ksteps(int split, int needed);
 // selection with max_work workgroups (the kernel skips those beyond *ba->n_work).
 hipError_t launch_select_mfma(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
-                              const BucketArgs* ba, int max_work, const CurveArgs* crv, unsigned long long* pairs,
+                              const BucketArgs* ba, int max_work, unsigned long long* pairs,
                               hipStream_t st);
-// curve order of the samples for MODE 2 (spatial_mfma.hip)
+// curve order of the samples (spatial_mfma.hip)
 int cov_partials();
-int cov_chunks(int m);
 int project_blocks(int n);
 size_t curve_sort_bytes(int n);
 // P [m * PR_DIMS + 1]: the basis, then the scale factor of CurveArgs::pscale
@@ -137,12 +133,9 @@ hipError_t launch_principal_basis(const float* X, int n, int m, const double* mu
 // halved at its median along the widest side of its box, recursively down to single tiles.
 hipError_t launch_curve_order(const float* X, int n, int m, const double* mu, const float* P, float* z, float* zpart,
                               uint32_t* code, uint32_t* scode, int32_t* vals, int32_t* perm, void* sort_tmp,
-                              size_t sort_bytes, int32_t* pos, int32_t* cid, float* zs, float* tbox, float* sbox,
-                              float* tree, bool median_splits, hipStream_t st);
+                              size_t sort_bytes, int32_t* pos, int32_t* cid, float* zs, float* tbox, float* tree,
+                              bool median_splits, hipStream_t st);
 // curve-ordered exact selection over the box tree (knn_tree.hip); lists [n, cap], lb [n] by curve position.
-// select_tree_fits: whether the tree walk suits the contraction length (else the
-// workgroup scan of launch_select_mfma with crv runs)
-bool select_tree_fits(int split, int kpad);
 hipError_t launch_select_tree(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
                               const CurveArgs& crv, unsigned long long* pairs, hipStream_t st);

@@ -11,7 +11,7 @@
 //   |y_i - y_j|^2 >= |z_i - z_j|^2 >= (gap between the boxes of their z)^2,
 // a candidate tile whose box lies farther from a query block's box than all
 // of the block's current thresholds holds no neighbour of any of its queries
-// and is skipped (selection kernel, knn_mfma.hip). The bound is made rigorous
+// and is skipped (selection kernel, knn_tree.hip). The bound is made rigorous
 // for the rounding of P, of z and of the box gaps by the margins set there.
 #include <rocprim/device/device_radix_sort.hpp>
 
@@ -785,8 +785,8 @@ hipError_t launch_principal_basis(const float* X, int n, int m, const double* mu
 
 hipError_t launch_curve_order(const float* X, int n, int m, const double* mu, const float* P, float* z, float* zpart,
                               uint32_t* code, uint32_t* scode, int32_t* vals, int32_t* perm, void* sort_tmp,
-                              size_t sort_bytes, int32_t* pos, int32_t* cid, float* zs, float* tbox, float* sbox,
-                              float* tree, bool median_splits, hipStream_t st)
+                              size_t sort_bytes, int32_t* pos, int32_t* cid, float* zs, float* tbox, float* tree,
+                              bool median_splits, hipStream_t st)
 {
     const int nb = project_blocks(n);
     auto project = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, st, X, n, m, mu, P, z, zpart); };
@@ -824,9 +824,6 @@ hipError_t launch_curve_order(const float* X, int n, int m, const double* mu, co
                            zs);
     }
     hipLaunchKernelGGL(k_zboxes, dim3((ntiles * PR_DIMS + 255) / 256), dim3(256), 0, st, zs, n, 32, ntiles, 0, tbox);
-    const int nsb = (ntiles + SB_TILES_MFMA - 1) / SB_TILES_MFMA;
-    hipLaunchKernelGGL(k_zboxes, dim3((nsb * PR_DIMS + 255) / 256), dim3(256), 0, st, tbox, ntiles, SB_TILES_MFMA, nsb,
-                       1, sbox);
     // the box tree: each level's boxes over groups of 64 boxes of the level below
     const TreeLayout t = tree_layout(ntiles);
     for (int l = 1; l <= t.top; ++l) {
