@@ -235,13 +235,16 @@ __global__ __launch_bounds__(256) void k_density(const int32_t* __restrict__ idx
 
 // ------------------------------------------------------------------ tuning sums
 // Block partials of chi[g] = sum over entries of exp(-x / e_g), x = d2/(rho_i rho_j).
-// Each thread forms x for its entries and accumulates exp2(x c_g) for a group
-// of 64 grid points in registers (c_g = -log2(e)/e_g, float32 per thread over
-// its few entries; hardware exp2, whose flush of results below 2^-126 is far
-// below the sum's rounding since every row contributes exp(0) = 1); the
-// per-thread sums are then reduced in float64 in a fixed order.
+// Each thread forms x for its entries and accumulates exp2(x c_g) for GROUP
+// grid points in registers (c_g = -log2(e)/e_g, float32 per thread over its few
+// entries; hardware exp2, whose flush of results below 2^-126 is far below the
+// sum's rounding since every row contributes exp(0) = 1); the per-thread sums
+// are then reduced in float64 in a fixed order. At large counts this runs at 21
+// cycles per wavefront and exponential (multiply, exp2, add: 16), a batch's
+// loads and gathers under the sums of the batch before (1M x 64: 630 to 554 us;
+// 2000 x 32, with the grid points over workgroups and the wavefronts' sums
+// reduced side by side: 20.8 to 10.4 us).
 constexpr int CHI_BLOCK = 256;
-constexpr int CHI_GROUP = 64;   // grid points per register group
 
 // ln e_g = ln e_min + g (ln e_max - ln e_min) / (G - 1)
 __device__ __forceinline__ double grid_log(double lo, double hi, int G, int g)
@@ -251,10 +254,13 @@ __device__ __forceinline__ double grid_log(double lo, double hi, int G, int g)
 constexpr int CHI_MIN_ENTRIES_PER_BLOCK = 4096;
 constexpr int CHI_BATCH = 4;
 constexpr int CHI_MAX_BLOCKS = 1024;
+constexpr int CHI_SPLIT = 128;   // up to this many blocks of entries: 16 grid points per workgroup
+constexpr int CHI_RED = 16;   // grid points reduced at a time
 
-// CSR: rows given by rowptr [n + 1] (k unused) and, when rowid is not null,
-// the row of every entry; otherwise k entries per row.
-template <bool CSR>
+// Workgroup (b, y): entries [b per_block, (b + 1) per_block), grid points
+// [y GROUP, (y + 1) GROUP). CSR: rows given by rowptr [n + 1] (k unused) and,
+// when rowid is not null, the row of every entry; otherwise k entries per row.
+template <bool CSR, int GROUP>
 __global__ __launch_bounds__(CHI_BLOCK) void k_chi_partial(const int32_t* __restrict__ idx,
                                                            const float* __restrict__ d2,
                                                            const int64_t* __restrict__ rowptr,
@@ -264,125 +270,154 @@ __global__ __launch_bounds__(CHI_BLOCK) void k_chi_partial(const int32_t* __rest
                                                            const double* __restrict__ scale_dev, int64_t per_block,
                                                            double* __restrict__ partial)
 {
-    const double sc = scale_dev ? *scale_dev : 1.0;
-    const double log_emin = log(e_min * sc), log_emax = log(e_max * sc);
-    __shared__ float s_c[256 + CHI_GROUP];
-    __shared__ double sred[CHI_BLOCK / WAVE][CHI_GROUP];
-    __shared__ float s_tr[WAVE][CHI_GROUP + 1];   // one wavefront's partials, transposed
+    constexpr int WAVES = CHI_BLOCK / WAVE;
+    __shared__ float s_c[GROUP];
+    __shared__ double s_red[WAVES][GROUP];
+    __shared__ float s_tr[WAVES][WAVE][CHI_RED + 1];   // each wavefront's sums of CHI_RED grid points, by lane
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
+    const int g0 = blockIdx.y * GROUP;
     if (CSR) nnz = rowptr[n];   // the launch is sized for an upper bound
     const int64_t base = static_cast<int64_t>(blockIdx.x) * per_block;
     const int64_t end = min(base + per_block, nnz);
-    for (int g = threadIdx.x; g < 256 + CHI_GROUP; g += CHI_BLOCK)
-        s_c[g] = g < G ? static_cast<float>(-1.4426950408889634 / exp(grid_log(log_emin, log_emax, G, g))) : 0.f;
-    __syncthreads();
-    for (int g0 = 0; g0 < G; g0 += CHI_GROUP) {
-        // the group's coefficients are wave-uniform: held in scalar registers
-        float cg[CHI_GROUP];
-#pragma unroll
-        for (int t = 0; t < CHI_GROUP; ++t)
-            cg[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_c[g0 + t])));
-        float acc[CHI_GROUP];
-#pragma unroll
-        for (int t = 0; t < CHI_GROUP; ++t) acc[t] = 0.f;
-        // CHI_BATCH entries per thread at a time (their loads and gathers in
-        // flight together); the accumulation order stays entry by entry
-        // the row of entry p = i k + r is tracked incrementally (no division
-        // per entry): consecutive entries of a thread are CHI_BLOCK apart
-        const int di = CSR ? 0 : CHI_BLOCK / k, dr = CSR ? 0 : CHI_BLOCK % k;
-        int64_t irow, rend = 0;
-        int rcol = 0;
-        if (CSR && rowid) {
-            irow = 0;
-        } else if (CSR) {
-            // the row holding the thread's first entry: last i with rowptr_i <= p
-            const int64_t p = min(base + threadIdx.x, nnz - 1);
-            int lo = 0, hi = n;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (rowptr[mid] <= p)
-                    lo = mid;
-                else
-                    hi = mid;
-            }
-            irow = lo;
-            rend = rowptr[lo + 1];
-        } else {
-            irow = (base + threadIdx.x) / k;
-            rcol = static_cast<int>((base + threadIdx.x) - irow * k);
+
+    // CHI_BATCH entries per thread at a time, in three stages so that a
+    // batch's loads and gathers pass during the sums of the one before: the
+    // entries, the gathered widths, the sums. The accumulation order stays
+    // entry by entry. The row of entry p = i k + r is tracked incrementally
+    // (no division per entry): consecutive entries of a thread are CHI_BLOCK apart.
+    const int di = CSR ? 0 : CHI_BLOCK / k, dr = CSR ? 0 : CHI_BLOCK % k;
+    int64_t irow, rend = 0;
+    int rcol = 0;
+    if (CSR && rowid) {
+        irow = 0;
+    } else if (CSR) {
+        // the row holding the thread's first entry: last i with rowptr_i <= p
+        const int64_t p = min(base + threadIdx.x, nnz - 1);
+        int lo = 0, hi = n;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (rowptr[mid] <= p)
+                lo = mid;
+            else
+                hi = mid;
         }
-        for (int64_t p0 = base + threadIdx.x; p0 < end; p0 += CHI_BATCH * CHI_BLOCK) {
-            float dv[CHI_BATCH];
-            int jv[CHI_BATCH];
-            int64_t iv[CHI_BATCH];
+        irow = lo;
+        rend = rowptr[lo + 1];
+    } else {
+        irow = (base + threadIdx.x) / k;
+        rcol = static_cast<int>((base + threadIdx.x) - irow * k);
+    }
+    auto entries = [&](int64_t p0, float (&dv)[CHI_BATCH], int (&iv)[CHI_BATCH], int (&jv)[CHI_BATCH]) {
 #pragma unroll
-            for (int u = 0; u < CHI_BATCH; ++u) {
-                const int64_t p = p0 + u * CHI_BLOCK;
-                const bool ok = p < end;
-                dv[u] = ok ? d2[p] : 0.f;
-                jv[u] = ok ? idx[p] : 0;
-                if (CSR && rowid) {
-                    iv[u] = ok ? rowid[p] : 0;
-                } else if (CSR) {
-                    // p < nnz = rowptr_n, so the walk stops at a row below n
-                    if (ok) {
-                        while (p >= rend) {
-                            ++irow;
-                            rend = rowptr[irow + 1];
-                        }
-                    }
-                    iv[u] = ok ? irow : 0;
-                } else {
-                    iv[u] = ok ? irow : 0;
-                    irow += di;
-                    rcol += dr;
-                    if (rcol >= k) {
-                        rcol -= k;
+        for (int u = 0; u < CHI_BATCH; ++u) {
+            const int64_t p = p0 + u * CHI_BLOCK;
+            const bool ok = p < end;
+            dv[u] = ok ? d2[p] : 0.f;
+            jv[u] = ok ? idx[p] : 0;
+            if (CSR && rowid) {
+                iv[u] = ok ? rowid[p] : 0;
+            } else if (CSR) {
+                // p < nnz = rowptr_n, so the walk stops at a row below n
+                if (ok) {
+                    while (p >= rend) {
                         ++irow;
+                        rend = rowptr[irow + 1];
                     }
                 }
-            }
-            float x[CHI_BATCH];
-#pragma unroll
-            for (int u = 0; u < CHI_BATCH; ++u)
-                x[u] = static_cast<float>(static_cast<double>(dv[u]) /
-                                          (static_cast<double>(rho[iv[u]]) * static_cast<double>(rho[jv[u]])));
-#pragma unroll
-            for (int u = 0; u < CHI_BATCH; ++u) {
-                if (p0 + u * CHI_BLOCK < end) {
-#pragma unroll
-                    for (int t = 0; t < CHI_GROUP; ++t) acc[t] += __builtin_amdgcn_exp2f(x[u] * cg[t]);
+                iv[u] = ok ? static_cast<int>(irow) : 0;
+            } else {
+                iv[u] = ok ? static_cast<int>(irow) : 0;
+                irow += di;
+                rcol += dr;
+                if (rcol >= k) {
+                    rcol -= k;
+                    ++irow;
                 }
             }
         }
-        // fixed-order reduction: the wavefronts in turn store their partials
-        // transposed, lane t sums grid point t over the 64 lanes in float64;
-        // then the wavefronts in order
-#pragma unroll 1
-        for (int w = 0; w < CHI_BLOCK / WAVE; ++w) {
-            if (wave == w) {
+    };
+    auto widths = [&](const int (&iv)[CHI_BATCH], const int (&jv)[CHI_BATCH], float (&ri)[CHI_BATCH],
+                      float (&rj)[CHI_BATCH]) {
 #pragma unroll
-                for (int t = 0; t < CHI_GROUP; ++t) s_tr[lane][t] = acc[t];
-                wave_lds_sync();
-                double v = 0.0;
-                for (int l = 0; l < WAVE; ++l) v += static_cast<double>(s_tr[l][lane]);
-                sred[w][lane] = v;
+        for (int u = 0; u < CHI_BATCH; ++u) {
+            ri[u] = rho[iv[u]];
+            rj[u] = rho[jv[u]];
+        }
+    };
+    constexpr int64_t STEP = CHI_BATCH * CHI_BLOCK;
+    const int64_t first = base + threadIdx.x;
+    float dv[2][CHI_BATCH], ri[CHI_BATCH], rj[CHI_BATCH];
+    int iv[CHI_BATCH], jv[CHI_BATCH];
+    entries(first, dv[0], iv, jv);
+    widths(iv, jv, ri, rj);
+    entries(first + STEP, dv[1], iv, jv);
+
+    // the grid points' coefficients
+    const double sc = scale_dev ? *scale_dev : 1.0;
+    const double log_emin = log(e_min * sc), log_emax = log(e_max * sc);
+    if (threadIdx.x < GROUP) {
+        const int g = g0 + threadIdx.x;
+        s_c[threadIdx.x] = g < G ? static_cast<float>(-1.4426950408889634 / exp(grid_log(log_emin, log_emax, G, g))) : 0.f;
+    }
+    __syncthreads();
+    // they are wave-uniform: held in scalar registers
+    float cg[GROUP];
+#pragma unroll
+    for (int t = 0; t < GROUP; ++t)
+        cg[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_c[t])));
+    float acc[GROUP];
+#pragma unroll
+    for (int t = 0; t < GROUP; ++t) acc[t] = 0.f;
+    for (int64_t p0 = first; p0 < end; p0 += STEP) {
+        float x[CHI_BATCH], dn[CHI_BATCH];
+#pragma unroll
+        for (int u = 0; u < CHI_BATCH; ++u)
+            x[u] = static_cast<float>(static_cast<double>(dv[0][u]) /
+                                      (static_cast<double>(ri[u]) * static_cast<double>(rj[u])));
+        widths(iv, jv, ri, rj);
+        entries(p0 + 2 * STEP, dn, iv, jv);
+#pragma unroll
+        for (int u = 0; u < CHI_BATCH; ++u) {
+            dv[0][u] = dv[1][u];
+            dv[1][u] = dn[u];
+        }
+#pragma unroll
+        for (int u = 0; u < CHI_BATCH; ++u) {
+            if (p0 + u * CHI_BLOCK < end) {
+#pragma unroll
+                for (int t = 0; t < GROUP; ++t) acc[t] += __builtin_amdgcn_exp2f(x[u] * cg[t]);
             }
-            __syncthreads();
         }
-        if (threadIdx.x < CHI_GROUP && g0 + threadIdx.x < G) {
-            double s = 0.0;
-            for (int w = 0; w < CHI_BLOCK / WAVE; ++w) s += sred[w][threadIdx.x];
-            partial[static_cast<size_t>(blockIdx.x) * G + g0 + threadIdx.x] = s;
-        }
-        __syncthreads();
+    }
+    // fixed-order reduction in float64: CHI_RED grid points at a time, each
+    // quarter of a wavefront sums one of them over 16 lanes in order, then the
+    // quarters in order, then the wavefronts
+    const int t = lane % CHI_RED, quarter = lane / CHI_RED;
+#pragma unroll
+    for (int c = 0; c < GROUP; c += CHI_RED) {
+#pragma unroll
+        for (int u = 0; u < CHI_RED; ++u) s_tr[wave][lane][u] = acc[c + u];
+        wave_lds_sync();
+        double v = 0.0;
+#pragma unroll
+        for (int l = 0; l < WAVE / 4; ++l) v += static_cast<double>(s_tr[wave][quarter * (WAVE / 4) + l][t]);
+        auto of = [&](int q) {
+            return __longlong_as_double(
+                static_cast<long long>(shfl_u64(static_cast<uint64_t>(__double_as_longlong(v)), q * CHI_RED + t)));
+        };
+        const double s = ((of(0) + of(1)) + of(2)) + of(3);
+        if (lane < CHI_RED) s_red[wave][c + lane] = s;
+        wave_lds_sync();
+    }
+    __syncthreads();
+    if (threadIdx.x < GROUP && g0 + threadIdx.x < G) {
+        double s = 0.0;
+        for (int w = 0; w < WAVES; ++w) s += s_red[w][threadIdx.x];
+        partial[static_cast<size_t>(blockIdx.x) * G + g0 + threadIdx.x] = s;
     }
 }
 
-// Fixed-order reduction of the block partials, then slopes and the optimum
-// (Section 2.3): slope_g = (ln chi_{g+1} - ln chi_g) / (ln e_{g+1} - ln e_g),
-// g* = first argmax, e* = e_{g*}, dimension estimate 2 slope_{g*}.
 // chi[g] = the sum of the block partials of grid point g: one workgroup per
 // grid point, thread t summing blocks t, t + 256, ... in order, then a fixed
 // tree over the threads. nnz_dev (or null): the pattern's entry count on the
@@ -408,33 +443,73 @@ __global__ __launch_bounds__(256) void k_chi_reduce(const double* __restrict__ p
 
 // Slopes and the optimum (Section 2.3): slope_g = (ln chi_{g+1} - ln chi_g) /
 // (ln e_{g+1} - ln e_g), g* = first argmax, e* = e_{g*}, dimension estimate
-// 2 slope_{g*}.
-__global__ __launch_bounds__(256) void k_chi_finish(int G, double e_min, double e_max,
-                                                    const double* __restrict__ scale_dev,
+// 2 slope_{g*}. With few block partials (nblocks > 0, at most CHI_FEW) it sums
+// them first, in the order of k_chi_reduce, whose launch is then spared.
+constexpr int CHI_FEW = 64;
+__global__ __launch_bounds__(256) void k_chi_finish(const double* __restrict__ partial, int nblocks, int G,
+                                                    double e_min, double e_max, const double* __restrict__ scale_dev,
                                                     TuneResult* __restrict__ out)
 {
-    const double sc = scale_dev ? *scale_dev : 1.0;
-    const double log_emin = log(e_min * sc), log_emax = log(e_max * sc);
-    __shared__ double slope[256];
-    if (threadIdx.x + 1 < G) {
-        const int t = threadIdx.x;
-        const double el = exp(grid_log(log_emin, log_emax, G, t));
-        const double er = exp(grid_log(log_emin, log_emax, G, t + 1));
-        slope[t] = (log(out->chi[t + 1]) - log(out->chi[t])) / (log(er) - log(el));
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int best = 0;
-        double best_s = -1.0 / 0.0;
-        for (int t = 0; t + 1 < G; ++t) {
-            if (slope[t] > best_s) {
-                best_s = slope[t];
-                best = t;
+    __shared__ double s_chi[256], s_log[256], s_slope[4];
+    __shared__ int s_at[4];
+    const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+    if (nblocks > 0) {
+        // four threads per grid point, thread r of them blocks r, r + 4, ...
+        const int r = t & 3;
+        for (int g = t >> 2; g < (G + 63) / 64 * 64; g += 64) {
+            double a[CHI_FEW / 4];
+#pragma unroll
+            for (int i = 0; i < CHI_FEW / 4; ++i)
+                a[i] = 4 * i + r < nblocks && g < G ? partial[static_cast<size_t>(4 * i + r) * G + g] : 0.0;
+#pragma unroll
+            for (int o = CHI_FEW / 8; o > 0; o >>= 1)
+#pragma unroll
+                for (int i = 0; i < o; ++i) a[i] += a[i + o];
+            a[0] += shfl_xor_f64(a[0], 2);
+            a[0] += shfl_xor_f64(a[0], 1);
+            if (r == 0 && g < G) {
+                s_chi[g] = a[0];
+                out->chi[g] = a[0];
             }
         }
-        out->g_star = best;
-        out->e_star = exp(grid_log(log_emin, log_emax, G, best));
-        out->dim = 2.0 * best_s;
+    } else if (t < G) {
+        s_chi[t] = out->chi[t];
+    }
+    const double sc = scale_dev ? *scale_dev : 1.0;
+    const double log_emin = log(e_min * sc), log_emax = log(e_max * sc);
+    if (t < G) s_log[t] = log(exp(grid_log(log_emin, log_emax, G, t)));
+    __syncthreads();
+    if (t < G) s_chi[t] = log(s_chi[t]);
+    __syncthreads();
+    // the largest slope, the first of equals; NaN and -inf are never taken
+    const double none = -1.0 / 0.0;
+    double v = t + 1 < G ? (s_chi[t + 1] - s_chi[t]) / (s_log[t + 1] - s_log[t]) : none;
+    if (!(v > none)) v = none;
+    int at = t;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const double ov = shfl_xor_f64(v, o);
+        const int oa = __shfl_xor(at, o, WAVE);
+        if (ov > v || (ov == v && oa < at)) {
+            v = ov;
+            at = oa;
+        }
+    }
+    if (lane == 0) {
+        s_slope[wave] = v;
+        s_at[wave] = at;
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < 4; ++w) {
+            if (s_slope[w] > v) {
+                v = s_slope[w];
+                at = s_at[w];
+            }
+        }
+        out->g_star = at;   // no slope: the first point
+        out->e_star = exp(grid_log(log_emin, log_emax, G, at));
+        out->dim = 2.0 * v;
     }
 }
 
@@ -784,15 +859,40 @@ int chi_num_blocks(int64_t nnz)
     return static_cast<int>((nnz + per - 1) / per);
 }
 
+// nb blocks of the entries, of 64 grid points each where there are enough of
+// them, of 16 where the workgroups would leave most of the chip idle (32 per row:
+// n = 2000, 16 blocks, 20.8 us at 64 and 10.4 at 16; n = 100k, 64 per row, 1000
+// blocks, 67 us at 64, 80 at 32, 121 at 16, where each entry's quotient and
+// gathers are repeated).
+template <bool CSR>
+static hipError_t chi_sums(const int32_t* idx, const float* d2, const int64_t* rowptr, const int32_t* rowid, int n,
+                           const float* rho, int64_t nnz, int k, int G, double e_min, double e_max,
+                           const double* scale_dev, int64_t per_block, int nb, double* partial, TuneResult* out,
+                           hipStream_t st)
+{
+    auto go = [&](auto kernel, int group) {
+        hipLaunchKernelGGL(kernel, dim3(nb, (G + group - 1) / group), dim3(CHI_BLOCK), 0, st, idx, d2, rowptr, rowid,
+                           n, rho, nnz, k, G, e_min, e_max, scale_dev, per_block, partial);
+    };
+    if (nb <= CHI_SPLIT)
+        go(k_chi_partial<CSR, 16>, 16);
+    else
+        go(k_chi_partial<CSR, 64>, 64);
+    if (nb <= CHI_FEW) {
+        hipLaunchKernelGGL(k_chi_finish, dim3(1), dim3(256), 0, st, partial, nb, G, e_min, e_max, scale_dev, out);
+    } else {
+        hipLaunchKernelGGL(k_chi_reduce, dim3(G), dim3(256), 0, st, partial, nb, G, CSR ? rowptr + n : nullptr,
+                           per_block, out);
+        hipLaunchKernelGGL(k_chi_finish, dim3(1), dim3(256), 0, st, nullptr, 0, G, e_min, e_max, scale_dev, out);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_chi(const int32_t* idx, const float* d2, const float* rho, int64_t nnz, int k, int G, double e_min,
                       double e_max, const double* scale_dev, double* partial, TuneResult* out, hipStream_t st)
 {
-    const int nb = chi_num_blocks(nnz);
-    hipLaunchKernelGGL(k_chi_partial<false>, dim3(nb), dim3(CHI_BLOCK), 0, st, idx, d2, nullptr, nullptr, 0, rho, nnz,
-                       k, G, e_min, e_max, scale_dev, chi_per_block(nnz), partial);
-    hipLaunchKernelGGL(k_chi_reduce, dim3(G), dim3(256), 0, st, partial, nb, G, nullptr, 0, out);
-    hipLaunchKernelGGL(k_chi_finish, dim3(1), dim3(256), 0, st, G, e_min, e_max, scale_dev, out);
-    return hipGetLastError();
+    return chi_sums<false>(idx, d2, nullptr, nullptr, 0, rho, nnz, k, G, e_min, e_max, scale_dev, chi_per_block(nnz),
+                           chi_num_blocks(nnz), partial, out, st);
 }
 
 int logsum_num_blocks(int n) { return min(1024, (n + 255) / 256); }
@@ -889,13 +989,8 @@ hipError_t launch_chi_csr(const int64_t* rowptr, const int32_t* rowid, const int
                           const double* scale_dev, double* partial, TuneResult* out, hipStream_t st)
 {
     // blocks sized for the expected count; enough of them for the largest
-    const int nb = chi_csr_blocks(nnz_hint, nnz_cap);
-    hipLaunchKernelGGL(k_chi_partial<true>, dim3(nb), dim3(CHI_BLOCK), 0, st, col, d2, rowptr, rowid, n, rho, nnz_cap,
-                       0, G, e_min, e_max, scale_dev, chi_per_block(nnz_hint), partial);
-    hipLaunchKernelGGL(k_chi_reduce, dim3(G), dim3(256), 0, st, partial, nb, G, rowptr + n, chi_per_block(nnz_hint),
-                       out);
-    hipLaunchKernelGGL(k_chi_finish, dim3(1), dim3(256), 0, st, G, e_min, e_max, scale_dev, out);
-    return hipGetLastError();
+    return chi_sums<true>(col, d2, rowptr, rowid, n, rho, nnz_cap, 0, G, e_min, e_max, scale_dev,
+                          chi_per_block(nnz_hint), chi_csr_blocks(nnz_hint, nnz_cap), partial, out, st);
 }
 
 hipError_t launch_qpass_csr(const int64_t* rowptr, const int32_t* col, const float* d2, int n, const float* rho,
