@@ -28,12 +28,12 @@ static void fixed_buffers(kvb_ctx ctx, Carve& dev, Carve& host)
 {
     ctx->tune_dev = dev.take<kvb::TuneResult>(1);
     ctx->build_dev = dev.take<BuildDev>(1);
-    ctx->fb_count_dev = dev.take<int>(1);
-    ctx->pairs_dev = dev.take<unsigned long long>(1);
+    ctx->pairs_dev = dev.take<unsigned long long>(PAIR_WORDS + 1);
+    ctx->fb_count_dev = reinterpret_cast<int*>(ctx->pairs_dev + PAIR_WORDS);
     ctx->tune_host = host.take<kvb::TuneResult>(1);
     ctx->build_host = host.take<BuildDev>(1);
     ctx->fb_count_host = host.take<int>(1);
-    ctx->pairs_host = host.take<unsigned long long>(1);
+    ctx->pairs_host = host.take<unsigned long long>(PAIR_WORDS);
     ctx->union_host = host.take<unsigned long long>(2);
     ctx->spec_host = host.take<double>(2 * SPEC_MAX);
 }
@@ -230,8 +230,7 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
     float* fb_bound = nullptr;
     const kvb::FallbackWork fw = take_fallback(cv, nn, &fb_bound);
 
-    KVB_HIP(ctx, hipMemsetAsync(ctx->fb_count_dev, 0, sizeof(int), ctx->stream));
-    KVB_HIP(ctx, hipMemsetAsync(ctx->pairs_dev, 0, sizeof(unsigned long long), ctx->stream));
+    KVB_HIP(ctx, hipMemsetAsync(ctx->pairs_dev, 0, COUNTER_BYTES, ctx->stream));
     float lb_scale = 1.0f;
     int kstride = kp;
     float* Xs = nullptr;        // curve-ordered samples (lists are then stored in that order)
@@ -380,10 +379,12 @@ int kvb_knn_pairs(kvb_ctx ctx, double* pairs_host)
 {
     if (check_ctx(ctx)) return KVB_E_INVALID;
     KVB_REQUIRE(ctx, pairs_host != nullptr, "pairs_host must be non-null");
-    KVB_HIP(ctx, hipMemcpyAsync(ctx->pairs_host, ctx->pairs_dev, sizeof(unsigned long long), hipMemcpyDeviceToHost,
+    KVB_HIP(ctx, hipMemcpyAsync(ctx->pairs_host, ctx->pairs_dev, PAIR_BYTES, hipMemcpyDeviceToHost,
                                 ctx->stream));
     KVB_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    *pairs_host = static_cast<double>(*ctx->pairs_host);
+    unsigned long long pairs = 0;
+    for (int s = 0; s < kvb::PAIR_SLOTS; ++s) pairs += ctx->pairs_host[s * kvb::PAIR_STRIDE];
+    *pairs_host = static_cast<double>(pairs);
     return KVB_OK;
 }
 

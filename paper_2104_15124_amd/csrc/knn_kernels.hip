@@ -143,7 +143,7 @@ __device__ __forceinline__ void score_tile(const float (&q)[R][M], const float (
                 uint64_t b = lane < bc[r] ? buf[r * WAVE + lane] : KEY_INF;
                 merge_into_list<E>(L[r], b);
                 bc[r] = 0;
-                tau[r] = key_dist(list_at<E>(L[r], kp - 1));
+                tau[r] = fminf(tau[r], key_dist(list_at<E>(L[r], kp - 1)));
                 mask = __ballot(valid && d <= tau[r]);
                 cnt = __popcll(mask);
                 wave_lds_sync();
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
             if (lane == 0) slast_out[i] = sl;
         }
     }
-    if (pair_count && lane == 0) atomicAdd(pair_count, pairs);
+    count_pairs(pair_count, pairs);
 }
 
 // ---- spatial order of the direct path
@@ -1309,7 +1309,7 @@ hipError_t launch_spatial_layout(const float* X, int n, int m, const int32_t* pe
 }
 
 template <int M, int R>
-static hipError_t launch_select_m(const SpatialView& sv, int n, int kp, uint64_t* keys, float* slast,
+static hipError_t launch_select_r(const SpatialView& sv, int n, int kp, uint64_t* keys, float* slast,
                                   unsigned long long* pairs, hipStream_t st)
 {
     const int rows_per_block = 4 * R;
@@ -1323,23 +1323,34 @@ static hipError_t launch_select_m(const SpatialView& sv, int n, int kp, uint64_t
     return hipGetLastError();
 }
 
+// Rows per wavefront: one while the rows are few enough for every wavefront to
+// be resident at once (sphere, n = 2000: 13 us at 1 row, 18 at 2, 37 at 5; 32000:
+// 146 against 151), two beyond (torus, n = 100k: 230 us at 1, 226 at 2, 240 at 3,
+// 268 at 5): more rows share a tile's loads and box tests, but scan each
+// other's tiles.
+constexpr int SELECT_ONE_ROW = 32768;
+
+template <int M>
+static hipError_t launch_select_m(const SpatialView& sv, int n, int kp, uint64_t* keys, float* slast,
+                                  unsigned long long* pairs, hipStream_t st)
+{
+    return n <= SELECT_ONE_ROW ? launch_select_r<M, 1>(sv, n, kp, keys, slast, pairs, st)
+                               : launch_select_r<M, 2>(sv, n, kp, keys, slast, pairs, st);
+}
+
 hipError_t launch_select_direct(const float* Xs, const float* tbox, const float* sbox, int n, int m, int kp,
                                 uint64_t* keys, float* slast, unsigned long long* pairs, hipStream_t st)
 {
     const SpatialView sv = {Xs, tbox, sbox};
-    // five rows per wavefront up to m = 4: each tile's loads and box tests
-    // serve more rows than at four, while the rows' union of near tiles stays
-    // small (torus, n = 100k: 438 us at 4 rows, 357 at 5, 365 at 6, 379 at 7);
-    // four beyond, where a fifth row's coordinates and list would spill
     switch (m) {
-    case 1: return launch_select_m<1, 5>(sv, n, kp, keys, slast, pairs, st);
-    case 2: return launch_select_m<2, 5>(sv, n, kp, keys, slast, pairs, st);
-    case 3: return launch_select_m<3, 5>(sv, n, kp, keys, slast, pairs, st);
-    case 4: return launch_select_m<4, 5>(sv, n, kp, keys, slast, pairs, st);
-    case 5: return launch_select_m<5, 4>(sv, n, kp, keys, slast, pairs, st);
-    case 6: return launch_select_m<6, 4>(sv, n, kp, keys, slast, pairs, st);
-    case 7: return launch_select_m<7, 4>(sv, n, kp, keys, slast, pairs, st);
-    case 8: return launch_select_m<8, 4>(sv, n, kp, keys, slast, pairs, st);
+    case 1: return launch_select_m<1>(sv, n, kp, keys, slast, pairs, st);
+    case 2: return launch_select_m<2>(sv, n, kp, keys, slast, pairs, st);
+    case 3: return launch_select_m<3>(sv, n, kp, keys, slast, pairs, st);
+    case 4: return launch_select_m<4>(sv, n, kp, keys, slast, pairs, st);
+    case 5: return launch_select_m<5>(sv, n, kp, keys, slast, pairs, st);
+    case 6: return launch_select_m<6>(sv, n, kp, keys, slast, pairs, st);
+    case 7: return launch_select_m<7>(sv, n, kp, keys, slast, pairs, st);
+    case 8: return launch_select_m<8>(sv, n, kp, keys, slast, pairs, st);
     default: return hipErrorInvalidValue;
     }
 }

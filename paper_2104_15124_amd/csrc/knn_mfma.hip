@@ -600,7 +600,7 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
             wave_lds_sync();
         }
     }
-    if (pair_count && lane == 0) atomicAdd(pair_count, pairs);
+    count_pairs(pair_count, pairs);
 
     if constexpr (LEARNED) return;
     // certificate lower bound for the candidates left out of each list

@@ -827,7 +827,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         }
         wave_lds_sync();
     }
-    if (pair_count && lane == 0) atomicAdd(pair_count, pairs);
+    count_pairs(pair_count, pairs);
 
     // certificate lower bound for the candidates left out of each list
     if (lane < nq_valid) {

@@ -9,9 +9,15 @@
 #include <string>
 #include <vector>
 
+#include "kvb_device.h"
 #include "kvb_kernels.h"
 
 namespace kvbh {
+
+// a k-NN call's counters, cleared together: the scored pairs, then the fallback rows
+constexpr size_t PAIR_WORDS = size_t(kvb::PAIR_SLOTS) * kvb::PAIR_STRIDE;
+constexpr size_t PAIR_BYTES = PAIR_WORDS * sizeof(unsigned long long);
+constexpr size_t COUNTER_BYTES = PAIR_BYTES + sizeof(int);
 
 struct ProfPair {
     int slot;
@@ -74,7 +80,7 @@ struct kvb_ctx_s {
     kvbh::BuildDev* build_host = nullptr;   // pinned
     int* fb_count_dev = nullptr;            // fallback rows of the last kvb_knn
     int* fb_count_host = nullptr;           // pinned
-    unsigned long long* pairs_dev = nullptr;   // candidate pairs scored by the last kvb_knn
+    unsigned long long* pairs_dev = nullptr;   // candidate pairs scored by the last kvb_knn (see count_pairs)
     unsigned long long* pairs_host = nullptr;  // pinned
     unsigned long long* union_host = nullptr;  // pinned [2]: reverse entries / check flags, invalid-input flag
     double* spec_host = nullptr;            // pinned [2 * SPEC_MAX]: eigenvalues in, coefficients out (spectral calls)

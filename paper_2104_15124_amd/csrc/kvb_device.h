@@ -236,6 +236,15 @@ __device__ __forceinline__ uint64_t list_at(const uint64_t (&L)[E], int t)
     return readlane_u64(v, src);
 }
 
+// Candidate pairs scored, counted over PAIR_SLOTS counters a cache line apart: a
+// single counter takes one wavefront's addition every 12 ns or so, which alone
+// kept 100k wavefronts 1.2 ms. Whole wavefront; slots may be null.
+constexpr int PAIR_SLOTS = 64, PAIR_STRIDE = 16;
+__device__ __forceinline__ void count_pairs(unsigned long long* slots, unsigned long long pairs)
+{
+    if (slots && lane_id() == 0) atomicAdd(slots + (blockIdx.x % PAIR_SLOTS) * PAIR_STRIDE, pairs);
+}
+
 // ---------------------------------------------------------------- reductions
 __device__ __forceinline__ double wave_sum_f64(double v)
 {

@@ -369,8 +369,7 @@ int learned_knn(kvb_ctx ctx, const float* X, int n, int m, int k, int kp, int32_
     Acts a = carve_acts(cv, P, CH, 0, false);
     hipStream_t st = ctx->stream;
 
-    KVB_HIP(ctx, hipMemsetAsync(ctx->fb_count_dev, 0, sizeof(int), st));
-    KVB_HIP(ctx, hipMemsetAsync(ctx->pairs_dev, 0, sizeof(unsigned long long), st));
+    KVB_HIP(ctx, hipMemsetAsync(ctx->pairs_dev, 0, COUNTER_BYTES, st));
     {
         Prof pr(ctx, KVB_PROF_ROUTE);
         for (int off = 0; off < n; off += CH) {
