@@ -42,11 +42,15 @@ namespace kvb {
 // (m + 2) roundings, inside the relative margin the refine step allows for
 // the selection scores.
 //
-// Candidates passing the current threshold of a row are appended to a
-// 64-entry LDS buffer; a full buffer is merged into the row's register list by
-// a bitonic network, which also tightens the threshold. Keys carry curve
-// positions; the re-rank maps them to original indices and breaks ties on
-// those, so ties order as in I(x, k).
+// Candidates passing the current threshold of a row are appended to that row's
+// buffer in LDS, twice the list's capacity of 64 E keys. When a further tile
+// might not fit, bisection over the scores finds a threshold that between kp
+// and 64 E of the keys do not exceed; the keys beyond it are dropped and the
+// row's threshold is lowered to it. At the end the buffer, cut down in the same
+// way, is sorted once. (Merging every 64 keys into a sorted list took three to
+// five networks per row where one is enough: 64 nearest of 100k on the torus,
+// 226 to 170 us.) Keys carry curve positions; the re-rank maps them to original
+// indices and breaks ties on those, so ties order as in I(x, k).
 struct SpatialView {
     const float* Xs;      // [n, m] coordinates in curve order
     const float* tbox;    // [tiles, 2, m]: lower corner, then upper corner
@@ -118,39 +122,111 @@ __device__ __forceinline__ void load_tile(const SpatialView& sv, int n, int t, i
     jo = static_cast<uint32_t>(jp);   // curve position; the refine step maps it to the sample id
 }
 
-// Score one tile of 64 candidates against the wavefront's R rows and append
-// the keys that pass each row's threshold (see k_select_direct).
-template <int M, int R, int E>
-__device__ __forceinline__ void score_tile(const float (&q)[R][M], const float (&x)[M], uint32_t jo, bool valid, int n,
-                                           int t, int kp, int rows_here, int lane, uint64_t* buf, uint64_t (&L)[R][E],
-                                           float (&tau)[R], int (&bc)[R], unsigned long long& pairs)
+template <int M>
+__device__ __forceinline__ float pair_dist2(const float (&q)[M], const float (&x)[M])
 {
-    pairs += static_cast<unsigned long long>(min(TILE, n - t * TILE)) * rows_here;
+    float tt = q[0] - x[0];
+    float d = tt * tt;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float tt = q[r][0] - x[0];
-        float d = tt * tt;
+    for (int c = 1; c < M; ++c) {
+        tt = q[c] - x[c];
+        d = fmaf(tt, tt, d);
+    }
+    return d;
+}
+
+// Append the lanes' keys whose score does not exceed tau to a row's buffer
+// (which has room for them). Whole wavefront.
+__device__ __forceinline__ void append_keys(uint64_t* buf, int& count, float tau, float d, uint32_t j, bool valid)
+{
+    const bool in = valid && d <= tau;
+    const uint64_t mask = __ballot(in);
+    if (!mask) return;
+    if (in) buf[count + mbcnt64(mask)] = make_key(d, j);
+    count += __popcll(mask);
+}
+
+// The 64 E smallest of more keys than a threshold can part (hundreds of equal
+// scores), sorted, at the front of the buffer. Whole wavefront. (An LDS pointer:
+// through a generic one the stores would not be ordered with the caller's LDS
+// reads.)
+using lds_key = __attribute__((address_space(3))) uint64_t;
+template <int E>
+__device__ __noinline__ void sort_front(lds_key* buf, int count)
+{
+    const int lane = lane_id();
+    uint64_t v[2 * E];
 #pragma unroll
-        for (int c = 1; c < M; ++c) {
-            tt = q[r][c] - x[c];
-            d = fmaf(tt, tt, d);
-        }
-        uint64_t mask = __ballot(valid && d <= tau[r]);
-        if (mask) {
-            int cnt = __popcll(mask);
-            if (bc[r] + cnt > WAVE) {
-                wave_lds_sync();
-                uint64_t b = lane < bc[r] ? buf[r * WAVE + lane] : KEY_INF;
-                merge_into_list<E>(L[r], b);
-                bc[r] = 0;
-                tau[r] = fminf(tau[r], key_dist(list_at<E>(L[r], kp - 1)));
-                mask = __ballot(valid && d <= tau[r]);
-                cnt = __popcll(mask);
-                wave_lds_sync();
+    for (int s = 0; s < 2 * E; ++s) v[s] = s * WAVE + lane < count ? buf[s * WAVE + lane] : KEY_INF;
+    bitonic_sort<2 * E>(v);
+    wave_lds_sync();
+#pragma unroll
+    for (int s = 0; s < E; ++s) buf[s * WAVE + lane] = v[s];
+    wave_lds_sync();
+}
+
+// Drop the farthest of a buffer's count keys (64 E < count <= 128 E) until
+// between kp and 64 E are left, which hold the kp smallest; no score above the
+// new tau is among the kp smallest. Whole wavefront.
+template <int E>
+__device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau, int kp)
+{
+    const int lane = lane_id();
+    wave_lds_sync();
+    uint64_t v[2 * E];
+    float d[2 * E];
+#pragma unroll
+    for (int s = 0; s < 2 * E; ++s) {
+        v[s] = s * WAVE + lane < count ? buf[s * WAVE + lane] : KEY_INF;
+        d[s] = key_dist(v[s]);   // +inf past the end: above every threshold tried
+    }
+    // lo: fewer than kp scores do not exceed it; hi: at least kp do not
+    // (scores are >= 0: their bits order like integers)
+    uint32_t lo = 0u, hi = __builtin_amdgcn_readfirstlane(__float_as_uint(tau));
+    int at = count, below = 0;
+    bool parted = false;
+    for (int it = 0;; ++it) {
+        const float a = __uint_as_float(lo), b = __uint_as_float(hi);
+        // twice where the counts' share falls, then the middle; where neither
+        // lies inside (infinite or adjacent ends), the middle of the bits
+        const float share = it < 2 ? static_cast<float>((kp + WAVE * E) / 2 - below) *
+                                         __builtin_amdgcn_rcpf(static_cast<float>(at - below))
+                                   : 0.5f;
+        uint32_t mid = __builtin_amdgcn_readfirstlane(__float_as_uint(fmaf(share, b - a, a)));
+        if (!(mid > lo && mid < hi)) mid = lo + (hi - lo) / 2;
+        if (mid == lo) break;
+        int c = 0;
+#pragma unroll
+        for (int s = 0; s < 2 * E; ++s) c += __popcll(__ballot(d[s] <= __uint_as_float(mid)));
+        if (c < kp) {
+            lo = mid;
+            below = c;
+        } else {
+            hi = mid;
+            at = c;
+            if (c <= WAVE * E) {
+                parted = true;
+                break;
             }
-            if ((mask >> lane) & 1ull) buf[r * WAVE + bc[r] + mbcnt64(mask)] = make_key(d, jo);
-            bc[r] += cnt;
         }
+    }
+    if (parted) {
+        const float thr = __uint_as_float(hi);
+        int w = 0;
+#pragma unroll
+        for (int s = 0; s < 2 * E; ++s) {
+            const bool in = d[s] <= thr;
+            const uint64_t mask = __ballot(in);
+            if (in) buf[w + mbcnt64(mask)] = v[s];
+            w += __popcll(mask);
+        }
+        tau = thr;
+        count = at;
+        wave_lds_sync();
+    } else {
+        sort_front<E>((lds_key*)buf, count);
+        count = WAVE * E;
+        tau = fminf(tau, key_dist(buf[kp - 1]));
     }
 }
 
@@ -160,7 +236,8 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
                                                        float* __restrict__ slast_out,
                                                        unsigned long long* __restrict__ pair_count)
 {
-    __shared__ uint64_t sbuf[4][R][WAVE];
+    constexpr int CAP = WAVE * E;   // of a list; a buffer holds twice as many
+    __shared__ uint64_t sbuf[4][R][2 * CAP];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row0 = (blockIdx.x * 4 + wave) * R;   // curve position of the first row
@@ -173,60 +250,88 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
 #pragma unroll
         for (int c = 0; c < M; ++c) q[r][c] = sv.Xs[static_cast<size_t>(p) * M + c];
     }
-    uint64_t L[R][E];
     float tau[R];
     int bc[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-        for (int s = 0; s < E; ++s) L[r][s] = KEY_INF;
-        tau[r] = __uint_as_float(0x7F800000u);
-        bc[r] = 0;
-    }
-    uint64_t* buf = &sbuf[wave][0][0];
     const int rows_here = min(R, n - row0);
     unsigned long long pairs = 0;
 
     const int ntiles = (n + TILE - 1) / TILE;
     const int nsb = (ntiles + SB_TILES - 1) / SB_TILES;
     const int own_t = row0 / TILE;
+    // the tiles base + t, t a bit of tm: their loads issued TILE_BATCH at a time
+    auto scan_tiles = [&](int base, uint64_t tm) {
+        while (tm) {
+            int tb[TILE_BATCH];
+            float xb[TILE_BATCH][M];
+            uint32_t jb[TILE_BATCH];
+#pragma unroll
+            for (int u = 0; u < TILE_BATCH; ++u) {
+                tb[u] = -1;
+                jb[u] = 0;
+                if (tm) {
+                    tb[u] = base + __builtin_ctzll(tm);
+                    tm &= tm - 1;
+                    load_tile<M>(sv, n, tb[u], lane, xb[u], jb[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < TILE_BATCH; ++u) {
+                if (tb[u] < 0) continue;
+                const bool valid = tb[u] * TILE + lane < n;
+                pairs += static_cast<unsigned long long>(min(TILE, n - tb[u] * TILE)) * rows_here;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (bc[r] > 2 * CAP - WAVE) cut_buffer<E>(sbuf[wave][r], bc[r], tau[r], kp);
+                    append_keys(sbuf[wave][r], bc[r], tau[r], pair_dist2<M>(q[r], xb[u]), jb[u], valid);
+                }
+            }
+        }
+    };
     // seed: the own tile and its curve neighbours, unconditionally. Each row's
     // first threshold is a coarse upper bound of the kp-th smallest seed
     // distance (valid for the whole scan: the kp-th smallest of a subset is at
     // least the kp-th smallest overall), so the seeds append little more than kp.
     constexpr int NS = 2 * SEED_TILES + 1;
     const int a0 = max(0, own_t - SEED_TILES), a1 = min(ntiles - 1, own_t + SEED_TILES);
-    float xs[NS][M];
-    uint32_t js[NS];
-#pragma unroll
-    for (int u = 0; u < NS; ++u) load_tile<M>(sv, n, min(a0 + u, a1), lane, xs[u], js[u]);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        float ds[NS];
+    {
+        float xs[NS][M];
+        uint32_t js[NS];
+        bool ok[NS];
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
-            float tt = q[r][0] - xs[u][0];
-            float d = tt * tt;
-#pragma unroll
-            for (int c = 1; c < M; ++c) {
-                tt = q[r][c] - xs[u][c];
-                d = fmaf(tt, tt, d);
-            }
-            const bool ok = (a0 + u <= a1) && ((a0 + u) * TILE + lane < n);
-            ds[u] = ok ? d : __uint_as_float(0x7F800000u);
+            load_tile<M>(sv, n, min(a0 + u, a1), lane, xs[u], js[u]);
+            ok[u] = (a0 + u <= a1) && ((a0 + u) * TILE + lane < n);
         }
-        tau[r] = seed_threshold<NS>(ds, kp);
-    }
+        bool fits = true;
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int t = a0 + u;
-        if (t <= a1)
-            score_tile<M, R, E>(q, xs[u], js[u], t * TILE + lane < n, n, t, kp, rows_here, lane, buf, L, tau, bc,
-                                pairs);
+        for (int r = 0; r < R; ++r) {
+            float ds[NS];
+#pragma unroll
+            for (int u = 0; u < NS; ++u) ds[u] = ok[u] ? pair_dist2<M>(q[r], xs[u]) : __uint_as_float(0x7F800000u);
+            bc[r] = 0;
+            tau[r] = seed_threshold<NS>(ds, kp);
+            int c = 0;
+#pragma unroll
+            for (int u = 0; u < NS; ++u) c += __popcll(__ballot(ok[u] && ds[u] <= tau[r]));
+            // more equal scores than the buffer holds: tile by tile below
+            fits = fits && c <= 2 * CAP;
+            if (c <= 2 * CAP) {
+#pragma unroll
+                for (int u = 0; u < NS; ++u)
+                    append_keys(sbuf[wave][r], bc[r], tau[r], ds[u], js[u], ok[u]);
+            }
+        }
+        if (fits) {
+            pairs += static_cast<unsigned long long>(min(n, (a1 + 1) * TILE) - a0 * TILE) * rows_here;
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) bc[r] = 0;
+            wave_lds_sync();
+            scan_tiles(a0, (1ull << (a1 - a0 + 1)) - 1ull);
+        }
     }
     // then every superblock within reach of some row (boxes tested 64 at a
-    // time, one per lane), inside it every tile within reach (16 lanes), the
-    // tiles' loads issued TILE_BATCH at a time
+    // time, one per lane), inside it every tile within reach (16 lanes)
     for (int sb0 = 0; sb0 < nsb; sb0 += WAVE) {
         const int sbl = sb0 + lane;
         bool near = false;
@@ -239,45 +344,26 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
             bool tnear = false;
             if (lane < SB_TILES && tl < ntiles && (tl < a0 || tl > a1))
                 tnear = box_near_rows<M, R>(sv.tbox + static_cast<size_t>(tl) * 2 * M, q, tau);
-            uint64_t tm = __ballot(tnear);
-            while (tm) {
-                int tb[TILE_BATCH];
-                float xb[TILE_BATCH][M];
-                uint32_t jb[TILE_BATCH];
-#pragma unroll
-                for (int u = 0; u < TILE_BATCH; ++u) {
-                    tb[u] = -1;
-                    jb[u] = 0;
-                    if (tm) {
-                        tb[u] = sb * SB_TILES + __builtin_ctzll(tm);
-                        tm &= tm - 1;
-                        load_tile<M>(sv, n, tb[u], lane, xb[u], jb[u]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < TILE_BATCH; ++u)
-                    if (tb[u] >= 0)
-                        score_tile<M, R, E>(q, xb[u], jb[u], tb[u] * TILE + lane < n, n, tb[u], kp, rows_here, lane,
-                                            buf, L, tau, bc, pairs);
-            }
+            scan_tiles(sb * SB_TILES, __ballot(tnear));
         }
     }
-    wave_lds_sync();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (bc[r] > 0) {
-            uint64_t b = lane < bc[r] ? buf[r * WAVE + lane] : KEY_INF;
-            merge_into_list<E>(L[r], b);
-        }
+        if (bc[r] > CAP) cut_buffer<E>(sbuf[wave][r], bc[r], tau[r], kp);
+        wave_lds_sync();
         if (row0 + r < n) {
+            uint64_t L[E];
+#pragma unroll
+            for (int s = 0; s < E; ++s) L[s] = s * WAVE + lane < bc[r] ? sbuf[wave][r][s * WAVE + lane] : KEY_INF;
+            bitonic_sort<E>(L);
             const int i = row0 + r;   // lists are stored by curve position
             uint64_t* dst = keys_out + static_cast<size_t>(i) * kp;
 #pragma unroll
             for (int s = 0; s < E; ++s) {
                 const int t = s * WAVE + lane;
-                if (t < kp) dst[t] = L[r][s];
+                if (t < kp) dst[t] = L[s];
             }
-            const float sl = key_dist(list_at<E>(L[r], kp - 1));
+            const float sl = key_dist(list_at<E>(L, kp - 1));
             if (lane == 0) slast_out[i] = sl;
         }
     }
@@ -1324,10 +1410,10 @@ static hipError_t launch_select_r(const SpatialView& sv, int n, int kp, uint64_t
 }
 
 // Rows per wavefront: one while the rows are few enough for every wavefront to
-// be resident at once (sphere, n = 2000: 13 us at 1 row, 18 at 2, 37 at 5; 32000:
-// 146 against 151), two beyond (torus, n = 100k: 230 us at 1, 226 at 2, 240 at 3,
-// 268 at 5): more rows share a tile's loads and box tests, but scan each
-// other's tiles.
+// be resident at once (sphere, n = 2000: 14 us at 1 row, 21 at 2, 28 at 3; 32000:
+// 142 against 143), two beyond (torus, n = 100k: 183 us at 1, 170 at 2, 180 at 3;
+// 1M: 3.19, 2.82 and 2.80 ms): more rows share a tile's loads and box tests, but
+// scan each other's tiles.
 constexpr int SELECT_ONE_ROW = 32768;
 
 template <int M>
