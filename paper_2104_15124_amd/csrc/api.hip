@@ -345,7 +345,7 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
         Prof pr(ctx, KVB_PROF_KNN_REFINE);
         KVB_HIP(ctx, kvb::launch_refine(X, nn, m, k, kp, kstride, keys, slast, lb_scale, idx, d2, row_flags,
                                         ctx->fb_count_dev, fb_list, fb_bound, static_cast<int>(ctx->force_fallback),
-                                        Xs, perm, ctx->stream));
+                                        Xs, perm, nullptr, ctx->stream));
     }
     {
         Prof pr(ctx, KVB_PROF_KNN_FALLBACK);

@@ -598,100 +598,116 @@ __device__ __forceinline__ double dist2_f64(const float* __restrict__ a, const f
 // inside the group; the result reaches the lane that owns the candidate's key.
 // d[s] receives the distance of key slot s of this lane (unchanged where the
 // key is KEY_INF or the row itself).
+//
+// group_distances4: rows of float4 pieces (NIT per lane), two candidates per
+// group at a time, their sums reduced together: the first exchange leaves each
+// lane one of the two. No load is guarded, so all of a pass are in flight at
+// once (behind guards they waited for one another): pieces beyond the row are
+// read from zeros. 160 candidates of 128 coordinates per row: 4M rows along the
+// curve 38.5 to 21.5 ms, 1M rows by bucket 9.1 to 5.2 (four candidates at a
+// time: 21.9 and 5.5).
+__device__ const float4 g_zero4 = {0.f, 0.f, 0.f, 0.f};
+
+template <int E, int LPC, int NIT>
+__device__ __forceinline__ void group_distances4(const float* __restrict__ X, int m, int i, int kp,
+                                                 const uint64_t (&v)[E], double (&d)[E])
+{
+    constexpr int CPW = WAVE / LPC;   // groups
+    constexpr int U = 2;              // candidates per group at a time
+    const int lane = lane_id();
+    const int g = lane / LPC, gl = lane % LPC;
+    bool in[NIT];
+    double q[NIT][4];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int c = 4 * (gl + LPC * it);
+        in[it] = c < m;
+        const float4 t = in[it] ? *reinterpret_cast<const float4*>(X + static_cast<size_t>(i) * m + c) : g_zero4;
+        q[it][0] = t.x;
+        q[it][1] = t.y;
+        q[it][2] = t.z;
+        q[it][3] = t.w;
+    }
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+        const int cj = (v[s] != KEY_INF) ? static_cast<int>(key_idx(v[s])) : -1;
+        const int tend = min(kp, (s + 1) * WAVE);
+        for (int t0 = s * WAVE; t0 < tend; t0 += U * CPW) {
+            float4 p[U][NIT];
+            bool ok[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                // an invalid slot reads row i and is zeroed
+                const int t = t0 + u * CPW;
+                const int j = __shfl(cj, (t % WAVE) + g, WAVE);
+                ok[u] = j >= 0 && j != i && t + g < tend;
+                const float* x = X + static_cast<size_t>(ok[u] ? j : i) * m + 4 * gl;
+#pragma unroll
+                for (int it = 0; it < NIT; ++it) {
+                    const float4* src = in[it] ? reinterpret_cast<const float4*>(x + 4 * LPC * it) : &g_zero4;
+                    p[u][it] = *src;
+                }
+            }
+            double acc[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                double a = 0.0;
+#pragma unroll
+                for (int it = 0; it < NIT; ++it) {
+                    const double e0 = q[it][0] - p[u][it].x, e1 = q[it][1] - p[u][it].y;
+                    const double e2 = q[it][2] - p[u][it].z, e3 = q[it][3] - p[u][it].w;
+                    a = fma(e0, e0, a);
+                    a = fma(e1, e1, a);
+                    a = fma(e2, e2, a);
+                    a = fma(e3, e3, a);
+                }
+                acc[u] = ok[u] ? a : 0.0;
+            }
+            // lane gl ends with candidate gl mod 2's sum over the group
+            const bool odd = gl & 1;
+            double r = (odd ? acc[1] : acc[0]) + shfl_xor_f64(odd ? acc[0] : acc[1], 1);
+#pragma unroll
+            for (int o = 2; o < LPC; o <<= 1) r += shfl_xor_f64(r, o);
+            // to the lanes that own the candidates
+            const int at = lane - (t0 % WAVE);
+            const bool mine = at >= 0 && at < U * CPW;
+            const double got = __shfl(r, mine ? (at % CPW) * LPC + at / CPW : 0, WAVE);
+            if (mine) d[s] = got;
+        }
+    }
+}
+
 template <int E, int LPC>
 __device__ __forceinline__ void group_distances(const float* __restrict__ X, int m, int i, int kp, bool vec4,
                                                 const uint64_t (&v)[E], double (&d)[E])
 {
+    if (vec4) {
+        if (m > 12 * LPC)
+            group_distances4<E, LPC, 4>(X, m, i, kp, v, d);
+        else
+            group_distances4<E, LPC, 3>(X, m, i, kp, v, d);
+        return;
+    }
     constexpr int CPW = WAVE / LPC;   // candidates per pass
-    // pieces of the row per lane: float4 pieces (m <= 16 LPC) or floats (m <= 16 LPC)
-    constexpr int QMAX = 16;
+    constexpr int QMAX = 16;          // floats of the row per lane (m <= 16 LPC)
     const int lane = lane_id();
     const int g = lane / LPC, gl = lane % LPC;
     const float* xi = X + static_cast<size_t>(i) * m;
-    float4 q4[4];
     float q1[QMAX];
-    const int nit = vec4 ? (m + 4 * LPC - 1) / (4 * LPC) : (m + LPC - 1) / LPC;
+    const int nit = (m + LPC - 1) / LPC;
 #pragma unroll
     for (int it = 0; it < QMAX; ++it) {
         q1[it] = 0.f;
-        if (!vec4 && it < nit) {
+        if (it < nit) {
             const int c = gl + LPC * it;
             if (c < m) q1[it] = xi[c];
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        q4[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (vec4 && it < nit) {
-            const int c = 4 * (gl + LPC * it);
-            if (c < m) q4[it] = *reinterpret_cast<const float4*>(xi + c);
         }
     }
 #pragma unroll
     for (int s = 0; s < E; ++s) {
         const int cj = (v[s] != KEY_INF) ? static_cast<int>(key_idx(v[s])) : -1;
         const int tend = min(kp, (s + 1) * WAVE);
-        int t0 = s * WAVE;
-        if (vec4) {
-            // two passes at a time: both candidates' pieces are loaded before
-            // either is summed (an invalid slot reads row i and is zeroed)
-            for (; t0 < tend; t0 += 2 * CPW) {
-                const int t1 = t0 + CPW;
-                const int ja = __shfl(cj, (t0 % WAVE) + g, WAVE);
-                const int jb = __shfl(cj, (t1 % WAVE) + g, WAVE);
-                const bool oka = ja >= 0 && ja != i && t0 + g < tend;
-                const bool okb = t1 < tend && jb >= 0 && jb != i && t1 + g < tend;
-                const float* xa = X + static_cast<size_t>(oka ? ja : i) * m;
-                const float* xb = X + static_cast<size_t>(okb ? jb : i) * m;
-                float4 pa[4], pb[4];
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int c = 4 * (gl + LPC * it);
-                    const bool in = it < nit && c < m;
-                    pa[it] = in ? *reinterpret_cast<const float4*>(xa + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    pb[it] = in ? *reinterpret_cast<const float4*>(xb + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-                double acca = 0.0, accb = 0.0;
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int c = 4 * (gl + LPC * it);
-                    if (it < nit && c < m) {
-                        const double a0 = static_cast<double>(q4[it].x) - pa[it].x;
-                        const double a1 = static_cast<double>(q4[it].y) - pa[it].y;
-                        const double a2 = static_cast<double>(q4[it].z) - pa[it].z;
-                        const double a3 = static_cast<double>(q4[it].w) - pa[it].w;
-                        acca = fma(a0, a0, acca);
-                        acca = fma(a1, a1, acca);
-                        acca = fma(a2, a2, acca);
-                        acca = fma(a3, a3, acca);
-                        const double b0 = static_cast<double>(q4[it].x) - pb[it].x;
-                        const double b1 = static_cast<double>(q4[it].y) - pb[it].y;
-                        const double b2 = static_cast<double>(q4[it].z) - pb[it].z;
-                        const double b3 = static_cast<double>(q4[it].w) - pb[it].w;
-                        accb = fma(b0, b0, accb);
-                        accb = fma(b1, b1, accb);
-                        accb = fma(b2, b2, accb);
-                        accb = fma(b3, b3, accb);
-                    }
-                }
-                if (!oka) acca = 0.0;
-                if (!okb) accb = 0.0;
-#pragma unroll
-                for (int o = 1; o < LPC; o <<= 1) {
-                    acca += shfl_xor_f64(acca, o);
-                    accb += shfl_xor_f64(accb, o);
-                }
-                // the group leaders' sums go to the owner lanes
-                const int sa = (lane - (t0 % WAVE)) * LPC;
-                const double gota = __shfl(acca, sa >= 0 && sa < WAVE ? sa : 0, WAVE);
-                if (lane >= t0 % WAVE && lane < t0 % WAVE + CPW) d[s] = gota;
-                const int sb = (lane - (t1 % WAVE)) * LPC;
-                const double gotb = __shfl(accb, sb >= 0 && sb < WAVE ? sb : 0, WAVE);
-                if (t1 < tend && lane >= t1 % WAVE && lane < t1 % WAVE + CPW) d[s] = gotb;
-            }
-            continue;
-        }
-        for (; t0 < tend; t0 += CPW) {
+        for (int t0 = s * WAVE; t0 < tend; t0 += CPW) {
             const int owner = (t0 % WAVE) + g;                 // lane holding this group's candidate
             const int j = __shfl(cj, owner, WAVE);
             double acc = 0.0;
@@ -729,6 +745,11 @@ __device__ __forceinline__ void group_distances(const float* __restrict__ X, int
 // from the recomputed distances only in the last bits) skip the sorting
 // network.
 //
+// Rows are taken in the order of the workgroups' XCDs (xcd_block): the rows in
+// flight on an XCD are neighbours along the curve or, with `order` (learned
+// routing: the samples grouped by their first bucket), of one bucket, and find
+// each other's candidates in its L2 (1M rows by bucket 13.5 to 9.1 ms).
+//
 // CV (curve-ordered scans): lists and bounds are stored by curve position r, their
 // keys hold curve positions; the candidates are read from the curve-ordered
 // copy Xs (neighbouring rows read neighbouring samples) and the keys are
@@ -741,11 +762,13 @@ __global__ __launch_bounds__(256) void k_refine(const float* __restrict__ X, int
                                                 int32_t* __restrict__ flags_out,
                                                 int* __restrict__ fb_count, int* __restrict__ fb_list,
                                                 float* __restrict__ fb_bound, int force_period,
-                                                const float* __restrict__ Xs, const int32_t* __restrict__ perm)
+                                                const float* __restrict__ Xs, const int32_t* __restrict__ perm,
+                                                const int32_t* __restrict__ order)
 {
     const int lane = lane_id();
-    const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // stored row
-    if (r >= n) return;
+    const int p = xcd_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (p >= n) return;
+    const int r = !CV && order ? order[p] : p;   // stored row
     const int i = CV ? perm[r] : r;   // sample id
     const float* xi = CV ? Xs + static_cast<size_t>(r) * m : X + static_cast<size_t>(i) * m;
     // candidate distances, self removed
@@ -1445,24 +1468,24 @@ template <int LPC, bool CV>
 static void launch_refine_l(const float* X, int n, int m, int k, int kp, int kstride, const uint64_t* keys,
                             const float* slast, float lb_scale, int32_t* idx, float* d2, int32_t* flags, int* fb_count,
                             int* fb_list, float* fb_bound, int force_period, const float* Xs, const int32_t* perm,
-                            hipStream_t st)
+                            const int32_t* order, hipStream_t st)
 {
     const dim3 grid((n + 3) / 4), block(256);
     if (kp <= 64)
         hipLaunchKernelGGL((k_refine<1, LPC, CV>), grid, block, 0, st, X, n, m, k, kp, kstride, keys, slast, lb_scale,
-                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm);
+                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm, order);
     else if (kp <= 128)
         hipLaunchKernelGGL((k_refine<2, LPC, CV>), grid, block, 0, st, X, n, m, k, kp, kstride, keys, slast, lb_scale,
-                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm);
+                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm, order);
     else
         hipLaunchKernelGGL((k_refine<4, LPC, CV>), grid, block, 0, st, X, n, m, k, kp, kstride, keys, slast, lb_scale,
-                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm);
+                           idx, d2, flags, fb_count, fb_list, fb_bound, force_period, Xs, perm, order);
 }
 
 hipError_t launch_refine(const float* X, int n, int m, int k, int kp, int kstride, const uint64_t* keys,
                          const float* slast, float lb_scale, int32_t* idx, float* d2, int32_t* flags,
                          int* fb_count, int* fb_list, float* fb_bound, int force_period, const float* Xs,
-                         const int32_t* perm, hipStream_t st)
+                         const int32_t* perm, const int32_t* order, hipStream_t st)
 {
     // rows of up to 24 floats stay with one lane per candidate; longer rows are
     // read by groups of lanes, each lane covering up to 4 float4 pieces (the
@@ -1472,10 +1495,10 @@ hipError_t launch_refine(const float* X, int n, int m, int k, int kp, int kstrid
     do {                                                                                                              \
         if (perm)                                                                                                     \
             launch_refine_l<LPC, true>(X, n, m, k, kp, kstride, keys, slast, lb_scale, idx, d2, flags, fb_count,     \
-                                       fb_list, fb_bound, force_period, Xs, perm, st);                                \
+                                       fb_list, fb_bound, force_period, Xs, perm, nullptr, st);                                \
         else                                                                                                          \
             launch_refine_l<LPC, false>(X, n, m, k, kp, kstride, keys, slast, lb_scale, idx, d2, flags, fb_count,    \
-                                        fb_list, fb_bound, force_period, nullptr, nullptr, st);                       \
+                                        fb_list, fb_bound, force_period, nullptr, nullptr, order, st);                       \
     } while (0)
     if (m <= 24)
         KVB_REFINE(0);

@@ -83,19 +83,6 @@ __device__ __forceinline__ float box_bound(const float* __restrict__ b, const fl
     return d > 0.f ? d * d * (1.f - 2e-6f) : 0.f;
 }
 
-// Workgroups are dispatched to the 8 XCDs round robin (workgroup b to XCD
-// b mod 8). Renumbering them so that each XCD receives one contiguous range of
-// curve positions makes the workgroups resident on an XCD at one time
-// neighbours along the curve, whose scans read the same candidate tiles
-// through that XCD's L2.
-__device__ __forceinline__ int xcd_block()
-{
-    constexpr int XCDS = 8;
-    const int b = blockIdx.x, g = gridDim.x;
-    const int x = b % XCDS, per = g / XCDS, rem = g % XCDS;
-    return x * per + min(x, rem) + b / XCDS;
-}
-
 // Sort query q's list in place (whole wavefront) and return its kp-th score.
 template <int E>
 __device__ __noinline__ float sort_query_list(uint64_t* __restrict__ dst, int kp)

@@ -236,6 +236,19 @@ __device__ __forceinline__ uint64_t list_at(const uint64_t (&L)[E], int t)
     return readlane_u64(v, src);
 }
 
+// Workgroups are dispatched to the 8 XCDs round robin (workgroup b to XCD
+// b mod 8). Renumbering them so that each XCD receives one contiguous range
+// makes the workgroups resident on an XCD at one time neighbours in the order
+// of their work (curve positions, rows grouped by bucket), which read the same
+// candidates through that XCD's L2.
+__device__ __forceinline__ int xcd_block()
+{
+    constexpr int XCDS = 8;
+    const int b = blockIdx.x, g = gridDim.x;
+    const int x = b % XCDS, per = g / XCDS, rem = g % XCDS;
+    return x * per + min(x, rem) + b / XCDS;
+}
+
 // Candidate pairs scored, counted over PAIR_SLOTS counters a cache line apart: a
 // single counter takes one wavefront's addition every 12 ns or so, which alone
 // kept 100k wavefronts 1.2 ms. Whole wavefront; slots may be null.

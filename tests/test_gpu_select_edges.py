@@ -43,6 +43,12 @@ def test_contraction_lengths(gpu_lib, mode, m):
     check(gpu_lib, workloads.gaussian_mixture(900, seed=m, m=m), 40, 32, mode)
 
 
+@pytest.mark.parametrize("m", [28, 40, 48, 52, 60, 72, 96, 100, 124, 144, 192, 196, 252])
+def test_recomputed_row_lengths(gpu_lib, m):
+    # every number of float4 pieces per lane, whole and partial
+    check(gpu_lib, workloads.gaussian_mixture(700, seed=m, m=m), 30, 67, "f32")
+
+
 @pytest.mark.parametrize("k,margin", [(64, 32), (65, 32), (96, 32), (97, 32), (160, 32), (193, 32), (224, 32),
                                       (256, 0)])
 def test_list_lengths(gpu_lib, k, margin):
