@@ -371,56 +371,82 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
 }
 
 // ---- spatial order of the direct path
-// Bounding box of the samples: per-block partial minima / maxima, then one block.
-__global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ X, int n, int m, int rows_per_block,
-                                                      float* __restrict__ part)
+// Bounding box of the samples: per-block partial minima / maxima (k_morton
+// reduces them). Coordinates together, one barrier: 3 us at 2000 x 3 and 5 at
+// 100k x 3 (6 and 14 with a tree of eight barriers per coordinate).
+constexpr int BBOX_THREADS = 1024;
+template <int M>
+__global__ __launch_bounds__(BBOX_THREADS) void k_bbox_partial(const float* __restrict__ X, int n, int rows_per_block,
+                                                               float* __restrict__ part)
 {
-    __shared__ float sl[256], sh[256];
+    constexpr int WAVES = BBOX_THREADS / WAVE;
+    __shared__ float s_b[WAVES][2 * M];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int r0 = blockIdx.x * rows_per_block, r1 = min(n, r0 + rows_per_block);
-    for (int c = 0; c < m; ++c) {
-        float lo = __uint_as_float(0x7F800000u), hi = -__uint_as_float(0x7F800000u);
-        for (int r = r0 + threadIdx.x; r < r1; r += blockDim.x) {
-            const float v = X[static_cast<size_t>(r) * m + c];
-            lo = fminf(lo, v);
-            hi = fmaxf(hi, v);
+    const float inf = __uint_as_float(0x7F800000u);
+    float lo[M], hi[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+        lo[c] = inf;
+        hi[c] = -inf;
+    }
+#pragma unroll 4
+    for (int r = r0 + threadIdx.x; r < r1; r += BBOX_THREADS) {
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            const float v = X[static_cast<size_t>(r) * M + c];
+            lo[c] = fminf(lo[c], v);
+            hi[c] = fmaxf(hi[c], v);
         }
-        sl[threadIdx.x] = lo;
-        sh[threadIdx.x] = hi;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (threadIdx.x < o) {
-                sl[threadIdx.x] = fminf(sl[threadIdx.x], sl[threadIdx.x + o]);
-                sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + o]);
-            }
-            __syncthreads();
+    }
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            lo[c] = fminf(lo[c], shfl_xor_f32(lo[c], o));
+            hi[c] = fmaxf(hi[c], shfl_xor_f32(hi[c], o));
         }
-        if (threadIdx.x == 0) {
-            part[static_cast<size_t>(blockIdx.x) * 2 * m + c] = sl[0];
-            part[static_cast<size_t>(blockIdx.x) * 2 * m + m + c] = sh[0];
+        if (lane == 0) {
+            s_b[wave][c] = lo[c];
+            s_b[wave][M + c] = hi[c];
         }
-        __syncthreads();
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * M) {
+        const int c = threadIdx.x;
+        float v = s_b[0][c];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v = c < M ? fminf(v, s_b[w][c]) : fmaxf(v, s_b[w][c]);
+        part[static_cast<size_t>(blockIdx.x) * 2 * M + c] = v;
     }
 }
 
 // Morton code of every sample: each coordinate quantised to b = min(31, 32 / m) bits
-// over the bounding box (the box partials are reduced here, redundantly per
-// thread: at most 1024 partials of 2m values), bits interleaved from the most
-// significant. value = sample index, so a stable sort breaks ties by index.
+// over the bounding box (every workgroup reduces the box partials: at most 1024
+// of 2m values), bits interleaved from the most significant. value = sample
+// index, so a stable sort breaks ties by index.
 __global__ __launch_bounds__(256) void k_morton(const float* __restrict__ X, int n, int m, int bits,
                                                 const float* __restrict__ part, int nparts,
                                                 uint32_t* __restrict__ code, int32_t* __restrict__ vals)
 {
     __shared__ float s_lo[8], s_scale[8];
-    if (threadIdx.x < m) {
-        const int c = threadIdx.x;
+    // a wavefront per coordinate, a partial per lane
+    for (int c = threadIdx.x >> 6; c < m; c += 4) {
         float lo = __uint_as_float(0x7F800000u), hi = -__uint_as_float(0x7F800000u);
-        for (int b = 0; b < nparts; ++b) {
+        for (int b = lane_id(); b < nparts; b += WAVE) {
             lo = fminf(lo, part[static_cast<size_t>(b) * 2 * m + c]);
             hi = fmaxf(hi, part[static_cast<size_t>(b) * 2 * m + m + c]);
         }
-        const float ext = hi - lo;
-        s_lo[c] = lo;
-        s_scale[c] = ext > 0.f ? static_cast<float>(1ull << bits) / ext : 0.f;
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            lo = fminf(lo, shfl_xor_f32(lo, o));
+            hi = fmaxf(hi, shfl_xor_f32(hi, o));
+        }
+        if (lane_id() == 0) {
+            const float ext = hi - lo;
+            s_lo[c] = lo;
+            s_scale[c] = ext > 0.f ? static_cast<float>(1ull << bits) / ext : 0.f;
+        }
     }
     __syncthreads();
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -472,29 +498,70 @@ static void gather_rows(const float* X, int n, int m, const int32_t* perm, float
         hipLaunchKernelGGL(k_gather_rows, grid, dim3(256), 0, st, X, n, m, perm, Xs);
 }
 
-// Box of `span` consecutive rows starting at row `first` of each group g
-// (rows beyond n are ignored); used for tiles over Xs and for superblocks over
-// tile boxes (span 16, rows = boxes, with `boxes` set).
-__global__ __launch_bounds__(256) void k_group_boxes(const float* __restrict__ src, int rows, int m, int span,
-                                                     int groups, int boxes, float* __restrict__ out)
+// Curve-ordered samples, tile boxes and superblock boxes in one launch: a
+// workgroup per superblock, a wavefront per tile, a sample per lane: 3 us at
+// 2000 x 3 and 5 at 100k x 3 (16 and 19 in three launches of one thread per
+// coordinate and box, each reading its rows one after the other).
+constexpr int LAYOUT_THREADS = SB_TILES * WAVE;
+template <int M>
+__global__ __launch_bounds__(LAYOUT_THREADS) void k_spatial_layout(const float* __restrict__ X, int n,
+                                                                   const int32_t* __restrict__ perm,
+                                                                   float* __restrict__ Xs, float* __restrict__ tbox,
+                                                                   float* __restrict__ sbox)
 {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= static_cast<int64_t>(groups) * m) return;
-    const int g = static_cast<int>(t / m), c = static_cast<int>(t % m);
-    const int r0 = g * span, r1 = min(rows, r0 + span);
-    float lo = __uint_as_float(0x7F800000u), hi = -__uint_as_float(0x7F800000u);
-    for (int r = r0; r < r1; ++r) {
-        if (boxes) {
-            lo = fminf(lo, src[static_cast<size_t>(r) * 2 * m + c]);
-            hi = fmaxf(hi, src[static_cast<size_t>(r) * 2 * m + m + c]);
-        } else {
-            const float v = src[static_cast<size_t>(r) * m + c];
-            lo = fminf(lo, v);
-            hi = fmaxf(hi, v);
+    __shared__ float s_lo[SB_TILES][M], s_hi[SB_TILES][M];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = blockIdx.x * SB_TILES + wave;   // tile
+    const int p = t * TILE + lane;
+    const float inf = __uint_as_float(0x7F800000u);
+    float lo[M], hi[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+        lo[c] = inf;
+        hi[c] = -inf;
+    }
+    if (p < n) {
+        const float* x = X + static_cast<size_t>(perm[p]) * M;
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            const float v = x[c];
+            Xs[static_cast<size_t>(p) * M + c] = v;
+            lo[c] = fminf(lo[c], v);
+            hi[c] = fmaxf(hi[c], v);
         }
     }
-    out[static_cast<size_t>(g) * 2 * m + c] = lo;
-    out[static_cast<size_t>(g) * 2 * m + m + c] = hi;
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            lo[c] = fminf(lo[c], shfl_xor_f32(lo[c], o));
+            hi[c] = fmaxf(hi[c], shfl_xor_f32(hi[c], o));
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            s_lo[wave][c] = lo[c];
+            s_hi[wave][c] = hi[c];
+            if (t * TILE < n) {
+                tbox[static_cast<size_t>(t) * 2 * M + c] = lo[c];
+                tbox[static_cast<size_t>(t) * 2 * M + M + c] = hi[c];
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < M) {
+        const int c = threadIdx.x;
+        float l = inf, h = -inf;
+#pragma unroll
+        for (int u = 0; u < SB_TILES; ++u) {   // tiles past the end hold empty boxes
+            l = fminf(l, s_lo[u][c]);
+            h = fmaxf(h, s_hi[u][c]);
+        }
+        sbox[static_cast<size_t>(blockIdx.x) * 2 * M + c] = l;
+        sbox[static_cast<size_t>(blockIdx.x) * 2 * M + M + c] = h;
+    }
 }
 
 // -------------------------------------------------------------------- refine
@@ -1401,7 +1468,19 @@ hipError_t launch_spatial_codes(const float* X, int n, int m, float* bbox_part, 
     const int bits = spatial_code_bits(n, m);
     const int nb = spatial_bbox_blocks(n);
     const int rpb = (n + nb - 1) / nb;
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(256), 0, st, X, n, m, rpb, bbox_part);
+    auto boxes = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(BBOX_THREADS), 0, st, X, n, rpb, bbox_part);
+    };
+    switch (m) {
+    case 1: boxes(k_bbox_partial<1>); break;
+    case 2: boxes(k_bbox_partial<2>); break;
+    case 3: boxes(k_bbox_partial<3>); break;
+    case 4: boxes(k_bbox_partial<4>); break;
+    case 5: boxes(k_bbox_partial<5>); break;
+    case 6: boxes(k_bbox_partial<6>); break;
+    case 7: boxes(k_bbox_partial<7>); break;
+    default: boxes(k_bbox_partial<8>); break;
+    }
     hipLaunchKernelGGL(k_morton, dim3((n + 255) / 256), dim3(256), 0, st, X, n, m, bits, bbox_part, nb, code, vals);
     return hipGetLastError();
 }
@@ -1409,12 +1488,22 @@ hipError_t launch_spatial_codes(const float* X, int n, int m, float* bbox_part, 
 hipError_t launch_spatial_layout(const float* X, int n, int m, const int32_t* perm, float* Xs, float* tbox,
                                  float* sbox, hipStream_t st)
 {
-    gather_rows(X, n, m, perm, Xs, st);
-    const int nt = spatial_tiles(n), ns = spatial_superblocks(n);
-    hipLaunchKernelGGL(k_group_boxes, dim3((nt * m + 255) / 256), dim3(256), 0, st, Xs, n, m, TILE, nt, 0, tbox);
-    hipLaunchKernelGGL(k_group_boxes, dim3((ns * m + 255) / 256), dim3(256), 0, st, tbox, nt, m, SB_TILES, ns, 1,
-                       sbox);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(spatial_superblocks(n)), dim3(LAYOUT_THREADS), 0, st, X, n, perm, Xs, tbox,
+                           sbox);
+        return hipGetLastError();
+    };
+    switch (m) {
+    case 1: return go(k_spatial_layout<1>);
+    case 2: return go(k_spatial_layout<2>);
+    case 3: return go(k_spatial_layout<3>);
+    case 4: return go(k_spatial_layout<4>);
+    case 5: return go(k_spatial_layout<5>);
+    case 6: return go(k_spatial_layout<6>);
+    case 7: return go(k_spatial_layout<7>);
+    case 8: return go(k_spatial_layout<8>);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int M, int R>

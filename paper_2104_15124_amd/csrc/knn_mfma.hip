@@ -371,9 +371,9 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
     // query ids of this wavefront (-1: none) and the candidate tile range
     int q0 = 0, tbeg = 0, tend = 0;
     if constexpr (LEARNED) {
-        const int w = blockIdx.x;
-        if (w >= *ba.n_work) return;   // whole workgroup
-        const int2 wk = ba.work[w];
+        const int nw = *ba.n_work;
+        if (static_cast<int>(blockIdx.x) >= nw) return;   // whole workgroup
+        const int2 wk = ba.work[xcd_index(blockIdx.x, nw)];   // a bucket's items on one XCD
         const int qend = ba.qptr[wk.x + 1];
         q0 = wk.y + wave * NQ;
         tbeg = ba.tptr[wk.x];

@@ -241,13 +241,13 @@ __device__ __forceinline__ uint64_t list_at(const uint64_t (&L)[E], int t)
 // makes the workgroups resident on an XCD at one time neighbours in the order
 // of their work (curve positions, rows grouped by bucket), which read the same
 // candidates through that XCD's L2.
-__device__ __forceinline__ int xcd_block()
+__device__ __forceinline__ int xcd_index(int b, int g)   // b < g
 {
     constexpr int XCDS = 8;
-    const int b = blockIdx.x, g = gridDim.x;
     const int x = b % XCDS, per = g / XCDS, rem = g % XCDS;
     return x * per + min(x, rem) + b / XCDS;
 }
+__device__ __forceinline__ int xcd_block() { return xcd_index(blockIdx.x, gridDim.x); }
 
 // Candidate pairs scored, counted over PAIR_SLOTS counters a cache line apart: a
 // single counter takes one wavefront's addition every 12 ns or so, which alone
