@@ -8,8 +8,8 @@
 //
 // Pipeline of kvb_knn for one row i:
 //   select   stream all n candidates through a distance test and keep the
-//            k' = k + margin smallest (distance, index) keys in a register
-//            list (one wavefront owns R rows; lanes hold candidates);
+//            k' = k + margin smallest (distance, index) keys (one wavefront
+//            owns R rows; lanes hold candidates);
 //   refine   recompute the k' candidates' squared distances in float64
 //            (rounded to float32), drop i itself, sort, decide membership at the
 //            k-th neighbour in float64, and check a certificate that no

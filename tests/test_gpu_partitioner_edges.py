@@ -65,3 +65,23 @@ def test_backward_exact_at_tile_edges(gpu_lib, B, m, h1, h2, nb):
     want_loss = (Z[:, hot] - Z[np.arange(B)[:, None], lab].mean(1)).mean()
     assert loss == np.float32(want_loss)
     ctx.close()
+
+
+@pytest.mark.parametrize("nb,P", [(32, 1), (32, 32), (96, 5), (992, 8), (1024, 4), (1024, 9), (1056, 4)])
+def test_routes_follow_the_logits(gpu_lib, nb, P):
+    # small integer logits: ties by the dozen in every row, to the smaller bucket
+    kvb, B, m = gpu_lib, 67, 8
+    rng = np.random.default_rng(nb + P)
+    X = torch.from_numpy(rng.integers(-1, 2, (B, m)).astype(np.float32)).cuda()
+    params = [sparse(rng, 32, m, 3), rng.integers(0, 2, 32) * 1.0, sparse(rng, 32, 32, 2), rng.integers(0, 2, 32) * 1.0,
+              sparse(rng, nb, 32, 2), np.zeros(nb)]
+    ctx = kvb.Context()
+    kvb.part_init(m, 32, 32, nb, P, ctx=ctx)
+    kvb.part_set_params(torch.from_numpy(learned.flatten(params).astype(np.float32)).cuda(), ctx=ctx)
+    home, probe = kvb.part_route(X, P, ctx=ctx)
+    pad = torch.cat([X, X[:(-B) % 32]])
+    Z = kvb.mlp_forward(pad, nb, ctx=ctx).cpu().numpy()[:B]
+    want = np.argsort(-Z, axis=1, kind="stable")[:, :P]
+    np.testing.assert_array_equal(probe.cpu().numpy(), want)
+    np.testing.assert_array_equal(home.cpu().numpy(), want[:, 0])
+    ctx.close()
