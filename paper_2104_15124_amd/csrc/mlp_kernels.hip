@@ -8,6 +8,8 @@
 // multiple of 16 (the caller pads).
 #include <algorithm>
 
+#include <type_traits>
+
 #include "kvb_device.h"
 #include "kvb_kernels.h"
 
@@ -91,6 +93,59 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmJob g)
     for (int q = 0; q < 4; ++q) {
         float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
         gemm_store4(g, m0 + 8 * q + 4 * half, col, bcol, v);
+    }
+}
+
+// Two by two output tiles per wavefront, each sum in the order of k_gemm_nt: half
+// the operand loads per product (the large forward products are bound by them).
+// 32768 rows of 128-256-256-1024: 180 to 115 us in three launches.
+__global__ __launch_bounds__(256) void k_gemm_nt_wide(GemmJob g)
+{
+    constexpr int U = 4;   // k-steps loaded together
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int tiles_n = g.N / 64;
+    const int tile = blockIdx.x * 4 + wave;
+    if (tile >= (g.M / 64) * tiles_n) return;
+    const int m0 = (tile / tiles_n) * 64, n0 = (tile % tiles_n) * 64;
+    const int half = lane >> 5;
+    const uint16_t* ap = g.A + static_cast<size_t>(m0 + (lane & 31)) * g.lda + half * 8;
+    const uint16_t* bp = g.B + static_cast<size_t>(n0 + (lane & 31)) * g.ldb + half * 8;
+    const size_t a32 = static_cast<size_t>(32) * g.lda, b32 = static_cast<size_t>(32) * g.ldb;
+    f32x16 acc[2][2] = {};
+    auto steps = [&](auto count, int s) {
+        constexpr int N = decltype(count)::value;
+        bf16x8 a[N][2], b[N][2];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                a[u][h] = *reinterpret_cast<const bf16x8*>(ap + h * a32 + (s + u) * 16);
+                b[u][h] = *reinterpret_cast<const bf16x8*>(bp + h * b32 + (s + u) * 16);
+            }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int w = 0; w < 2; ++w)
+                    acc[h][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u][h], b[u][w], acc[h][w], 0, 0, 0);
+    };
+    const int ks = g.K / 16;
+    int s = 0;
+    for (; s + U <= ks; s += U) steps(std::integral_constant<int, U>{}, s);
+    for (; s < ks; ++s) steps(std::integral_constant<int, 1>{}, s);
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const int col = n0 + 32 * w + (lane & 31);
+        const float bcol = g.bias ? g.bias[col] : 0.f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4] = {acc[h][w][4 * q], acc[h][w][4 * q + 1], acc[h][w][4 * q + 2], acc[h][w][4 * q + 3]};
+                gemm_store4(g, m0 + 32 * h + 8 * q + 4 * half, col, bcol, v);
+            }
     }
 }
 
@@ -429,10 +484,18 @@ __global__ __launch_bounds__(256) void k_fill_normal(float* __restrict__ p, int6
 static bool gemm_ok(const GemmJob& g) { return g.M % 32 == 0 && g.N % 32 == 0 && g.K % 16 == 0; }
 static int gemm_tiles(const GemmJob& g) { return (g.M / 32) * (g.N / 32); }
 
+constexpr int GEMM_WIDE_MIN = 2048;
 hipError_t launch_gemm_nt(const GemmJob& g, hipStream_t st)
 {
     if (!gemm_ok(g)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gemm_nt, dim3((gemm_tiles(g) + 3) / 4), dim3(256), 0, st, g);
+    // two by two tiles each where that still leaves two wavefronts per SIMD (as
+    // the products of 32768 routed rows do, 38 against 60 us; a training batch's
+    // 32 to 256 tiles are one wavefront each, or k_gemm_nt_split)
+    const int wide = g.M % 64 == 0 && g.N % 64 == 0 ? gemm_tiles(g) / 4 : 0;
+    if (wide >= GEMM_WIDE_MIN)
+        hipLaunchKernelGGL(k_gemm_nt_wide, dim3((wide + 3) / 4), dim3(256), 0, st, g);
+    else
+        hipLaunchKernelGGL(k_gemm_nt, dim3((gemm_tiles(g) + 3) / 4), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 

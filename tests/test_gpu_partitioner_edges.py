@@ -85,3 +85,22 @@ def test_routes_follow_the_logits(gpu_lib, nb, P):
     np.testing.assert_array_equal(probe.cpu().numpy(), want)
     np.testing.assert_array_equal(home.cpu().numpy(), want[:, 0])
     ctx.close()
+
+
+@pytest.mark.parametrize("B,h1,h2,nb", [(32768, 64, 256, 1024), (16960, 256, 96, 512), (8192, 1024, 64, 1024)])
+def test_large_forward_exact(gpu_lib, B, h1, h2, nb):
+    # small integers: every product and sum is exact in BF16 and float32
+    kvb, m = gpu_lib, 17
+    rng = np.random.default_rng(nb)
+    X = rng.integers(-1, 2, (B, m)).astype(np.float32)
+    W1, W2, W3 = (sparse(rng, r, c, 3).astype(np.float32) for r, c in ((h1, m), (h2, h1), (nb, h2)))
+    b = [rng.integers(0, 2, r).astype(np.float32) for r in (h1, h2, nb)]
+    H = np.maximum(X @ W1.T + b[0], 0)
+    H = np.maximum(H @ W2.T + b[1], 0)
+    want = H @ W3.T + b[2]
+    ctx = kvb.Context()
+    kvb.part_init(m, h1, h2, nb, 2, ctx=ctx)
+    flat = learned.flatten([W1, b[0], W2, b[1], W3, b[2]]).astype(np.float32)
+    kvb.part_set_params(torch.from_numpy(flat).cuda(), ctx=ctx)
+    np.testing.assert_array_equal(kvb.mlp_forward(torch.from_numpy(X).cuda(), nb, ctx=ctx).cpu().numpy(), want)
+    ctx.close()
