@@ -1019,10 +1019,12 @@ __global__ __launch_bounds__(256) void k_refine(const float* __restrict__ X, int
         if (nkept == kk) bound = kept_max * (1.f + dl) * (1.f + 1e-6f);
         if (slast) {
             // certificate: every candidate the select step dropped has a true
-            // squared distance >= slast * lb_scale; it must exceed the largest kept
+            // squared distance >= slast * lb_scale; it must exceed the largest
+            // kept. A list of fewer than k - 1 others leaves the row unfinished
+            // whatever its bound.
             const float lb = slast[r] * lb_scale;
             const float ub = kept_max * (1.f + dl) * (1.f + 1e-6f);
-            certified = lb > ub;
+            certified = nkept == kk && lb > ub;
         } else {
             // no bound on the dropped candidates (learned routing): the row is
             // only completed by the exact scan when too few candidates were found

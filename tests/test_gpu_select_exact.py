@@ -1,0 +1,46 @@
+"""Exactness of the curve-ordered selection where its scores are coarse (run on
+an MI355X): BF16 scores of one term per coordinate order close candidates
+wrongly, so a row's list may lack true neighbours, and only the certificate and
+the exact fallback make the row right.
+
+The samples are tight clusters in a 4-dimensional subspace: inside a cluster
+the scores' error exceeds the distances. The float64 oracle is the reference.
+"""
+import numpy as np
+import pytest
+import torch
+
+from parity import say
+
+pytestmark = pytest.mark.gpu
+
+
+def clusters(n, m, radius, seed):
+    rng = np.random.default_rng(seed)
+    V, _ = np.linalg.qr(rng.standard_normal((m, 4)))
+    centres = 2 * rng.standard_normal((5, 4))
+    return ((centres[rng.integers(5, size=n)] + radius * rng.standard_normal((n, 4))) @ V.T).astype(np.float32)
+
+
+def search(kvb, X, k, margin, split):
+    """kvb_knn into arrays of -1 / NaN, so that an entry left out is seen."""
+    n, m = X.shape
+    ctx = kvb.Context()
+    ctx.set_option(kvb.OPT_BF16_SPLIT, split)
+    Xd = torch.from_numpy(X).cuda()
+    idx = torch.full((n, k), -1, dtype=torch.int32, device="cuda")
+    d2 = torch.full((n, k), float("nan"), device="cuda")
+    ctx.check(ctx.lib.kvb_knn(ctx.h, kvb._ptr(Xd), n, m, k, kvb.KNN_BF16, margin, kvb._ptr(idx), kvb._ptr(d2), None))
+    fallback = kvb.knn_fallback_rows(ctx)
+    ctx.close()
+    say(f"[select-exact] n={n} m={m} k={k} margin={margin} split={split}: fallback rows {fallback}")
+    return idx.cpu().numpy(), d2.cpu().numpy()
+
+
+@pytest.mark.parametrize("m", [96, 128])
+def test_rows_are_complete(gpu_lib, m):
+    """Without a margin a list short of its keys may be short of the row's k - 1
+    neighbours: such a row goes to the exact fallback, with every entry written."""
+    gi, gd = search(gpu_lib, clusters(12000, m, 0.02, m), 64, 0, 1)
+    assert (gi >= 0).all() and not np.isnan(gd).any()
+    assert (np.diff(np.sort(gi, axis=1), axis=1) > 0).all()
