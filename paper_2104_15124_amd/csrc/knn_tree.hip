@@ -46,9 +46,14 @@
 // (1 KB per K-step) and take the full product.
 //
 // A tile is skipped only when a rigorous bound on its distances exceeds the
-// thresholds at that time, which bound the final ones; the certificate
-// epilogue (derivation in knn_mfma.hip) therefore holds: every candidate
-// missing from a list has a score at or above the list's last.
+// thresholds at that time, which bound the final ones. A threshold counts
+// computed scores, a bound speaks of true distances: a counted candidate may lie
+// beyond the distance of its threshold by the score's error E_q, so pass 2 tests the
+// noted tiles against the threshold and E_q. Should a list end short of kp keys
+// all the same (a tile that is walked again is tested without E_q), its last score is
+// no bound; its threshold is one: every candidate missing from a list has a
+// score above the threshold or a true distance beyond it, and the certificate
+// (derivation in knn_mfma.hip) takes the smaller of the two.
 #include <type_traits>
 
 #include "knn_mfma_common.h"
@@ -402,21 +407,33 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
 
     // the distance threshold of a score threshold (rounded up)
     auto dist_threshold = [](float score, float yq) { return fmaxf(score + yq, 0.f) * (1.f + 4.8e-7f); };
-    // distance thresholds and, LONG, projected thresholds from W.tau; returns
+    // lane q < 32: bound on the error of query q's scores (the certificate's E_i)
+    auto score_error = [&](int q) {
+        const double Rd = static_cast<double>(R);
+        const double yi2 = static_cast<double>(W.yq[q]), yi = sqrt(yi2);
+        return em.gamma * (Rd + 1.05 * yi) * (Rd + 1.05 * yi) + em.norm * Rd * Rd + em.cross * yi * Rd + 1e-30;
+    };
+    // distance thresholds and, LONG, projected thresholds from W.tau (`counted`:
+    // those of every candidate whose computed score is at or below it); returns
     // the wavefront's largest distance threshold (read from one lane, so that
     // the compiler sees a wave-uniform value and keeps the branches on it,
     // and the state they update, scalar).
     // |x_i - x_j|^2 <= thr implies |z_i - z_j| <= (sqrt(thr) + yerr) / pscale + zslack
     // (see BoxBound), hence s' <= that^2 - |z_i|^2 + E_i.
-    auto publish = [&]() {
+    auto publish = [&](bool counted) {
         wave_lds_sync();
         float t = -TINF;
         if (lane < TNQ) {
             t = lane < nq_valid ? dist_threshold(W.tau[lane], W.yq[lane]) : -TINF;
-            const float b = (sqrtf(fmaxf(t, 0.f)) * (1.f + 1e-6f) + bb.yerr) / bb.pscale + zslack;
-            const float g2 = b * b * (1.f + 4e-6f);
-            W.gt[lane] = lane < nq_valid ? g2 : -TINF;
-            if constexpr (LONG) W.zt[lane] = lane < nq_valid ? g2 + zconst : -TINF;
+            auto projected = [&](float d2) {
+                const float b = (sqrtf(fmaxf(d2, 0.f)) * (1.f + 1e-6f) + bb.yerr) / bb.pscale + zslack;
+                return b * b * (1.f + 4e-6f);
+            };
+            W.gt[lane] = lane < nq_valid ? projected(t) : -TINF;
+            if constexpr (LONG) {
+                const float tz = counted ? t + static_cast<float>(score_error(lane) * (1.0 + 1e-6)) : t;
+                W.zt[lane] = lane < nq_valid ? projected(tz) + zconst : -TINF;
+            }
         }
         wave_lds_sync();
         pt.gt = W.gt[l31];
@@ -548,7 +565,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
                 W.tau[acc_row(r + 1, half)] = t1n;
             }
         }
-        return publish();
+        return publish(false);
     };
     unsigned long long pairs = 0;
     int nrec = 0;       // tiles noted (the count goes on beyond TREC)
@@ -729,6 +746,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     int at[16];   // the next free key of this half's queries' lists (from lists_q0)
 #pragma unroll
     for (int r = 0; r < 16; ++r) at[r] = acc_row(r, half) * CAP;
+    if constexpr (LONG) publish(true);
     const bool rewalk = nrec > TREC;   // the notes overflowed: the fill tiles, then the tree again
     if (rewalk) walk_start();
     int ri = 0;
@@ -821,9 +839,9 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
             bitonic_sort<E>(L);
 #pragma unroll
             for (int s = 0; s < E; ++s) lists_q0[static_cast<size_t>(q) * CAP + s * WAVE + lane] = L[s];
-            // the list's kp-th score, for the certificate below
+            // the list's kp-th score (+inf where it is short), for the certificate below
             const float sl = key_dist(list_at<E>(L, kp - 1));
-            if (lane == 0) W.tau[q] = sl;
+            if (lane == 0) W.tau[q] = fminf(sl, W.tau[q]);
         }
         wave_lds_sync();
     }
@@ -831,15 +849,11 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
 
     // certificate lower bound for the candidates left out of each list
     if (lane < nq_valid) {
-        const double Rd = static_cast<double>(R);
         const int qg = q0 + lane;
-        const float sl = W.tau[lane];
-        const double yi2 = static_cast<double>(ynorm2[qg]);
-        const double yi = sqrt(yi2);
-        const double Ei = em.gamma * (Rd + 1.05 * yi) * (Rd + 1.05 * yi) + em.norm * Rd * Rd + em.cross * yi * Rd + 1e-30;
-        const double t = static_cast<double>(sl) + yi2 - Ei;
+        const double yi2 = static_cast<double>(W.yq[lane]);
+        const double t = static_cast<double>(W.tau[lane]) + yi2 - score_error(lane);
         double B = t > 0.0 ? sqrt(t) : 0.0;
-        B -= em.center * (yi + Rd);
+        B -= em.center * (sqrt(yi2) + static_cast<double>(R));
         B = B > 0.0 ? B : 0.0;
         lb_out[qg] = static_cast<float>(B * B * (1.0 - 1.0 / 1048576.0));
     }

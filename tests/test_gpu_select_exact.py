@@ -10,7 +10,8 @@ import numpy as np
 import pytest
 import torch
 
-from parity import say
+import workloads
+from parity import check_knn_rows, knn_reference, say
 
 pytestmark = pytest.mark.gpu
 
@@ -22,7 +23,7 @@ def clusters(n, m, radius, seed):
     return ((centres[rng.integers(5, size=n)] + radius * rng.standard_normal((n, 4))) @ V.T).astype(np.float32)
 
 
-def search(kvb, X, k, margin, split):
+def search(kvb, X, k, margin, split, mode="bf16"):
     """kvb_knn into arrays of -1 / NaN, so that an entry left out is seen."""
     n, m = X.shape
     ctx = kvb.Context()
@@ -30,10 +31,10 @@ def search(kvb, X, k, margin, split):
     Xd = torch.from_numpy(X).cuda()
     idx = torch.full((n, k), -1, dtype=torch.int32, device="cuda")
     d2 = torch.full((n, k), float("nan"), device="cuda")
-    ctx.check(ctx.lib.kvb_knn(ctx.h, kvb._ptr(Xd), n, m, k, kvb.KNN_BF16, margin, kvb._ptr(idx), kvb._ptr(d2), None))
+    ctx.check(ctx.lib.kvb_knn(ctx.h, kvb._ptr(Xd), n, m, k, kvb.MODES[mode], margin, kvb._ptr(idx), kvb._ptr(d2), None))
     fallback = kvb.knn_fallback_rows(ctx)
     ctx.close()
-    say(f"[select-exact] n={n} m={m} k={k} margin={margin} split={split}: fallback rows {fallback}")
+    say(f"[select-exact] n={n} m={m} k={k} margin={margin} {mode} split={split}: fallback rows {fallback}")
     return idx.cpu().numpy(), d2.cpu().numpy()
 
 
@@ -44,3 +45,28 @@ def test_rows_are_complete(gpu_lib, m):
     gi, gd = search(gpu_lib, clusters(12000, m, 0.02, m), 64, 0, 1)
     assert (gi >= 0).all() and not np.isnan(gd).any()
     assert (np.diff(np.sort(gi, axis=1), axis=1) > 0).all()
+
+
+def check(kvb, X, k, margin, split, mode="bf16", nrows=2000):
+    gi, gd = search(kvb, X, k, margin, split, mode)
+    rows = np.random.default_rng(k).choice(len(X), nrows, replace=False)
+    ri, rd = knn_reference(X, k, rows)
+    check_knn_rows(gi[rows], gd[rows], ri, rd, k, rows)
+
+
+@pytest.mark.parametrize("margin", [0, 8, 32])
+@pytest.mark.parametrize("m", [96, 128])
+def test_coarse_scores(gpu_lib, m, margin):
+    for radius in (0.005, 0.02):
+        check(gpu_lib, clusters(12000, m, radius, m), 64, margin, 1)
+    check(gpu_lib, workloads.gaussian_mixture(16384, seed=m, m=m), 64, margin, 1)
+    check(gpu_lib, workloads.sphere3_lifted(65536, seed=m, m=m), 16, margin, 1, nrows=1000)
+    check(gpu_lib, clusters(12000, 84, 0.02, m), 64, margin, 6)   # 6 m + 3 terms of at most 512
+
+
+@pytest.mark.parametrize("m,mode,split", [(100, "bf16", 1), (64, "bf16", 3), (16, "bf16", 3), (16, "f32", 3),
+                                          (100, "f32", 3)])
+def test_more_tiles_than_notes(gpu_lib, m, mode, split):
+    # no tile of 25000 unstructured samples can be skipped: 782 tiles within reach of every query
+    for margin in (0, 32):
+        check(gpu_lib, workloads.gaussian_iid(25000, m, seed=m), 40, margin, split, mode, nrows=1000)
