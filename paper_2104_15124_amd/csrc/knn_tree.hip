@@ -14,18 +14,27 @@
 // threshold is a value that at least kp of those 32 D scores do not exceed, found
 // by bisection (a lane's count, added over the half's lanes); it is at or
 // above the query's kp-th score, and close to it while no lane holds more than
-// D of the kp nearest (D is two above the mean, or more). The tiles are visited as a walk down the
-// tree: a node's (up to 64) children are bounded at once, one per lane,
-// against the query tile's box, the pending child with the smallest bound is
-// taken first (so the thresholds fall early), and every child is re-tested
-// against the wavefront's largest distance threshold when taken. Tiles in
-// which some score is at or below its query's threshold are noted.
+// D of the kp nearest: D is 5 up to kp = 96, 8 up to 192, 12 beyond (the mean per
+// lane is kp / 32; eight at kp = 256 put 474 candidates below the threshold). The
+// tiles are visited as a walk down the tree: a node's (up to 64) children are bounded
+// at once, one per lane, against the query tile's box, the pending child with the
+// smallest bound is taken first (so the thresholds fall early), and every child is
+// re-tested against the wavefront's largest distance threshold when taken. Tiles
+// in which some score is at or below its query's threshold are noted; pass 1 ends
+// with the walk or when TREC tiles are noted.
 //
-// Pass 2 goes over the noted tiles alone, forms the same scores again and
-// writes those at or below the final threshold straight into the query's list
-// in global scratch: some kp keys per query, each written once. A list that
-// overflows is sorted and merged with the tile's keys (the threshold falls to
-// its kp-th score). At the end each list is sorted once.
+// Pass 2 goes over the noted tiles, forms the same scores again and writes
+// those at or below the threshold straight into the query's list in global
+// scratch: some kp keys per query, each written once. Where the notes were full
+// before the walk was over it then goes on with the walk, each tile scored once, its
+// keys written in the same way (walking the tree again from its root took
+// samples none of whose tiles can be skipped twice the products: Gaussian, n = 100k,
+// m = 16 and 64, 22.0 and 35.6 ms, 15.1 and 21.4 now; 5-manifold, n = 1M, 126 to 98).
+// A list without room for a tile's keys is cut by a lower threshold that at least kp
+// of its keys do not exceed. Lists of kp within 32 of their capacity are sorted instead
+// once full, and take further keys from a buffer in LDS, 32 at a time (k + margin =
+// 256, n = 200k, m = 16: 20.7 to 11.0 ms against a sort per tile; 14.5 by one
+// pass of sorted lists). At the end each list is sorted once.
 //
 // A scan that keeps sorted lists while its thresholds fall appends each query's
 // candidates several times over and merges its list some ten times; those
@@ -50,10 +59,9 @@
 // computed scores, a bound speaks of true distances: a counted candidate may lie
 // beyond the distance of its threshold by the score's error E_q, so pass 2 tests the
 // noted tiles against the threshold and E_q. Should a list end short of kp keys
-// all the same (a tile that is walked again is tested without E_q), its last score is
-// no bound; its threshold is one: every candidate missing from a list has a
-// score above the threshold or a true distance beyond it, and the certificate
-// (derivation in knn_mfma.hip) takes the smaller of the two.
+// all the same, its last score is no bound; its threshold is one: every candidate
+// missing from a list has a score above the threshold or a true distance beyond it,
+// and the certificate (derivation in knn_mfma.hip) takes the smaller of the two.
 #include <type_traits>
 
 #include "knn_mfma_common.h"
@@ -63,7 +71,12 @@ namespace kvb {
 namespace {
 
 constexpr int TNQ = 32;      // queries per wavefront
-constexpr int TREC = 384;    // tiles pass 1 notes; beyond that pass 2 walks the tree again
+constexpr int TREC = 384;    // tiles pass 1 notes
+// Tiles in flight. Short contractions stream the fragments of two tiles ahead
+// of the products (a tile with no hits is too short to cover the next one's
+// loads); long ones the projections of two.
+constexpr int TREE_DEPTH = 3;
+constexpr int TBUF = 32;     // keys buffered per query of a full list
 constexpr float TINF = __builtin_inff();
 
 // the wavefront's LDS state
@@ -78,8 +91,7 @@ struct alignas(16) TreeLds {
     uint64_t mask[TREE_LEVELS];         //       pending children
     int base[TREE_LEVELS];              //       first child
     int lvl;                            //       level of the current pending list
-    uint64_t ovf[2][TNQ];               // keys of a tile that overflow a list, per half
-    uint32_t rec[TREC];                 // the noted tiles
+    uint32_t rec[TREC + TREE_DEPTH];    // the noted tiles, then those in flight when the notes were full
 };
 
 // the tree's shape
@@ -285,6 +297,75 @@ __device__ __noinline__ float overflow_list(uint64_t* __restrict__ dst, int cnt,
     return key_dist(list_at<E>(L, kp - 1));
 }
 
+// A list of cnt keys (unsorted, CAP - 32 < cnt) cut: the keys above tau are dropped,
+// and while more than kp + (CAP - kp) / 4 are left, those above a lower threshold that at
+// least kp do not exceed. Returns the count in the upper half and the threshold's
+// bits; nothing is dropped where equal scores leave no such threshold. Whole wavefront.
+template <int E>
+__device__ __noinline__ uint64_t cut_list(uint64_t* __restrict__ dst, int cnt, int kp, float tau)
+{
+    const int lane = lane_id();
+    const int most = kp + (WAVE * E - kp) / 4;
+    uint64_t v[E];
+    uint32_t d[E];
+    uint32_t first = ~0u;
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+        v[s] = s * WAVE + lane < cnt ? dst[s * WAVE + lane] : ~0ull;
+        d[s] = static_cast<uint32_t>(v[s] >> 32);
+        first = min(first, d[s]);
+    }
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) first = min(first, static_cast<uint32_t>(xor_lane(first, o)));
+    auto count = [&](uint32_t t) {
+        int c = 0;
+#pragma unroll
+        for (int s = 0; s < E; ++s) c += __popcll(__ballot(d[s] <= t));
+        return c;
+    };
+    // as ordered bits; lo: fewer than kp scores do not exceed it; hi: at many do not
+    uint32_t lo = __builtin_amdgcn_readfirstlane(first) - 1u;
+    uint32_t hi = __builtin_amdgcn_readfirstlane(float_order_bits(tau));
+    int at = count(hi);
+    while (at > most && hi - lo > 1u) {
+        // the middle of the values, or of the bits where rounding leaves it at an end
+        const float a = order_bits_float(lo), b = order_bits_float(hi);
+        uint32_t mid = __builtin_amdgcn_readfirstlane(float_order_bits(a + 0.5f * (b - a)));
+        if (!(mid > lo && mid < hi)) mid = lo + (hi - lo) / 2;
+        const int c = count(mid);
+        if (c < kp) {
+            lo = mid;
+        } else {
+            hi = mid;
+            at = c;
+        }
+    }
+    if (at > most) return static_cast<uint64_t>(cnt) << 32 | __float_as_uint(tau);
+    int w = 0;
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+        const uint64_t mask = __ballot(d[s] <= hi);
+        if (d[s] <= hi) dst[w + mbcnt64(mask)] = v[s];
+        w += __popcll(mask);
+    }
+    return static_cast<uint64_t>(w) << 32 | __float_as_uint(order_bits_float(hi));
+}
+
+// A list of cnt keys sorted, the places behind them filled; returns the kp-th
+// score. Whole wavefront.
+template <int E>
+__device__ __noinline__ float sort_list(uint64_t* __restrict__ dst, int cnt, int kp)
+{
+    const int lane = lane_id();
+    uint64_t L[E];
+#pragma unroll
+    for (int s = 0; s < E; ++s) L[s] = s * WAVE + lane < cnt ? dst[s * WAVE + lane] : KEY_INF;
+    bitonic_sort<E>(L);
+#pragma unroll
+    for (int s = 0; s < E; ++s) dst[s * WAVE + lane] = L[s];
+    return key_dist(list_at<E>(L, kp - 1));
+}
+
 // stores of this wavefront complete before its later loads read them
 __device__ __forceinline__ void wave_global_sync()
 {
@@ -295,13 +376,8 @@ __device__ __forceinline__ void wave_global_sync()
 
 }  // namespace
 
-// Tiles in flight. Short contractions stream the fragments of two tiles ahead
-// of the products (a tile with no hits is too short to cover the next one's
-// loads); long ones the projections of two.
-constexpr int TREE_DEPTH = 3;
-
-// K-steps of a long product's batch of loads: all of up to 14 BF16 (32 FP32)
-// fragments, else in equal batches.
+// K-steps of a long product's batch of loads: all of up to 15 BF16 (32 FP32)
+// fragments, else BF16 in halves and FP32 in equal batches of at most 32.
 template <class Tr, int KS>
 constexpr int tree_batch()
 {
@@ -310,7 +386,15 @@ constexpr int tree_batch()
     return sizeof(typename Tr::frag) == 16 && KS >= 16 ? (KS + 1) / 2 : (KS + nb - 1) / nb;
 }
 
-template <class Tr, int KS, bool LONG, int E, int D, int WPE>
+// The lists' room: CAP = 64 E keys. BUF: kp may be within 32 of it, a full list is
+// kept sorted and takes further keys from a buffer; else it is cut.
+template <class Tr, int KS, bool LONG>
+constexpr size_t tree_operand_bytes()
+{
+    return LONG ? static_cast<size_t>(KS) * WAVE * sizeof(typename Tr::frag) : 0;
+}
+
+template <class Tr, int KS, bool LONG, int E, int D, bool BUF, int WPE>
 __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     const typename Tr::elem* __restrict__ Aq, const typename Tr::elem* __restrict__ Bc, int n, int kp,
     const float* __restrict__ ynorm2, const unsigned* __restrict__ rmax_bits, ErrModel em,
@@ -327,6 +411,10 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     __shared__ TreeShape s_shape;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     frag* s_a = reinterpret_cast<frag*>(s_dyn);   // LONG: the query operand, [k-step][lane]
+    // BUF: each query's buffer of TBUF keys and its count (-1: the list is not
+    // sorted yet); else a tile's keys that a list has no room for, per half
+    uint64_t* s_keys = reinterpret_cast<uint64_t*>(s_dyn + tree_operand_bytes<Tr, KS, LONG>());
+    int* s_nbuf = reinterpret_cast<int*>(s_keys + TNQ * TBUF);
 
     const int lane = lane_id();
     const int half = lane >> 5, l31 = lane & 31;
@@ -402,6 +490,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     if (lane < TNQ) {
         W.yq[lane] = lane < nq_valid ? ynorm2[q0 + lane] : 0.f;
         W.tau[lane] = lane < nq_valid ? TINF : -TINF;
+        if constexpr (BUF) s_nbuf[lane] = -1;
     }
     __syncthreads();
 
@@ -568,7 +657,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         return publish(false);
     };
     unsigned long long pairs = 0;
-    int nrec = 0;       // tiles noted (the count goes on beyond TREC)
+    int nrec = 0;       // tiles noted (at most TREC)
     int pend = 0;       // noted since the last refresh
     auto take_scores = [&](const f32x16& acc, int tile) {
         const int cand = tile * 32 + l31;
@@ -588,7 +677,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
             for (int d = D - 1; d > 0; --d) top[r][d] = __builtin_amdgcn_fmed3f(top[r][d - 1], x, top[r][d]);
             top[r][0] = fminf(top[r][0], x);
         }
-        if (nrec < TREC && lane == 0) W.rec[nrec] = static_cast<uint32_t>(tile);
+        if (lane == 0) W.rec[nrec] = static_cast<uint32_t>(tile);
         ++nrec;
         ++pend;
     };
@@ -725,7 +814,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     auto walk_next = [&](float& tb) { return next_tile(wthr, tb); };
     walk_start();
     pipe_start(walk_next);
-    while (tq[0] >= 0) {
+    while (tq[0] >= 0 && nrec < TREC) {
         tq[DEPTH - 1] = tq[DEPTH - 2] >= 0 ? walk_next(tbq[DEPTH - 1]) : -1;
         fetch(DEPTH - 1);
         // the current tile may have fallen out of reach since it was taken
@@ -746,30 +835,46 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     int at[16];   // the next free key of this half's queries' lists (from lists_q0)
 #pragma unroll
     for (int r = 0; r < 16; ++r) at[r] = acc_row(r, half) * CAP;
-    if constexpr (LONG) publish(true);
-    const bool rewalk = nrec > TREC;   // the notes overflowed: the fill tiles, then the tree again
-    if (rewalk) walk_start();
+    // the noted tiles and those in flight when the notes were full, then the rest of the walk
+    const bool more = tq[0] >= 0;
+    int nlist = nrec;
+#pragma unroll
+    for (int d = 0; d + 1 < DEPTH; ++d) {
+        if (tq[d] < 0) continue;
+        if (lane == 0) W.rec[nlist] = static_cast<uint32_t>(tq[d]);
+        ++nlist;
+    }
+    if constexpr (LONG)
+        publish(true);
+    else
+        wave_lds_sync();
     int ri = 0;
-    const int nlist = rewalk ? nfill : nrec;
-    auto noted_next = [&](float& tb) -> int {
+    auto list_next = [&](float& tb) -> int {
         tb = 0.f;
-        if (ri < nlist) return rewalk ? f0 + ri++ : __builtin_amdgcn_readfirstlane(static_cast<int>(W.rec[ri++]));
-        return rewalk ? next_tile(wthr, tb) : -1;
+        if (ri < nlist) return __builtin_amdgcn_readfirstlane(static_cast<int>(W.rec[ri++]));
+        return more ? next_tile(wthr, tb) : -1;
     };
-    pipe_start(noted_next);
-    while (tq[0] >= 0) {
-        tq[DEPTH - 1] = tq[DEPTH - 2] >= 0 ? noted_next(tbq[DEPTH - 1]) : -1;
+    int fell = 0;   // thresholds lowered since they were last published
+    pipe_start(list_next);
+    for (int done = 0; tq[0] >= 0; ++done) {
+        if (done >= nlist && (done == nlist || fell >= 8)) {   // beyond the noted tiles
+            wthr = publish(false);
+            fell = 0;
+        }
+        tq[DEPTH - 1] = tq[DEPTH - 2] >= 0 ? list_next(tbq[DEPTH - 1]) : -1;
         fetch(DEPTH - 1);
-        bool reach = true;
-        if constexpr (LONG) reach = z_reach(zq[0], tq[0]);
+        bool reach = tbq[0] <= wthr;
+        if constexpr (LONG) reach = reach && z_reach(zq[0], tq[0]);
         if (reach) {
             const int cand = tq[0] * 32 + l31;
             const bool valid = cand < n;
+            if (done >= nrec)
+                pairs += static_cast<unsigned long long>(nq_valid) * __popcll(__ballot(valid) & 0xFFFFFFFFull);
             const f32x16 acc = scores(tq[0], bq[0]);
             float tv[16];
             rows16(W.tau, tv);
             const uint32_t below = (1u << l31) - 1u;
-            uint32_t missed = 0;   // rows whose list would overflow: not stored here
+            uint32_t missed = 0;   // rows whose list has no room: not stored here
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const bool in = valid && acc[r] <= tv[r];
@@ -783,36 +888,102 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
                 at[r] = room ? next : at[r];
             }
             if (__ballot(missed != 0)) {
+                wave_lds_sync();
+                wave_global_sync();
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const uint64_t over = __ballot((missed >> r) & 1u);   // by half
-                    if (!over) continue;
-                    const bool in = valid && acc[r] <= tv[r];
-                    const uint64_t mask = __ballot(in);
-                    const uint32_t mh = half ? static_cast<uint32_t>(mask >> 32) : static_cast<uint32_t>(mask);
-                    if (in) W.ovf[half][__popc(mh & below)] = make_key(acc[r], static_cast<uint32_t>(cand));
-                    wave_lds_sync();
-                    wave_global_sync();
+                    const bool over = (missed >> r) & 1u;
+                    const uint64_t om = __ballot(over);   // by half
+                    if (!om) continue;
+                    const int qh = acc_row(r, half);
+                    auto keys_of = [&](float t, uint32_t& mh) {   // this tile's keys of the full lists
+                        const bool in = over && valid && acc[r] <= t;
+                        const uint64_t mask = __ballot(in);
+                        mh = half ? static_cast<uint32_t>(mask >> 32) : static_cast<uint32_t>(mask);
+                        return in;
+                    };
+                    uint32_t mh;
+                    bool in = keys_of(tv[r], mh);
+                    if constexpr (BUF) {
+                        const int b = s_nbuf[qh];
+                        const uint64_t make = __ballot(over && (b < 0 || b + __popc(mh) > TBUF));
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (!((over >> (32 * h)) & 1ull)) continue;
-                        const int q = acc_row(r, h);
-                        const int c = __builtin_amdgcn_readlane(at[r], 32 * h) - q * CAP;
-                        const int add = __popc(static_cast<uint32_t>(mask >> (32 * h)));
-                        const float nt = overflow_list<E>(lists_q0 + static_cast<size_t>(q) * CAP, c, &W.ovf[h][0], add,
-                                                          kp);
-                        if (lane == 0) W.tau[q] = nt;
-                        if (half == h) at[r] = (q + 1) * CAP;
+                        for (int h = 0; h < 2; ++h) {
+                            if (!((make >> (32 * h)) & 1ull)) continue;
+                            const int q = acc_row(r, h);
+                            uint64_t* dst = lists_q0 + static_cast<size_t>(q) * CAP;
+                            const int bq = __builtin_amdgcn_readlane(b, 32 * h);
+                            const float nt =
+                                bq < 0 ? sort_list<E>(dst, __builtin_amdgcn_readlane(at[r], 32 * h) - q * CAP, kp)
+                                       : merge_query_list<E>(dst, s_keys + q * TBUF, bq, kp);
+                            wave_lds_sync();
+                            if (lane == 0) {
+                                W.tau[q] = fminf(W.tau[q], nt);
+                                s_nbuf[q] = 0;
+                            }
+                            if (half == h) at[r] = (q + 1) * CAP;
+                            ++fell;
+                        }
+                        wave_lds_sync();
+                        in = keys_of(W.tau[qh], mh);
+                        const int nb = s_nbuf[qh];
+                        if (in) s_keys[qh * TBUF + nb + __popc(mh & below)] = make_key(acc[r], static_cast<uint32_t>(cand));
+                        wave_lds_sync();
+                        if (over && l31 == 0) s_nbuf[qh] = nb + __popc(mh);
+                        wave_lds_sync();
+                    } else {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (!((om >> (32 * h)) & 1ull)) continue;
+                            const int q = acc_row(r, h);
+                            const uint64_t cut = cut_list<E>(lists_q0 + static_cast<size_t>(q) * CAP,
+                                                             __builtin_amdgcn_readlane(at[r], 32 * h) - q * CAP, kp,
+                                                             W.tau[q]);
+                            if (lane == 0) W.tau[q] = __uint_as_float(static_cast<uint32_t>(cut));
+                            if (half == h) at[r] = q * CAP + static_cast<int>(cut >> 32);
+                            ++fell;
+                        }
+                        wave_lds_sync();
+                        in = keys_of(W.tau[qh], mh);
+                        const int next = at[r] + __popc(mh), slot = at[r] + __popc(mh & below);
+                        const bool room = next <= (qh + 1) * CAP;
+                        if (in && room) lists_q0[slot] = make_key(acc[r], static_cast<uint32_t>(cand));
+                        const uint64_t full = __ballot(over && !room);
+                        if (over && room) at[r] = next;
+                        if (full) {   // equal scores fill the list
+                            if (in) s_keys[half * TNQ + __popc(mh & below)] = make_key(acc[r], static_cast<uint32_t>(cand));
+                            wave_lds_sync();
+                            wave_global_sync();
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                if (!((full >> (32 * h)) & 1ull)) continue;
+                                const int q = acc_row(r, h);
+                                const int c = __builtin_amdgcn_readlane(at[r], 32 * h) - q * CAP;
+                                const int add = __popc(__builtin_amdgcn_readlane(mh, 32 * h));
+                                const float nt = overflow_list<E>(lists_q0 + static_cast<size_t>(q) * CAP, c,
+                                                                  s_keys + h * TNQ, add, kp);
+                                if (lane == 0) W.tau[q] = fminf(W.tau[q], nt);
+                                if (half == h) at[r] = (q + 1) * CAP;
+                            }
+                            wave_lds_sync();
+                        }
                     }
-                    wave_lds_sync();
-                    wave_global_sync();
                 }
+                wave_global_sync();
             }
         }
         shift();
     }
     // the lists' stores complete before other lanes read them
+    wave_lds_sync();
     wave_global_sync();
+    if constexpr (BUF) {
+        for (int q = 0; q < nq_valid; ++q) {
+            const int b = __builtin_amdgcn_readfirstlane(s_nbuf[q]);
+            if (b > 0) merge_query_list<E>(lists_q0 + static_cast<size_t>(q) * CAP, s_keys + q * TBUF, b, kp);
+        }
+        wave_global_sync();
+    }
     // each list sorted in place, the next one's loads in flight meanwhile;
     // query q's count moved to lane q
     int cnt_lane = 0;
@@ -870,22 +1041,25 @@ static hipError_t launch_tree(const void* Aq, const void* Bc, int n, int kp, con
     const int ntiles = (n + 31) / 32;
     if (crv.layout.cnt[0] != ntiles) return hipErrorInvalidValue;
     const dim3 grid(ntiles), block(WAVE);
-    const size_t dyn = LONG ? static_cast<size_t>(KS) * WAVE * sizeof(typename Tr::frag) : 0;
     const elem* A = static_cast<const elem*>(Aq);
     const elem* B = static_cast<const elem*>(Bc);
     // scores kept per lane and query: the mean share of the kp nearest is kp /
     // 32. Two wavefronts per SIMD, or one where the kept scores, or the query
     // operand in LDS, leave no room for two (then the products' loads run ahead).
     constexpr int W5 = LONG && KS * sizeof(typename Tr::frag) > 13 * 16 ? 1 : 2, W8 = LONG ? 1 : 2;
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel, bool buf) {
+        const size_t keys = buf ? TNQ * TBUF * sizeof(uint64_t) + TNQ * sizeof(int) : 2 * TNQ * sizeof(uint64_t);
+        const size_t dyn = tree_operand_bytes<Tr, KS, LONG>() + keys;
         hipLaunchKernelGGL(kernel, grid, block, dyn, st, A, B, n, kp, ynorm2, rmax, em, lists, lb, crv, pairs);
     };
     if (kp <= 96)
-        go(k_select_tree<Tr, KS, LONG, 2, 5, W5>);
+        go(k_select_tree<Tr, KS, LONG, 2, 5, false, W5>, false);
     else if (cap == 128)
-        go(k_select_tree<Tr, KS, LONG, 2, 8, W8>);
+        go(k_select_tree<Tr, KS, LONG, 2, 8, true, W8>, true);
+    else if (kp <= 192)
+        go(k_select_tree<Tr, KS, LONG, 4, 8, false, W8>, false);
     else
-        go(k_select_tree<Tr, KS, LONG, 4, 8, W8>);
+        go(k_select_tree<Tr, KS, LONG, 4, 12, true, 1>, true);
     return hipGetLastError();
 }
 

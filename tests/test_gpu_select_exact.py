@@ -47,7 +47,7 @@ def test_rows_are_complete(gpu_lib, m):
     assert (np.diff(np.sort(gi, axis=1), axis=1) > 0).all()
 
 
-def check(kvb, X, k, margin, split, mode="bf16", nrows=2000):
+def check(kvb, X, k, margin, split, mode="bf16", nrows=600):
     gi, gd = search(kvb, X, k, margin, split, mode)
     rows = np.random.default_rng(k).choice(len(X), nrows, replace=False)
     ri, rd = knn_reference(X, k, rows)
@@ -60,13 +60,30 @@ def test_coarse_scores(gpu_lib, m, margin):
     for radius in (0.005, 0.02):
         check(gpu_lib, clusters(12000, m, radius, m), 64, margin, 1)
     check(gpu_lib, workloads.gaussian_mixture(16384, seed=m, m=m), 64, margin, 1)
-    check(gpu_lib, workloads.sphere3_lifted(65536, seed=m, m=m), 16, margin, 1, nrows=1000)
+    check(gpu_lib, workloads.sphere3_lifted(65536, seed=m, m=m), 16, margin, 1, nrows=300)
     check(gpu_lib, clusters(12000, 84, 0.02, m), 64, margin, 6)   # 6 m + 3 terms of at most 512
 
 
-@pytest.mark.parametrize("m,mode,split", [(100, "bf16", 1), (64, "bf16", 3), (16, "bf16", 3), (16, "f32", 3),
-                                          (100, "f32", 3)])
+# k and margin on every kind of list: cut at 128 keys, sorted at 128, cut at 256, sorted at 256
+LISTS = [(40, 0), (64, 32), (65, 32), (128, 0), (97, 32), (160, 32), (161, 32), (224, 32)]
+
+
+@pytest.mark.parametrize("m,mode,split", [(16, "f32", 3), (16, "bf16", 3), (64, "bf16", 3), (100, "f32", 3)])
 def test_more_tiles_than_notes(gpu_lib, m, mode, split):
     # no tile of 25000 unstructured samples can be skipped: 782 tiles within reach of every query
+    X = workloads.gaussian_iid(25000, m, seed=m)
+    for k, margin in LISTS:
+        check(gpu_lib, X, k, margin, split, mode, nrows=500)
+
+
+def test_more_tiles_than_notes_coarse(gpu_lib):
     for margin in (0, 32):
-        check(gpu_lib, workloads.gaussian_iid(25000, m, seed=m), 40, margin, split, mode, nrows=1000)
+        check(gpu_lib, workloads.gaussian_iid(25000, 100, seed=3), 40, margin, 1, nrows=500)
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16"])
+@pytest.mark.parametrize("k,margin", [(40, 0), (64, 32), (96, 32), (128, 32), (224, 32)])
+def test_more_tiles_than_notes_equal_scores(gpu_lib, k, margin, mode):
+    # corners of a 12-cube, six or so samples at each: 70 at distance 1, 400 at sqrt 2
+    X = np.random.default_rng(k).integers(0, 2, (25000, 12)).astype(np.float32)
+    check(gpu_lib, X, k, margin, 3, mode, nrows=500)
