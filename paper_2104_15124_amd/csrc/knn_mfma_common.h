@@ -1,5 +1,5 @@
 // Pieces shared by the matrix-core selection kernels (knn_mfma.hip: the
-// all-tiles and learned-bucket scans; knn_tree.hip: the curve-ordered walk
+// all-tiles and learned-bucket scans; knn_tree.h: the curve-ordered walk
 // of the tile-box tree): MFMA operand traits, the accumulator layout, the
 // per-query list merge and sort in global scratch, the projected-box distance
 // bound and the XCD-aware workgroup order.

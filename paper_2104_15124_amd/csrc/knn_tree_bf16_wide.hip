@@ -1,0 +1,18 @@
+// The curve-ordered select of BF16 operands beyond 10 K-steps.
+#include "knn_tree.h"
+
+namespace kvb {
+
+hipError_t tree_bf16_wide(int ks, const TreeCall& c)
+{
+    switch (ks) {
+    case 13: return launch_tree<TraitsBF16, 13, true>(c);
+    case 16: return launch_tree<TraitsBF16, 16, true>(c);
+    case 20: return launch_tree<TraitsBF16, 20, true>(c);
+    case 25: return launch_tree<TraitsBF16, 25, true>(c);
+    case 32: return launch_tree<TraitsBF16, 32, true>(c);
+    default: return hipErrorNotSupported;
+    }
+}
+
+}  // namespace kvb

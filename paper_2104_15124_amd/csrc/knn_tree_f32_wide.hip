@@ -1,0 +1,17 @@
+// The curve-ordered select of FP32 operands beyond 32 K-steps.
+#include "knn_tree.h"
+
+namespace kvb {
+
+hipError_t tree_f32_wide(int ks, const TreeCall& c)
+{
+    switch (ks) {
+    case 48: return launch_tree<TraitsF32, 48, true>(c);
+    case 64: return launch_tree<TraitsF32, 64, true>(c);
+    case 96: return launch_tree<TraitsF32, 96, true>(c);
+    case 128: return launch_tree<TraitsF32, 128, true>(c);
+    default: return hipErrorNotSupported;
+    }
+}
+
+}  // namespace kvb

@@ -135,7 +135,7 @@ hipError_t launch_curve_order(const float* X, int n, int m, const double* mu, co
                               uint32_t* code, uint32_t* scode, int32_t* vals, int32_t* perm, void* sort_tmp,
                               size_t sort_bytes, int32_t* pos, int32_t* cid, float* zs, float* tbox, float* tree,
                               bool median_splits, hipStream_t st);
-// curve-ordered exact selection over the box tree (knn_tree.hip); lists [n, cap], lb [n] by curve position.
+// curve-ordered exact selection over the box tree (knn_tree.h); lists [n, cap], lb [n] by curve position.
 hipError_t launch_select_tree(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
                               const CurveArgs& crv, unsigned long long* pairs, hipStream_t st);

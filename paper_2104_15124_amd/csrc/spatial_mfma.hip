@@ -11,7 +11,7 @@
 //   |y_i - y_j|^2 >= |z_i - z_j|^2 >= (gap between the boxes of their z)^2,
 // a candidate tile whose box lies farther from a query block's box than all
 // of the block's current thresholds holds no neighbour of any of its queries
-// and is skipped (selection kernel, knn_tree.hip). The bound is made rigorous
+// and is skipped (selection kernel, knn_tree.h). The bound is made rigorous
 // for the rounding of P, of z and of the box gaps by the margins set there.
 #include <rocprim/device/device_radix_sort.hpp>
 
