@@ -28,8 +28,9 @@ static void fixed_buffers(kvb_ctx ctx, Carve& dev, Carve& host)
 {
     ctx->tune_dev = dev.take<kvb::TuneResult>(1);
     ctx->build_dev = dev.take<BuildDev>(1);
-    ctx->pairs_dev = dev.take<unsigned long long>(PAIR_WORDS + 1);
+    ctx->pairs_dev = dev.take<unsigned long long>(PAIR_WORDS + 2);
     ctx->fb_count_dev = reinterpret_cast<int*>(ctx->pairs_dev + PAIR_WORDS);
+    ctx->wide_count_dev = ctx->fb_count_dev + 1;
     ctx->tune_host = host.take<kvb::TuneResult>(1);
     ctx->build_host = host.take<BuildDev>(1);
     ctx->fb_count_host = host.take<int>(1);
@@ -310,6 +311,8 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                 crv.tree = tree;
                 crv.layout = tl;
                 crv.pscale = P + size_t(m) * kvb::PR_DIMS;
+                crv.wide_count = ctx->wide_count_dev;
+                crv.wide = vals;   // free once the order is made
                 // a float32 dot product of m terms errs by at most m u |y| |p| (|p| <= 1 + m u)
                 crv.zcoef = static_cast<float>((m + 2) * u * 1.01);
                 // |y_i - y_j| - |x_i - x_j| <= u (|x_i - mu| + |x_j - mu|) for y = fl(x - mu)
@@ -337,7 +340,7 @@ static int knn_run(kvb_ctx ctx, size_t base, const float* X, int64_t n, int32_t 
                                                      crv, ctx->pairs_dev, ctx->stream));
             else
                 KVB_HIP(ctx, kvb::launch_select_mfma(split, Aq, Bc, nn, kpad, kp, ynorm2, rmax, em, keys, cap, slast,
-                                                     nullptr, 0, ctx->pairs_dev, ctx->stream));
+                                                     nullptr, 0, nullptr, ctx->pairs_dev, ctx->stream));
         }
         kstride = cap;
     }

@@ -337,6 +337,10 @@ __global__ __launch_bounds__(256) void k_prep_rows_thread(const float* __restric
 // rows map to sample ids through cid (-1 for padding). Lists of queries are
 // created on the first probe pass and merged into on later ones (the list's
 // kp-th score is the starting threshold); no certificate is computed.
+//
+// MODE 2 (curve order): the query tiles that the tree walk handed over
+// (crv.wide), a wavefront each, every tile scanned. lb_out holds their queries'
+// thresholds, which the lists start from.
 template <class Tr, int KS, int WV, int E, int MODE>
 __global__ __launch_bounds__(64 * WV) void k_select_mfma(
     const typename Tr::elem* __restrict__ Aq,
@@ -344,7 +348,8 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
                                                           const float* __restrict__ ynorm2,
                                                           const unsigned* __restrict__ rmax_bits, ErrModel em,
                                                           uint64_t* __restrict__ lists, float* __restrict__ lb_out,
-                                                          BucketArgs ba,
+                                                          BucketArgs ba, const int* __restrict__ wide_count,
+                                                          const int* __restrict__ wide,
                                                           unsigned long long* __restrict__ pair_count)
 {
     constexpr bool LEARNED = MODE == 1;
@@ -379,6 +384,12 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
         tbeg = ba.tptr[wk.x];
         tend = ba.tptr[wk.x + 1];
         if (lane < NQ) s_qid[wave][lane] = q0 + lane < qend ? ba.qids[q0 + lane] : -1;
+    } else if constexpr (MODE == 2) {
+        const int w = blockIdx.x * WV, count = *wide_count;
+        if (w >= count) return;   // whole workgroup
+        tend = (n + 31) / 32;
+        q0 = w + wave < count ? wide[w + wave] * NQ : n;
+        if (lane < NQ) s_qid[wave][lane] = q0 + lane < n ? q0 + lane : -1;
     } else {
         q0 = (blockIdx.x * WV + wave) * NQ;
         tend = (n + 31) / 32;
@@ -403,9 +414,12 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            tauv[r] = (!LEARNED || s_qid[wave][acc_row(r, half)] >= 0) ? __uint_as_float(0x7F800000u)
-                                                                      : -__uint_as_float(0x7F800000u);
+        for (int r = 0; r < 16; ++r) {
+            const int qid = s_qid[wave][acc_row(r, half)];
+            tauv[r] = MODE != 0 && qid < 0 ? -__uint_as_float(0x7F800000u)
+                      : MODE == 2          ? lb_out[qid]
+                                           : __uint_as_float(0x7F800000u);
+        }
         for (int q = 0; q < NQ; ++q) {
             const int qg = s_qid[wave][q];
             if (qg >= 0)
@@ -446,7 +460,7 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
     for (int i = 0; i < NQ / 4; ++i) cntw[i] = 0u;
     auto cnt_of = [&](int q) { return static_cast<int>((cntw[q >> 2] >> (8 * (q & 3))) & 0xFFu); };
     // lists that start empty are filled by the first tiles without merging
-    bool filling = !LEARNED || ba.first;
+    bool filling = MODE == 0 || (LEARNED && ba.first);
     const int fill_tiles = CAP / 32;   // the whole list capacity: a tighter first threshold
     for (int it = 0; tile >= 0; ++it) {
         const int stage = it & 1;
@@ -499,8 +513,8 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
             acc = KS > 1 ? acc0 + acc1 : acc0;
         }
 
-        const int cand = MODE != 0 ? cid_cur : tile * 32 + (lane & 31);
-        const bool valid = MODE != 0 ? cand >= 0 : cand < n;
+        const int cand = LEARNED ? cid_cur : tile * 32 + (lane & 31);
+        const bool valid = LEARNED ? cand >= 0 : cand < n;
         pairs += static_cast<unsigned long long>(nq_valid) *
                  static_cast<unsigned long long>(__popcll(__ballot(valid) & 0xFFFFFFFFull));
         if (filling) {
@@ -549,7 +563,7 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
                         if (qg >= 0)
                             nt = merge_query_list<E>(lists + static_cast<size_t>(qg) * CAP, &s_buf[wave][qa_][0], ca,
                                                      kp);
-                        if (half == 0) tauv[r] = nt;
+                        if (half == 0) tauv[r] = MODE == 2 ? fminf(tauv[r], nt) : nt;
                         ca = 0;
                         cntw[qa_ >> 2] &= ~(0xFFu << (8 * (qa_ & 3)));
                     }
@@ -559,7 +573,7 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
                         if (qg >= 0)
                             nt = merge_query_list<E>(lists + static_cast<size_t>(qg) * CAP, &s_buf[wave][qb_][0], cb,
                                                      kp);
-                        if (half == 1) tauv[r] = nt;
+                        if (half == 1) tauv[r] = MODE == 2 ? fminf(tauv[r], nt) : nt;
                         cb = 0;
                         cntw[qb_ >> 2] &= ~(0xFFu << (8 * (qb_ & 3)));
                     }
@@ -608,7 +622,8 @@ __global__ __launch_bounds__(64 * WV) void k_select_mfma(
     if (lane < NQ) {
         const int qg = s_qid[wave][lane];
         if (qg >= 0) {
-            const float sl = key_dist(lists[static_cast<size_t>(qg) * CAP + (kp - 1)]);
+            float sl = key_dist(lists[static_cast<size_t>(qg) * CAP + (kp - 1)]);
+            if (MODE == 2) sl = fminf(sl, lb_out[qg]);   // as in k_select_tree
             const double yi2 = static_cast<double>(ynorm2[qg]);
             const double yi = sqrt(yi2);
             const double Ei =
@@ -682,7 +697,7 @@ hipError_t launch_prep(const float* X, int n, int m, int split, int kpad, double
 template <class Tr, int KS, int WV>
 static hipError_t launch_sel(const void* Aq, const void* Bc, int n, int kp, const float* ynorm2, const unsigned* rmax,
                              ErrModel em, uint64_t* lists, int cap, float* lb, const BucketArgs* ba, int max_work,
-                             unsigned long long* pairs, hipStream_t st)
+                             const CurveArgs* crv, unsigned long long* pairs, hipStream_t st)
 {
     using elem = typename Tr::elem;
     const int rows_per_block = WV * 32;
@@ -698,19 +713,28 @@ static hipError_t launch_sel(const void* Aq, const void* Bc, int n, int kp, cons
         const dim3 grid(max_work);
         if (cap == 128)
             hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 2, 1>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, *ba, pairs);
+                               lists, lb, *ba, nullptr, nullptr, pairs);
         else
             hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 4, 1>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
-                               lists, lb, *ba, pairs);
+                               lists, lb, *ba, nullptr, nullptr, pairs);
         return hipGetLastError();
     }
     const dim3 grid((n + rows_per_block - 1) / rows_per_block);
+    if (crv) {
+        if (cap == 128)
+            hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 2, 2>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
+                               lists, lb, nb, crv->wide_count, crv->wide, pairs);
+        else
+            hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 4, 2>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em,
+                               lists, lb, nb, crv->wide_count, crv->wide, pairs);
+        return hipGetLastError();
+    }
     if (cap == 128)
         hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 2, 0>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em, lists,
-                           lb, nb, pairs);
+                           lb, nb, nullptr, nullptr, pairs);
     else
         hipLaunchKernelGGL((k_select_mfma<Tr, KS, WV, 4, 0>), grid, block, 0, st, A, B, n, kp, ynorm2, rmax, em, lists,
-                           lb, nb, pairs);
+                           lb, nb, nullptr, nullptr, pairs);
     return hipGetLastError();
 }
 
@@ -733,7 +757,7 @@ int mfma_pick_ksteps(int split, int needed)
 }
 
 #define KVB_SEL_CASE(TR, K, WV) \
-    case K: return launch_sel<TR, K, WV>(Aq, Bc, n, kp, ynorm2, rmax, em, lists, cap, lb, ba, max_work, pairs, st);
+    case K: return launch_sel<TR, K, WV>(Aq, Bc, n, kp, ynorm2, rmax, em, lists, cap, lb, ba, max_work, crv, pairs, st);
 
 int select_mfma_queries_per_block(int split, int kpad)
 {
@@ -744,7 +768,7 @@ int select_mfma_queries_per_block(int split, int kpad)
 
 hipError_t launch_select_mfma(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
-                              const BucketArgs* ba, int max_work, unsigned long long* pairs,
+                              const BucketArgs* ba, int max_work, const CurveArgs* crv, unsigned long long* pairs,
                               hipStream_t st)
 {
     const int ks = kpad / mfma_kstep(split);

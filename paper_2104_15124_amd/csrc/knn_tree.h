@@ -14,14 +14,14 @@
 // threshold is a value that at least kp of those 32 D scores do not exceed, found
 // by bisection (a lane's count, added over the half's lanes); it is at or
 // above the query's kp-th score, and close to it while no lane holds more than
-// D of the kp nearest: D is 5 up to kp = 96, 8 up to 192, 12 beyond (the mean per
+// D of the kp nearest: D is 5 up to kp = 96, 8 up to 224, 12 beyond (the mean per
 // lane is kp / 32; eight at kp = 256 put 474 candidates below the threshold). The
 // tiles are visited as a walk down the tree: a node's (up to 64) children are bounded
 // at once, one per lane, against the query tile's box, the pending child with the
 // smallest bound is taken first (so the thresholds fall early), and every child is
 // re-tested against the wavefront's largest distance threshold when taken. Tiles
 // in which some score is at or below its query's threshold are noted; pass 1 ends
-// with the walk or when TREC tiles are noted.
+// with the walk or when a set number of tiles are noted.
 //
 // Pass 2 goes over the noted tiles, forms the same scores again and writes
 // those at or below the threshold straight into the query's list in global
@@ -29,7 +29,9 @@
 // before the walk was over it then goes on with the walk, each tile scored once, its
 // keys written in the same way (walking the tree again from its root took
 // samples none of whose tiles can be skipped twice the products: Gaussian, n = 100k,
-// m = 16 and 64, 22.0 and 35.6 ms, 15.1 and 21.4 now; 5-manifold, n = 1M, 126 to 98).
+// m = 16 and 64, 22.0 and 35.6 ms against 15.1 and 21.4; 5-manifold, n = 1M, 126 to
+// 98). Where the tiles within reach are many (tree_wide_min), the wavefronts end after
+// pass 1 and hand their query tiles over to scans that keep no scores: 10.5 and 16.9 ms.
 // A list without room for a tile's keys is cut by a lower threshold that at least kp
 // of its keys do not exceed. Lists of kp within 32 of their capacity are sorted instead
 // once full, and take further keys from a buffer in LDS, 32 at a time (k + margin =
@@ -67,6 +69,7 @@
 // takes a quarter of the time; knn_tree.hip picks the launcher.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "knn_mfma_common.h"
@@ -76,7 +79,8 @@ namespace kvb {
 namespace {
 
 constexpr int TNQ = 32;      // queries per wavefront
-constexpr int TREC = 384;    // tiles pass 1 notes
+constexpr int TASK = 128;    // noted tiles at which a query tile is handed over
+constexpr int TREACH = WAVE * WAVE;   // the reach where every sampled tile is within reach of every sampled query tile
 // Tiles in flight. Short contractions stream the fragments of two tiles ahead
 // of the products (a tile with no hits is too short to cover the next one's
 // loads); long ones the projections of two.
@@ -84,7 +88,8 @@ constexpr int TREE_DEPTH = 3;
 constexpr int TBUF = 32;     // keys buffered per query of a full list
 constexpr float TINF = __builtin_inff();
 
-// the wavefront's LDS state
+// the wavefront's LDS state; NOTES: the tiles that pass 1 notes
+template <int NOTES>
 struct alignas(16) TreeLds {
     float tau[TNQ];                     // score thresholds (-inf: no query)
     float zt[TNQ];                      // thresholds of the projected scores (long contractions)
@@ -96,7 +101,7 @@ struct alignas(16) TreeLds {
     uint64_t mask[TREE_LEVELS];         //       pending children
     int base[TREE_LEVELS];              //       first child
     int lvl;                            //       level of the current pending list
-    uint32_t rec[TREC + TREE_DEPTH];    // the noted tiles, then those in flight when the notes were full
+    uint32_t rec[NOTES + TREE_DEPTH];    // the noted tiles, then those in flight when the notes were full
 };
 
 // the tree's shape
@@ -134,6 +139,19 @@ __device__ __forceinline__ const float* node_box(const float* tbox, const float*
                       : tree + (static_cast<size_t>(sh->off[level]) + v) * 2 * PR_DIMS;
 }
 
+__device__ __forceinline__ void load_box(const float* box, float (&b)[2 * PR_DIMS])
+{
+    const float4* src = reinterpret_cast<const float4*>(box);
+#pragma unroll
+    for (int u = 0; u < PR_DIMS / 2; ++u) {
+        const float4 t = src[u];
+        b[4 * u] = t.x;
+        b[4 * u + 1] = t.y;
+        b[4 * u + 2] = t.z;
+        b[4 * u + 3] = t.w;
+    }
+}
+
 // A group of up to 64 tiles (level 0), one per lane: first tile, pending
 // tiles and each lane's tile bound. base < 0: the walk is over.
 struct TileGroup {
@@ -155,15 +173,11 @@ __device__ __forceinline__ float child_bound(const float* tbox, const float* tre
     if (level == 0) take = take && (v < f0 || v >= f0 + nfill);
     if (!take) return __builtin_nanf("");
     float b[2 * PR_DIMS];
-    const float4* src = reinterpret_cast<const float4*>(node_box(tbox, tree, sh, level, v));
+    load_box(node_box(tbox, tree, sh, level, v), b);
+    if (level == 0) {
 #pragma unroll
-    for (int u = 0; u < PR_DIMS / 2; ++u) {
-        const float4 t = src[u];
-        b[4 * u] = t.x;
-        b[4 * u + 1] = t.y;
-        b[4 * u + 2] = t.z;
-        b[4 * u + 3] = t.w;
-        if (level == 0) reinterpret_cast<float4*>(gbox[lane])[u] = t;
+        for (int u = 0; u < PR_DIMS / 2; ++u)
+            reinterpret_cast<float4*>(gbox[lane])[u] = make_float4(b[4 * u], b[4 * u + 1], b[4 * u + 2], b[4 * u + 3]);
     }
     return box_bound(b, qbox, qbox + PR_DIMS, bb);
 }
@@ -195,7 +209,8 @@ struct PointTest {
 // The next group of tiles within reach of thr, after the current one is
 // exhausted: up the levels until a pending child within reach, the nearest
 // one taken, then down to its tiles. Whole wavefront.
-__device__ __forceinline__ TileGroup climb(TreeLds& W, const TreeShape* sh, const float* tbox, const float* tree,
+template <int NOTES>
+__device__ __forceinline__ TileGroup climb(TreeLds<NOTES>& W, const TreeShape* sh, const float* tbox, const float* tree,
                                         BoxBound bb, const PointTest& pt, float thr, int f0, int nfill)
 {
     const int lane = lane_id();
@@ -371,6 +386,22 @@ __device__ __noinline__ float sort_list(uint64_t* __restrict__ dst, int cnt, int
     return key_dist(list_at<E>(L, kp - 1));
 }
 
+// Bound on the error of the scores of a query of squared norm yi2 (E_i), and the
+// lower bound on the squared distance of its candidates with a score at or above s.
+__device__ __forceinline__ double score_error(float yi2, float R, const ErrModel& em)
+{
+    const double Rd = static_cast<double>(R), yi = sqrt(static_cast<double>(yi2));
+    return em.gamma * (Rd + 1.05 * yi) * (Rd + 1.05 * yi) + em.norm * Rd * Rd + em.cross * yi * Rd + 1e-30;
+}
+__device__ __forceinline__ float certificate_bound(float s, float yi2, float R, const ErrModel& em)
+{
+    const double t = static_cast<double>(s) + static_cast<double>(yi2) - score_error(yi2, R, em);
+    double B = t > 0.0 ? sqrt(t) : 0.0;
+    B -= em.center * (sqrt(static_cast<double>(yi2)) + static_cast<double>(R));
+    B = B > 0.0 ? B : 0.0;
+    return static_cast<float>(B * B * (1.0 - 1.0 / 1048576.0));
+}
+
 // stores of this wavefront complete before its later loads read them
 __device__ __forceinline__ void wave_global_sync()
 {
@@ -403,7 +434,7 @@ template <class Tr, int KS, bool LONG, int E, int D, bool BUF, int WPE>
 __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     const typename Tr::elem* __restrict__ Aq, const typename Tr::elem* __restrict__ Bc, int n, int kp,
     const float* __restrict__ ynorm2, const unsigned* __restrict__ rmax_bits, ErrModel em,
-    uint64_t* __restrict__ lists, float* __restrict__ lb_out, CurveArgs crv,
+    uint64_t* __restrict__ lists, float* __restrict__ lb_out, CurveArgs crv, int probe, int wide_min,
     unsigned long long* __restrict__ pair_count)
 {
     using elem = typename Tr::elem;
@@ -412,7 +443,9 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     constexpr int KR = LONG ? 1 : KS;           // fragments of a tile kept in registers
     constexpr int CAP = WAVE * E;
     constexpr int FILL = CAP / 32;
-    __shared__ TreeLds W;
+    // the notes; fewer where the operand and the buffers would leave room for only three wavefronts per CU
+    constexpr int NOTES = LONG && BUF ? 224 : 384;
+    __shared__ TreeLds<NOTES> W;
     __shared__ TreeShape s_shape;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     frag* s_a = reinterpret_cast<frag*>(s_dyn);   // LONG: the query operand, [k-step][lane]
@@ -431,7 +464,8 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         }
     }
     const int ntiles = crv.layout.cnt[0];
-    const int t0 = xcd_block();   // this wavefront's query tile
+    // this wavefront's query tile
+    const int t0 = probe ? static_cast<int>(static_cast<int64_t>(blockIdx.x) * ntiles / gridDim.x) : xcd_block();
     const int q0 = t0 * TNQ;
     const int nq_valid = min(TNQ, n - q0);
     uint64_t* lists_q0 = lists + static_cast<size_t>(q0) * CAP;
@@ -501,12 +535,6 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
 
     // the distance threshold of a score threshold (rounded up)
     auto dist_threshold = [](float score, float yq) { return fmaxf(score + yq, 0.f) * (1.f + 4.8e-7f); };
-    // lane q < 32: bound on the error of query q's scores (the certificate's E_i)
-    auto score_error = [&](int q) {
-        const double Rd = static_cast<double>(R);
-        const double yi2 = static_cast<double>(W.yq[q]), yi = sqrt(yi2);
-        return em.gamma * (Rd + 1.05 * yi) * (Rd + 1.05 * yi) + em.norm * Rd * Rd + em.cross * yi * Rd + 1e-30;
-    };
     // distance thresholds and, LONG, projected thresholds from W.tau (`counted`:
     // those of every candidate whose computed score is at or below it); returns
     // the wavefront's largest distance threshold (read from one lane, so that
@@ -525,7 +553,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
             };
             W.gt[lane] = lane < nq_valid ? projected(t) : -TINF;
             if constexpr (LONG) {
-                const float tz = counted ? t + static_cast<float>(score_error(lane) * (1.0 + 1e-6)) : t;
+                const float tz = counted ? t + static_cast<float>(score_error(W.yq[lane], R, em) * (1.0 + 1e-6)) : t;
                 W.zt[lane] = lane < nq_valid ? projected(tz) + zconst : -TINF;
             }
         }
@@ -662,7 +690,7 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         return publish(false);
     };
     unsigned long long pairs = 0;
-    int nrec = 0;       // tiles noted (at most TREC)
+    int nrec = 0;       // tiles noted (at most NOTES)
     int pend = 0;       // noted since the last refresh
     auto take_scores = [&](const f32x16& acc, int tile) {
         const int cand = tile * 32 + l31;
@@ -771,6 +799,25 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         return __ballot(tile * 32 + l31 < n && hit) != 0ull;
     };
 
+    // how many of 64 tiles spread over the samples are within reach of some query
+    auto sampled_reach = [&]() {
+        const int v = static_cast<int>(static_cast<int64_t>(lane) * ntiles / WAVE);
+        float b[2 * PR_DIMS];
+        load_box(crv.tbox + static_cast<size_t>(v) * 2 * PR_DIMS, b);
+        bool in = false;
+        for (int q = 0; q < nq_valid; ++q) {
+            float g2 = 0.f;
+#pragma unroll
+            for (int c = 0; c < PR_DIMS; ++c) {
+                const float z = __int_as_float(
+                    __builtin_amdgcn_readlane(__float_as_int(pt.z[c % 4]), q + 32 * (c / 4)));
+                const float g = fmaxf(fmaxf(b[c] - z, z - b[PR_DIMS + c]), 0.f);
+                g2 = fmaf(g, g, g2);
+            }
+            in = in || g2 <= W.gt[q];
+        }
+        return __popcll(__ballot(in));
+    };
     constexpr int DEPTH = TREE_DEPTH;
     constexpr int ZR = LONG ? DEPTH : 1, BR = LONG ? 1 : DEPTH;
     int tq[DEPTH];         // the tiles in flight, the current one first (-1: none)
@@ -819,7 +866,16 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     auto walk_next = [&](float& tb) { return next_tile(wthr, tb); };
     walk_start();
     pipe_start(walk_next);
-    while (tq[0] >= 0 && nrec < TREC) {
+    // a launch of 64 query tiles spread over the samples adds up their reach by the
+    // thresholds of the fill (looser than a walk's)
+    if (probe) {
+        const int reach = sampled_reach();
+        if (lane == 0) atomicAdd(crv.wide_count + 1, reach);
+        return;
+    }
+    const bool wide = crv.wide_count[1] > wide_min;
+    const int notes = wide ? TASK : NOTES;
+    while (tq[0] >= 0 && nrec < notes) {
         tq[DEPTH - 1] = tq[DEPTH - 2] >= 0 ? walk_next(tbq[DEPTH - 1]) : -1;
         fetch(DEPTH - 1);
         // the current tile may have fallen out of reach since it was taken
@@ -835,6 +891,11 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
         shift();
     }
     wthr = refresh(9);
+    if (wide && tq[0] >= 0) {   // the scans start from these thresholds
+        if (lane < nq_valid) lb_out[q0 + lane] = W.tau[lane];
+        if (lane == 0) crv.wide[atomicAdd(crv.wide_count, 1)] = t0;
+        return;
+    }
 
     // ================================================================ pass 2
     int at[16];   // the next free key of this half's queries' lists (from lists_q0)
@@ -1024,15 +1085,202 @@ __global__ __launch_bounds__(WAVE, WPE) void k_select_tree(
     count_pairs(pair_count, pairs);
 
     // certificate lower bound for the candidates left out of each list
-    if (lane < nq_valid) {
-        const int qg = q0 + lane;
-        const double yi2 = static_cast<double>(W.yq[lane]);
-        const double t = static_cast<double>(W.tau[lane]) + yi2 - score_error(lane);
-        double B = t > 0.0 ? sqrt(t) : 0.0;
-        B -= em.center * (sqrt(yi2) + static_cast<double>(R));
-        B = B > 0.0 ? B : 0.0;
-        lb_out[qg] = static_cast<float>(B * B * (1.0 - 1.0 / 1048576.0));
+    if (lane < nq_valid) lb_out[q0 + lane] = certificate_bound(W.tau[lane], W.yq[lane], R, em);
+}
+
+// The query tiles of short contractions that k_select_tree handed over (crv.wide),
+// a wavefront each: many tiles are within reach, so there is little to walk or to
+// note. Every tile within reach by its box (and, unless all sampled ones were, by the
+// single queries) is scored once, 64 boxes bounded at a time from the own group on;
+// lists start empty from the thresholds in lb_out and take keys from buffers in
+// LDS, TBUF at a time. Bound by the latency of a tile's chain (box tests, products,
+// compares); without kept scores the registers hold up to four wavefronts per
+// SIMD instead of two, which is what this form is for (tree_wide_min).
+template <class Tr, int KS>
+constexpr int scan_waves()
+{
+    constexpr int fr = TREE_DEPTH * KS * static_cast<int>(sizeof(typename Tr::frag) / 4);
+    return fr <= 36 ? 4 : fr <= 64 ? 3 : 2;
+}
+
+template <class Tr, int KS, int E>
+__global__ __launch_bounds__(WAVE, (scan_waves<Tr, KS>())) void k_select_scan(
+    const typename Tr::elem* __restrict__ Aq, const typename Tr::elem* __restrict__ Bc, int n, int kp,
+    const float* __restrict__ ynorm2, const unsigned* __restrict__ rmax_bits, ErrModel em,
+    uint64_t* __restrict__ lists, float* __restrict__ lb_out, CurveArgs crv,
+    unsigned long long* __restrict__ pair_count)
+{
+    using elem = typename Tr::elem;
+    using frag = typename Tr::frag;
+    constexpr int kpad = KS * Tr::KSTEP;
+    constexpr int CAP = WAVE * E;
+    constexpr int DEPTH = TREE_DEPTH;
+    __shared__ uint64_t s_buf[TNQ][TBUF];
+    __shared__ __attribute__((aligned(16))) float s_tau[TNQ];   // score thresholds (-inf: no query)
+    __shared__ float s_yq[TNQ], s_box[2 * PR_DIMS];
+    const int count = *crv.wide_count;
+    if (static_cast<int>(blockIdx.x) >= count) return;
+    const int lane = lane_id();
+    const int half = lane >> 5, l31 = lane & 31;
+    const int t0 = crv.wide[xcd_index(blockIdx.x, count)];
+    const int q0 = t0 * TNQ;
+    const int nq_valid = min(TNQ, n - q0);
+    const int ntiles = crv.layout.cnt[0];
+    uint64_t* lists_q0 = lists + static_cast<size_t>(q0) * CAP;
+    frag qa[KS];
+    {
+        const elem* src = Aq + static_cast<size_t>(min(q0 + l31, n - 1)) * kpad + half * Tr::VEC;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qa[s] = Tr::load(src + s * Tr::KSTEP);
     }
+    const float R = __uint_as_float(*rmax_bits);
+    BoxBound bb;
+    bb.zerr = crv.zcoef * R;
+    bb.pscale = *crv.pscale;
+    bb.yerr = crv.ycoef * R;
+    PointTest pt;
+    {
+        const float4 z = reinterpret_cast<const float4*>(crv.zs + static_cast<size_t>(min(q0 + l31, n - 1)) * PR_DIMS)[half];
+        pt.z[0] = z.x;
+        pt.z[1] = z.y;
+        pt.z[2] = z.z;
+        pt.z[3] = z.w;
+    }
+    if (lane < 2 * PR_DIMS) s_box[lane] = crv.tbox[static_cast<size_t>(t0) * 2 * PR_DIMS + lane];
+    if (lane < TNQ) {
+        s_yq[lane] = lane < nq_valid ? ynorm2[q0 + lane] : 0.f;
+        s_tau[lane] = lane < nq_valid ? lb_out[q0 + lane] : -TINF;
+    }
+    for (int q = 0; q < nq_valid; ++q)
+#pragma unroll
+        for (int s = 0; s < E; ++s) lists_q0[static_cast<size_t>(q) * CAP + s * WAVE + lane] = KEY_INF;
+    wave_lds_sync();
+    wave_global_sync();
+    auto reach_threshold = [&]() {
+        const float t = l31 < nq_valid ? fmaxf(s_tau[l31] + s_yq[l31], 0.f) * (1.f + 4.8e-7f) : -TINF;
+        const float p = (sqrtf(fmaxf(t, 0.f)) * (1.f + 1e-6f) + bb.yerr) / bb.pscale + 2.f * 2.8285f * bb.zerr;
+        pt.gt = l31 < nq_valid ? p * p * (1.f + 4e-6f) : -TINF;
+        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wave_max_f32(t))));
+    };
+    float wthr = reach_threshold();
+    float tauv[16];   // this lane's accumulator register r holds row acc_row(r, half)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tauv[r] = s_tau[acc_row(r, half)];
+    // the buffers' fill, wave-uniform: query q's count in byte q % 4 of cntw[q / 4]
+    uint32_t cntw[TNQ / 4];
+#pragma unroll
+    for (int i = 0; i < TNQ / 4; ++i) cntw[i] = 0u;
+    auto cnt_of = [&](int q) { return static_cast<int>((cntw[q >> 2] >> (8 * (q & 3))) & 0xFFu); };
+
+    const int ngroups = (ntiles + WAVE - 1) / WAVE;
+    int grp = t0 / WAVE, left = ngroups;   // the next group, groups not yet taken
+    int base = 0;
+    uint64_t mask = 0ull;
+    const bool test = crv.wide_count[1] < TREACH;   // against the single queries too
+    auto next_tile = [&]() -> int {
+        while (true) {
+            if (!mask) {
+                if (left == 0) return -1;
+                --left;
+                base = grp * WAVE;
+                grp = grp + 1 == ngroups ? 0 : grp + 1;
+                const int v = base + lane;
+                float b[2 * PR_DIMS], qb[2 * PR_DIMS];
+                load_box(crv.tbox + static_cast<size_t>(min(v, ntiles - 1)) * 2 * PR_DIMS, b);
+#pragma unroll
+                for (int c = 0; c < 2 * PR_DIMS; ++c) qb[c] = s_box[c];
+                mask = __ballot(v < ntiles && box_bound(b, qb, qb + PR_DIMS, bb) <= wthr);
+                continue;
+            }
+            const int c = __builtin_ctzll(mask);
+            mask &= mask - 1;
+            if (test) {
+                const float4* nb = reinterpret_cast<const float4*>(crv.tbox + static_cast<size_t>(base + c) * 2 * PR_DIMS);
+                if (!pt.reach(nb[half], nb[PR_DIMS / 4 + half])) continue;
+            }
+            return base + c;
+        }
+    };
+    int tq[DEPTH];
+    frag bq[DEPTH][KS];
+    auto load_tile = [&](int t, frag (&b)[KS]) {
+        const elem* src = Bc + static_cast<size_t>(max(t, 0)) * 32 * kpad + lane * Tr::VEC;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) b[s] = Tr::load(src + s * 64 * Tr::VEC);
+    };
+#pragma unroll
+    for (int d = 0; d + 1 < DEPTH; ++d) {
+        tq[d] = next_tile();
+        load_tile(tq[d], bq[d]);
+    }
+    unsigned long long pairs = 0;
+    bool fell = false;
+    while (tq[0] >= 0) {
+        if (fell) {
+            wthr = reach_threshold();
+            fell = false;
+        }
+        tq[DEPTH - 1] = next_tile();
+        load_tile(tq[DEPTH - 1], bq[DEPTH - 1]);
+        f32x16 acc = {};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) acc = Tr::mma(qa[s], bq[0][s], acc);
+        const int cand = tq[0] * 32 + l31;
+        const bool valid = cand < n;
+        pairs += static_cast<unsigned long long>(nq_valid) * __popcll(__ballot(valid) & 0xFFFFFFFFull);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            uint64_t hit = __ballot(valid && acc[r] <= tauv[r]);
+            if (!hit) continue;
+            const int qa_ = acc_row(r, 0), qb_ = acc_row(r, 1);
+            int ca = cnt_of(qa_), cb = cnt_of(qb_);
+            const bool fa = ca + __popc(static_cast<uint32_t>(hit)) > TBUF;
+            const bool fb = cb + __popc(static_cast<uint32_t>(hit >> 32)) > TBUF;
+            if (fa || fb) {
+                wave_lds_sync();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (!(h ? fb : fa)) continue;
+                    const int q = h ? qb_ : qa_;
+                    const float nt = merge_query_list<E>(lists_q0 + static_cast<size_t>(q) * CAP, &s_buf[q][0],
+                                                         h ? cb : ca, kp);
+                    if (half == h) tauv[r] = fminf(tauv[r], nt);
+                    if (lane == 0) s_tau[q] = fminf(s_tau[q], nt);
+                    (h ? cb : ca) = 0;
+                    cntw[q >> 2] &= ~(0xFFu << (8 * (q & 3)));
+                }
+                fell = true;
+                wave_lds_sync();
+                hit = __ballot(valid && acc[r] <= tauv[r]);
+            }
+            const int pa = __popc(static_cast<uint32_t>(hit)), pb = __popc(static_cast<uint32_t>(hit >> 32));
+            // (mbcnt64 counts the lower half's lanes too in the upper half)
+            const int slot0 = half ? qb_ * TBUF + cb - pa : qa_ * TBUF + ca;
+            if (valid && acc[r] <= tauv[r])
+                (&s_buf[0][0])[slot0 + mbcnt64(hit)] = make_key(acc[r], static_cast<uint32_t>(cand));
+            cntw[qa_ >> 2] += static_cast<uint32_t>(pa) << (8 * (qa_ & 3));
+            cntw[qb_ >> 2] += static_cast<uint32_t>(pb) << (8 * (qb_ & 3));
+        }
+#pragma unroll
+        for (int d = 0; d + 1 < DEPTH; ++d) {
+            tq[d] = tq[d + 1];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) bq[d][s] = bq[d + 1][s];
+        }
+    }
+    wave_lds_sync();
+    int cnt_lane = 0;   // query q's count moved to lane q
+#pragma unroll
+    for (int q = 0; q < TNQ; ++q)
+        if (lane == q) cnt_lane = cnt_of(q);
+    for (int q = 0; q < nq_valid; ++q) {
+        const float nt = merge_query_list<E>(lists_q0 + static_cast<size_t>(q) * CAP, &s_buf[q][0],
+                                             __builtin_amdgcn_readlane(cnt_lane, q), kp);
+        if (lane == 0) s_tau[q] = fminf(s_tau[q], nt);
+    }
+    wave_lds_sync();
+    count_pairs(pair_count, pairs);
+    if (lane < nq_valid) lb_out[q0 + lane] = certificate_bound(s_tau[lane], s_yq[lane], R, em);
 }
 
 // ------------------------------------------------------------------ launcher
@@ -1056,10 +1304,31 @@ hipError_t tree_f32_wide(int ks, const TreeCall& c);
 hipError_t tree_bf16(int ks, const TreeCall& c);       // up to 10
 hipError_t tree_bf16_wide(int ks, const TreeCall& c);
 
-template <class Tr, int KS, bool LONG>
+// long contractions: the query operand in LDS, the pairwise projected bound
+constexpr bool tree_long(int split, int ks) { return ks > (split == 0 ? 16 : 5); }
+
+// Query tiles are handed over where the sampled reach (k_select_tree) exceeds
+// this. Short contractions, to k_select_scan: where some 2048 tiles and a
+// sixteenth of all are within a query tile's reach (Gaussian n = 100k m = 16
+// 15.2 to 10.5 ms; 12-dimensional clusters n = 1M, a tenth within reach, 109 to 78;
+// 5-dimensional Gaussian n = 100k, 1200 tiles, 4.2 by the walk and 4.7; the mixture n =
+// 8M, one tile in 60, 98 and 125). Long ones, to the workgroup scan of every tile: where
+// every sampled tile is (Gaussian n = 100k m = 128 BF16 45 to 20 ms; 7-dimensional
+// Gaussian n = 30k m = 64, 99% of them, 3.9 by the walk and 4.6) and the query tiles
+// fill the chip (Gaussian n = 8000 m = 64 BF16 2.4 and 2.9; n = 30k 5.7 and 5.0).
+constexpr int tree_wide_min(bool is_long, int ntiles)
+{
+    if (is_long) return ntiles > 512 ? TREACH - 1 : TREACH;
+    if (ntiles <= 2048) return TREACH;
+    const int share = static_cast<int>(int64_t(2048) * TREACH / ntiles);
+    return share > TREACH / 16 ? share : TREACH / 16;
+}
+
+template <class Tr, int KS>
 static hipError_t launch_tree(const TreeCall& c)
 {
     using elem = typename Tr::elem;
+    constexpr bool LONG = tree_long(std::is_same<Tr, TraitsF32>::value ? 0 : 3, KS);
     const int n = c.n, kp = c.kp, cap = c.cap;
     if (kp > cap || (cap != 128 && cap != 256)) return hipErrorInvalidValue;
     const int ntiles = (n + 31) / 32;
@@ -1071,20 +1340,35 @@ static hipError_t launch_tree(const TreeCall& c)
     // 32. Two wavefronts per SIMD, or one where the kept scores, or the query
     // operand in LDS, leave no room for two (then the products' loads run ahead).
     constexpr int W5 = LONG && KS * sizeof(typename Tr::frag) > 13 * 16 ? 1 : 2, W8 = LONG ? 1 : 2;
+    const int wide_min = tree_wide_min(LONG, ntiles);
     auto go = [&](auto kernel, bool buf) {
         const size_t keys = buf ? TNQ * TBUF * sizeof(uint64_t) + TNQ * sizeof(int) : 2 * TNQ * sizeof(uint64_t);
         const size_t dyn = tree_operand_bytes<Tr, KS, LONG>() + keys;
-        hipLaunchKernelGGL(kernel, grid, block, dyn, c.st, A, B, n, kp, c.ynorm2, c.rmax, c.em, c.lists, c.lb, c.crv,
-                           c.pairs);
+        auto run = [&](dim3 g, int probe) {
+            hipLaunchKernelGGL(kernel, g, block, dyn, c.st, A, B, n, kp, c.ynorm2, c.rmax, c.em, c.lists, c.lb, c.crv,
+                               probe, wide_min, c.pairs);
+        };
+        if (wide_min < TREACH) run(dim3(WAVE), 1);
+        run(grid, 0);
     };
     if (kp <= 96)
         go(k_select_tree<Tr, KS, LONG, 2, 5, false, W5>, false);
     else if (cap == 128)
         go(k_select_tree<Tr, KS, LONG, 2, 8, true, W8>, true);
-    else if (kp <= 192)
+    else if (kp <= 224)
         go(k_select_tree<Tr, KS, LONG, 4, 8, false, W8>, false);
     else
         go(k_select_tree<Tr, KS, LONG, 4, 12, true, 1>, true);
+    if constexpr (!LONG) {   // (the long ones: launch_select_tree)
+        auto scan = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, c.st, A, B, n, kp, c.ynorm2, c.rmax, c.em, c.lists, c.lb, c.crv,
+                               c.pairs);
+        };
+        if (wide_min < TREACH && cap == 128)
+            scan(k_select_scan<Tr, KS, 2>);
+        else if (wide_min < TREACH)
+            scan(k_select_scan<Tr, KS, 4>);
+    }
     return hipGetLastError();
 }
 

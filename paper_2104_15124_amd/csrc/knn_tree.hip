@@ -9,8 +9,11 @@ hipError_t launch_select_tree(int split, const void* Aq, const void* Bc, int n, 
 {
     const int ks = kpad / mfma_kstep(split);
     const TreeCall c = {Aq, Bc, n, kp, ynorm2, rmax, em, lists, cap, lb, crv, pairs, st};
-    if (split == 0) return ks <= 32 ? tree_f32(ks, c) : tree_f32_wide(ks, c);
-    return ks <= 10 ? tree_bf16(ks, c) : tree_bf16_wide(ks, c);
+    const hipError_t e = split == 0 ? (ks <= 32 ? tree_f32(ks, c) : tree_f32_wide(ks, c))
+                                    : (ks <= 10 ? tree_bf16(ks, c) : tree_bf16_wide(ks, c));
+    if (e != hipSuccess || !tree_long(split, ks) || tree_wide_min(true, crv.layout.cnt[0]) >= TREACH) return e;
+    // the query tiles handed over
+    return launch_select_mfma(split, Aq, Bc, n, kpad, kp, ynorm2, rmax, em, lists, cap, lb, nullptr, 0, &crv, pairs, st);
 }
 
 }  // namespace kvb

@@ -6,11 +6,11 @@ namespace kvb {
 hipError_t tree_bf16_wide(int ks, const TreeCall& c)
 {
     switch (ks) {
-    case 13: return launch_tree<TraitsBF16, 13, true>(c);
-    case 16: return launch_tree<TraitsBF16, 16, true>(c);
-    case 20: return launch_tree<TraitsBF16, 20, true>(c);
-    case 25: return launch_tree<TraitsBF16, 25, true>(c);
-    case 32: return launch_tree<TraitsBF16, 32, true>(c);
+    case 13: return launch_tree<TraitsBF16, 13>(c);
+    case 16: return launch_tree<TraitsBF16, 16>(c);
+    case 20: return launch_tree<TraitsBF16, 20>(c);
+    case 25: return launch_tree<TraitsBF16, 25>(c);
+    case 32: return launch_tree<TraitsBF16, 32>(c);
     default: return hipErrorNotSupported;
     }
 }

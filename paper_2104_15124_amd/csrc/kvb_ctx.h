@@ -14,10 +14,11 @@
 
 namespace kvbh {
 
-// a k-NN call's counters, cleared together: the scored pairs, then the fallback rows
+// a k-NN call's counters, cleared together: the scored pairs, then the
+// fallback rows, the query tiles handed over by the tree walk and its measured reach
 constexpr size_t PAIR_WORDS = size_t(kvb::PAIR_SLOTS) * kvb::PAIR_STRIDE;
 constexpr size_t PAIR_BYTES = PAIR_WORDS * sizeof(unsigned long long);
-constexpr size_t COUNTER_BYTES = PAIR_BYTES + sizeof(int);
+constexpr size_t COUNTER_BYTES = PAIR_BYTES + 3 * sizeof(int);
 
 struct ProfPair {
     int slot;
@@ -80,6 +81,7 @@ struct kvb_ctx_s {
     kvbh::BuildDev* build_host = nullptr;   // pinned
     int* fb_count_dev = nullptr;            // fallback rows of the last kvb_knn
     int* fb_count_host = nullptr;           // pinned
+    int* wide_count_dev = nullptr;          // query tiles that k_select_tree handed over in the last kvb_knn
     unsigned long long* pairs_dev = nullptr;   // candidate pairs scored by the last kvb_knn (see count_pairs)
     unsigned long long* pairs_host = nullptr;  // pinned
     unsigned long long* union_host = nullptr;  // pinned [2]: reverse entries / check flags, invalid-input flag

@@ -55,6 +55,8 @@ struct CurveArgs {
     const float* pscale;// |v| >= *pscale |P^T v| for every v (set with the basis)
     float zcoef;        // computed projected coordinates are within zcoef R of P^T y (R = max |y|)
     float ycoef;        // |y_i - y_j| exceeds |x_i - x_j| by at most ycoef R
+    int* wide_count;    // [2], 0 before the select: query tiles handed over by k_select_tree; the sampled reach
+    int* wide;          // [tiles] the query tiles handed over
 };
 
 struct TuneResult {
@@ -118,7 +120,7 @@ int mfma_pick_ksteps(int split, int needed);
 // selection with max_work workgroups (the kernel skips those beyond *ba->n_work).
 hipError_t launch_select_mfma(int split, const void* Aq, const void* Bc, int n, int kpad, int kp, const float* ynorm2,
                               const unsigned* rmax, ErrModel em, uint64_t* lists, int cap, float* lb,
-                              const BucketArgs* ba, int max_work, unsigned long long* pairs,
+                              const BucketArgs* ba, int max_work, const CurveArgs* crv, unsigned long long* pairs,
                               hipStream_t st);
 // curve order of the samples (spatial_mfma.hip)
 int cov_partials();

@@ -47,7 +47,7 @@ def test_rows_are_complete(gpu_lib, m):
     assert (np.diff(np.sort(gi, axis=1), axis=1) > 0).all()
 
 
-def check(kvb, X, k, margin, split, mode="bf16", nrows=600):
+def check(kvb, X, k, margin, split, mode="bf16", nrows=300):
     gi, gd = search(kvb, X, k, margin, split, mode)
     rows = np.random.default_rng(k).choice(len(X), nrows, replace=False)
     ri, rd = knn_reference(X, k, rows)
@@ -60,7 +60,7 @@ def test_coarse_scores(gpu_lib, m, margin):
     for radius in (0.005, 0.02):
         check(gpu_lib, clusters(12000, m, radius, m), 64, margin, 1)
     check(gpu_lib, workloads.gaussian_mixture(16384, seed=m, m=m), 64, margin, 1)
-    check(gpu_lib, workloads.sphere3_lifted(65536, seed=m, m=m), 16, margin, 1, nrows=300)
+    check(gpu_lib, workloads.sphere3_lifted(20000, seed=m, m=m), 16, margin, 1, nrows=150)
     check(gpu_lib, clusters(12000, 84, 0.02, m), 64, margin, 6)   # 6 m + 3 terms of at most 512
 
 
@@ -68,12 +68,23 @@ def test_coarse_scores(gpu_lib, m, margin):
 LISTS = [(40, 0), (64, 32), (65, 32), (128, 0), (97, 32), (160, 32), (161, 32), (224, 32)]
 
 
-@pytest.mark.parametrize("m,mode,split", [(16, "f32", 3), (16, "bf16", 3), (64, "bf16", 3), (100, "f32", 3)])
-def test_more_tiles_than_notes(gpu_lib, m, mode, split):
-    # no tile of 25000 unstructured samples can be skipped: 782 tiles within reach of every query
+@pytest.mark.parametrize("m,mode", [(16, "f32"), (16, "bf16"), (64, "bf16"), (100, "f32")])
+def test_more_tiles_than_notes(gpu_lib, m, mode):
+    # no tile of the unstructured samples can be skipped (some 700 tiles within reach of
+    # every query), those of a far cluster can
     X = workloads.gaussian_iid(25000, m, seed=m)
+    X[::10] = X[::10] * 0.1 + 40
     for k, margin in LISTS:
-        check(gpu_lib, X, k, margin, split, mode, nrows=500)
+        check(gpu_lib, X, k, margin, 3, mode, nrows=500)
+
+
+@pytest.mark.parametrize("n,m,mode", [(70001, 12, "f32"), (70001, 16, "bf16"), (70001, 31, "f32"),   # short contractions
+                                      (25001, 64, "bf16"), (25001, 100, "f32"), (17000, 160, "bf16")])
+def test_every_tile_within_reach(gpu_lib, n, m, mode):
+    # the query tiles are handed over from the walk to the scans of every tile
+    X = workloads.gaussian_iid(n, m, seed=m)
+    for k, margin in ((9, 0), (40, 32), (97, 31), (224, 32)):
+        check(gpu_lib, X, k, margin, 3, mode, nrows=200)
 
 
 def test_more_tiles_than_notes_coarse(gpu_lib):
