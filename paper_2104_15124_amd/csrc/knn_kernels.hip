@@ -43,14 +43,14 @@ namespace kvb {
 // the selection scores.
 //
 // Candidates passing the current threshold of a row are appended to that row's
-// buffer in LDS, twice the list's capacity of 64 E keys. When a further tile
-// might not fit, bisection over the scores finds a threshold that between kp
-// and 64 E of the keys do not exceed; the keys beyond it are dropped and the
-// row's threshold is lowered to it. At the end the buffer, cut down in the same
-// way, is sorted once. (Merging every 64 keys into a sorted list took three to
-// five networks per row where one is enough: 64 nearest of 100k on the torus,
-// 226 to 170 us.) Keys carry curve positions; the re-rank maps them to original
-// indices and breaks ties on those, so ties order as in I(x, k).
+// buffer in LDS, larger than the list's capacity of 64 E keys. When it is full
+// (CutRule), bisection over the scores finds a threshold that between kp and 64 E
+// of the keys do not exceed; the keys beyond it are dropped and the row's threshold
+// is lowered to it. At the end the buffer, cut down in the same way, is sorted
+// once. (Merging every 64 keys into a sorted list took three to five networks per
+// row where one is enough: 64 nearest of 100k on the torus, 226 to 170 us.) Keys
+// carry curve positions; the re-rank maps them to original indices and breaks ties
+// on those, so ties order as in I(x, k).
 struct SpatialView {
     const float* Xs;      // [n, m] coordinates in curve order
     const float* tbox;    // [tiles, 2, m]: lower corner, then upper corner
@@ -146,37 +146,58 @@ __device__ __forceinline__ void append_keys(uint64_t* buf, int& count, float tau
     count += __popcll(mask);
 }
 
+// When a row's buffer is cut and how far. Up to five coordinates a row's
+// candidates come from few tiles and a cut costs more than a loose threshold: the
+// buffer is filled (twice the capacity; 256 keys for lists of 64, which a buffer of
+// 128 cut at every further key where kp is 64). From six on the tiles within reach
+// grow steeply with the threshold: it is lowered after every 32 further keys (64
+// where the threshold has to be close to exact), and the smaller buffer leaves
+// room for more wavefronts. Eight coordinates, Gaussian n = 300k: k = 16 19.3 to 16.4
+// ms, k = 160 35.3 to 28.1 (16.1 and 25.5 by merges); six, n = 100k, k = 160 3.19 to 2.59.
+template <int M, int E>
+struct CutRule {
+    static constexpr int CAP = WAVE * E;   // of a list
+    static constexpr int BUF = M >= 6 ? CAP + 2 * WAVE : E == 1 ? 4 * WAVE : 2 * CAP;
+    static constexpr int S = BUF / WAVE;   // keys per lane
+    __device__ static int full(int kp)     // cut a buffer of more keys than this (a tile adds up to 64)
+    {
+        return M >= 6 ? kp + (kp + 32 <= CAP ? 32 : 64) : BUF - WAVE;
+    }
+    __device__ static int keep(int kp) { return M >= 6 ? min(kp + 8, CAP) : CAP; }   // to at most this many
+};
+
 // The 64 E smallest of more keys than a threshold can part (hundreds of equal
 // scores), sorted, at the front of the buffer. Whole wavefront. (An LDS pointer:
 // through a generic one the stores would not be ordered with the caller's LDS
 // reads.)
 using lds_key = __attribute__((address_space(3))) uint64_t;
-template <int E>
+template <int E, int S>
 __device__ __noinline__ void sort_front(lds_key* buf, int count)
 {
+    constexpr int P = S <= 4 ? 4 : 8;   // the network's power of two
     const int lane = lane_id();
-    uint64_t v[2 * E];
+    uint64_t v[P];
 #pragma unroll
-    for (int s = 0; s < 2 * E; ++s) v[s] = s * WAVE + lane < count ? buf[s * WAVE + lane] : KEY_INF;
-    bitonic_sort<2 * E>(v);
+    for (int s = 0; s < P; ++s) v[s] = s < S && s * WAVE + lane < count ? buf[s * WAVE + lane] : KEY_INF;
+    bitonic_sort<P>(v);
     wave_lds_sync();
 #pragma unroll
     for (int s = 0; s < E; ++s) buf[s * WAVE + lane] = v[s];
     wave_lds_sync();
 }
 
-// Drop the farthest of a buffer's count keys (64 E < count <= 128 E) until
-// between kp and 64 E are left, which hold the kp smallest; no score above the
+// Drop the farthest of a buffer's count keys (most < count <= 64 S) until
+// between kp and `most` are left, which hold the kp smallest; no score above the
 // new tau is among the kp smallest. Whole wavefront.
-template <int E>
-__device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau, int kp)
+template <int E, int S>
+__device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau, int kp, int most)
 {
     const int lane = lane_id();
     wave_lds_sync();
-    uint64_t v[2 * E];
-    float d[2 * E];
+    uint64_t v[S];
+    float d[S];
 #pragma unroll
-    for (int s = 0; s < 2 * E; ++s) {
+    for (int s = 0; s < S; ++s) {
         v[s] = s * WAVE + lane < count ? buf[s * WAVE + lane] : KEY_INF;
         d[s] = key_dist(v[s]);   // +inf past the end: above every threshold tried
     }
@@ -189,7 +210,7 @@ __device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau
         const float a = __uint_as_float(lo), b = __uint_as_float(hi);
         // twice where the counts' share falls, then the middle; where neither
         // lies inside (infinite or adjacent ends), the middle of the bits
-        const float share = it < 2 ? static_cast<float>((kp + WAVE * E) / 2 - below) *
+        const float share = it < 2 ? static_cast<float>((kp + most) / 2 - below) *
                                          __builtin_amdgcn_rcpf(static_cast<float>(at - below))
                                    : 0.5f;
         uint32_t mid = __builtin_amdgcn_readfirstlane(__float_as_uint(fmaf(share, b - a, a)));
@@ -197,14 +218,14 @@ __device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau
         if (mid == lo) break;
         int c = 0;
 #pragma unroll
-        for (int s = 0; s < 2 * E; ++s) c += __popcll(__ballot(d[s] <= __uint_as_float(mid)));
+        for (int s = 0; s < S; ++s) c += __popcll(__ballot(d[s] <= __uint_as_float(mid)));
         if (c < kp) {
             lo = mid;
             below = c;
         } else {
             hi = mid;
             at = c;
-            if (c <= WAVE * E) {
+            if (c <= most) {
                 parted = true;
                 break;
             }
@@ -214,7 +235,7 @@ __device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau
         const float thr = __uint_as_float(hi);
         int w = 0;
 #pragma unroll
-        for (int s = 0; s < 2 * E; ++s) {
+        for (int s = 0; s < S; ++s) {
             const bool in = d[s] <= thr;
             const uint64_t mask = __ballot(in);
             if (in) buf[w + mbcnt64(mask)] = v[s];
@@ -224,8 +245,8 @@ __device__ __forceinline__ void cut_buffer(uint64_t* buf, int& count, float& tau
         count = at;
         wave_lds_sync();
     } else {
-        sort_front<E>((lds_key*)buf, count);
-        count = WAVE * E;
+        sort_front<E, S>((lds_key*)buf, count);
+        count = min(count, most);
         tau = fminf(tau, key_dist(buf[kp - 1]));
     }
 }
@@ -236,8 +257,10 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
                                                        float* __restrict__ slast_out,
                                                        unsigned long long* __restrict__ pair_count)
 {
-    constexpr int CAP = WAVE * E;   // of a list; a buffer holds twice as many
-    __shared__ uint64_t sbuf[4][R][2 * CAP];
+    using Cut = CutRule<M, E>;
+    constexpr int CAP = Cut::CAP, BUF = Cut::BUF;
+    const int full = Cut::full(kp), keep = Cut::keep(kp);
+    __shared__ uint64_t sbuf[4][R][BUF];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row0 = (blockIdx.x * 4 + wave) * R;   // curve position of the first row
@@ -281,7 +304,7 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
                 pairs += static_cast<unsigned long long>(min(TILE, n - tb[u] * TILE)) * rows_here;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    if (bc[r] > 2 * CAP - WAVE) cut_buffer<E>(sbuf[wave][r], bc[r], tau[r], kp);
+                    if (bc[r] > full) cut_buffer<E, Cut::S>(sbuf[wave][r], bc[r], tau[r], kp, keep);
                     append_keys(sbuf[wave][r], bc[r], tau[r], pair_dist2<M>(q[r], xb[u]), jb[u], valid);
                 }
             }
@@ -314,8 +337,8 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
 #pragma unroll
             for (int u = 0; u < NS; ++u) c += __popcll(__ballot(ok[u] && ds[u] <= tau[r]));
             // more equal scores than the buffer holds: tile by tile below
-            fits = fits && c <= 2 * CAP;
-            if (c <= 2 * CAP) {
+            fits = fits && c <= BUF;
+            if (c <= BUF) {
 #pragma unroll
                 for (int u = 0; u < NS; ++u)
                     append_keys(sbuf[wave][r], bc[r], tau[r], ds[u], js[u], ok[u]);
@@ -349,7 +372,7 @@ __global__ __launch_bounds__(256) void k_select_direct(SpatialView sv, int n, in
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (bc[r] > CAP) cut_buffer<E>(sbuf[wave][r], bc[r], tau[r], kp);
+        if (bc[r] > CAP) cut_buffer<E, Cut::S>(sbuf[wave][r], bc[r], tau[r], kp, CAP);
         wave_lds_sync();
         if (row0 + r < n) {
             uint64_t L[E];
@@ -1523,19 +1546,26 @@ static hipError_t launch_select_r(const SpatialView& sv, int n, int kp, uint64_t
     return hipGetLastError();
 }
 
-// Rows per wavefront: one while the rows are few enough for every wavefront to
-// be resident at once (sphere, n = 2000: 14 us at 1 row, 21 at 2, 28 at 3; 32000:
-// 142 against 143), two beyond (torus, n = 100k: 183 us at 1, 170 at 2, 180 at 3;
-// 1M: 3.19, 2.82 and 2.80 ms): more rows share a tile's loads and box tests, but
-// scan each other's tiles.
-constexpr int SELECT_ONE_ROW = 32768;
+// Rows per wavefront: more rows share a tile's loads and box tests, but scan each
+// other's tiles. Up to five coordinates one while the rows are few enough for every
+// wavefront to be resident at once (sphere, n = 2000: 14 us at 1 row, 21 at 2, 28 at
+// 3; 32000: 142 against 143), two beyond (torus, n = 100k: 183 us at 1, 170 at 2, 180
+// at 3; 1M: 3.19, 2.82 and 2.80 ms). From six on a row's tiles are many and mostly its
+// neighbours' too: two (n = 30k, m = 8, k = 64: 0.72 ms at 1, 0.62 at 2), and three for lists
+// of up to 128 of many samples (n = 300k, k = 16: 17.5 ms at 2, 16.4 at 3; longer lists fill
+// the LDS: k = 160 28.1 and 29.3).
+constexpr int SELECT_ONE_ROW = 32768, SELECT_THREE_ROWS = 262144;
 
 template <int M>
 static hipError_t launch_select_m(const SpatialView& sv, int n, int kp, uint64_t* keys, float* slast,
                                   unsigned long long* pairs, hipStream_t st)
 {
-    return n <= SELECT_ONE_ROW ? launch_select_r<M, 1>(sv, n, kp, keys, slast, pairs, st)
-                               : launch_select_r<M, 2>(sv, n, kp, keys, slast, pairs, st);
+    if constexpr (M >= 6) {
+        if (n > SELECT_THREE_ROWS && kp <= 128) return launch_select_r<M, 3>(sv, n, kp, keys, slast, pairs, st);
+    } else {
+        if (n <= SELECT_ONE_ROW) return launch_select_r<M, 1>(sv, n, kp, keys, slast, pairs, st);
+    }
+    return launch_select_r<M, 2>(sv, n, kp, keys, slast, pairs, st);
 }
 
 hipError_t launch_select_direct(const float* Xs, const float* tbox, const float* sbox, int n, int m, int kp,

@@ -69,3 +69,27 @@ def test_every_pair_counted(gpu_lib, n):
     ctx = gpu_lib.Context()
     check(gpu_lib, workloads.gaussian_iid(n, 3, seed=n), 1, 0, ctx)
     assert gpu_lib.knn_pairs(ctx) == n * n
+
+
+@pytest.mark.parametrize("m", [5, 6, 8])
+@pytest.mark.parametrize("k,margin", [(8, 24), (24, 9), (56, 8), (64, 0), (88, 8), (97, 31), (192, 32), (225, 0), (256, 0)])
+def test_list_lengths_by_coordinates(gpu_lib, m, k, margin):
+    # buffers cut after 32 or 64 further keys, and filled ones, on both sides of each length
+    for n in (300, 3001):
+        check(gpu_lib, workloads.gaussian_iid(n, m, seed=k), k, margin)
+
+
+@pytest.mark.parametrize("copies,k", [(100, 20), (300, 90), (700, 20), (700, 200)])
+def test_duplicates_in_eight_coordinates(gpu_lib, copies, k):
+    rng = np.random.default_rng(copies)
+    X = np.repeat(rng.integers(-2, 3, (9, 8)).astype(np.float32), copies, axis=0)[rng.permutation(9 * copies)]
+    idx, d2, _ = gpu_lib.knn(torch.from_numpy(X).cuda(), k, "f32", 8)
+    ri, rd = oracle.knn(X, k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ri)
+    np.testing.assert_array_equal(d2.cpu().numpy(), rd.astype(np.float32))
+
+
+@pytest.mark.parametrize("n", [262144, 262145, 262146, 262147])
+def test_rows_per_wavefront_in_six_coordinates(gpu_lib, n):
+    # two rows up to 262144 samples, then three; the last wavefront has 2, 2, 3 and 1
+    check(gpu_lib, workloads.gaussian_iid(n, 6, seed=1), 30, 32)
