@@ -406,12 +406,12 @@ __global__ __launch_bounds__(256) void k_route_topp(const float* __restrict__ Z,
     if (lane == 0 && home) home[i] = chosen[0];
 }
 
-// The same for NB <= 1024: the row is read once, 16 logits per lane in order
+// The same for NB <= 64 NV: the row is read once, NV logits per lane in order
 // bits (a taken one is 0, below every logit's), and a round takes the wavefront's
 // maximum and, of the lanes that hold it, the smallest bucket. Bound by reading
 // the logits; re-reading the row from the caches in every round took 130 us for
 // 32768 rows of 1024 and four rounds, this 35 (3.8 TB/s).
-constexpr int TOPP_NV = 16;
+template <int NV>
 __global__ __launch_bounds__(256) void k_route_topp_row(const float* __restrict__ Z, int rows, int NB, int P,
                                                         int32_t* __restrict__ home, int32_t* __restrict__ probe)
 {
@@ -419,12 +419,12 @@ __global__ __launch_bounds__(256) void k_route_topp_row(const float* __restrict_
     const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (i >= rows) return;
     const float* z = Z + static_cast<size_t>(i) * NB;
-    float raw[TOPP_NV];
+    float raw[NV];
 #pragma unroll
-    for (int u = 0; u < TOPP_NV; ++u) raw[u] = z[min(u * WAVE + lane, NB - 1)];
-    uint32_t v[TOPP_NV];
+    for (int u = 0; u < NV; ++u) raw[u] = z[min(u * WAVE + lane, NB - 1)];
+    uint32_t v[NV];
 #pragma unroll
-    for (int u = 0; u < TOPP_NV; ++u) {
+    for (int u = 0; u < NV; ++u) {
         float x = raw[u];
         if (x != x) x = -INFINITY;   // a NaN logit ranks last
         if (x == 0.f) x = 0.f;       // zeros of either sign tie
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(256) void k_route_topp_row(const float* __restrict_
         uint32_t bv = 0;
         int bu = 0;
 #pragma unroll
-        for (int u = 0; u < TOPP_NV; ++u) {
+        for (int u = 0; u < NV; ++u) {
             bu = v[u] > bv ? u : bu;
             bv = max(bv, v[u]);
         }
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(256) void k_route_topp_row(const float* __restrict_
         for (m &= m - 1; m; m &= m - 1)
             best = min(best, __builtin_amdgcn_readlane(bu * WAVE + lane, __builtin_ctzll(m)));
 #pragma unroll
-        for (int u = 0; u < TOPP_NV; ++u)
+        for (int u = 0; u < NV; ++u)
             if (u * WAVE + lane == best) v[u] = 0u;
         if (lane == 0) {
             probe[static_cast<size_t>(i) * P + p] = best;
@@ -560,10 +560,19 @@ hipError_t launch_adam(float* p, const float* g, float* m1, float* m2, int64_t c
 hipError_t launch_route_topp(const float* Z, int rows, int NB, int P, int32_t* home, int32_t* probe, hipStream_t st)
 {
     if (P < 1 || P > 32 || P > NB) return hipErrorInvalidValue;
-    // up to 1024 buckets a row fits the registers of a wavefront; wider rows are
-    // read again in every round
-    if (NB <= TOPP_NV * WAVE)
-        hipLaunchKernelGGL(k_route_topp_row, dim3((rows + 3) / 4), dim3(256), 0, st, Z, rows, NB, P, home, probe);
+    // up to 1024 buckets a row fits the registers of a wavefront, 1, 4 or 16 logits
+    // per lane (65536 rows of 32 buckets with their forward pass: 47 us with 1, 94 with 16, 77
+    // by the wider rows' kernel; of 256: 94 with 4, 133, 162); wider rows are read again
+    // in every round
+    auto row = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((rows + 3) / 4), dim3(256), 0, st, Z, rows, NB, P, home, probe);
+    };
+    if (NB <= WAVE)
+        row(k_route_topp_row<1>);
+    else if (NB <= 4 * WAVE)
+        row(k_route_topp_row<4>);
+    else if (NB <= 16 * WAVE)
+        row(k_route_topp_row<16>);
     else if (P <= 8)
         hipLaunchKernelGGL(k_route_topp<8>, dim3((rows + 3) / 4), dim3(256), 0, st, Z, rows, NB, P, home, probe);
     else

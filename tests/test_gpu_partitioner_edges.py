@@ -104,3 +104,9 @@ def test_large_forward_exact(gpu_lib, B, h1, h2, nb):
     kvb.part_set_params(torch.from_numpy(flat).cuda(), ctx=ctx)
     np.testing.assert_array_equal(kvb.mlp_forward(torch.from_numpy(X).cuda(), nb, ctx=ctx).cpu().numpy(), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("nb,P", [(64, 4), (64, 32), (256, 9), (288, 9)])
+def test_routes_at_every_row_width(gpu_lib, nb, P):
+    # the largest rows of one and of four logits per lane, and one beyond
+    test_routes_follow_the_logits(gpu_lib, nb, P)
