@@ -215,13 +215,15 @@ __global__ __launch_bounds__(256) void k_project_chunk(const double* __restrict_
 {
     __shared__ double red[4][RHS * SP_VECS];
     const int j0 = blockIdx.x * SP_VECS;
-    const int r0 = blockIdx.y * chunk, r1 = min(n, r0 + chunk);
+    // 64 bits: the last chunk's end, and a thread's row past it, may lie beyond 2^31
+    const int64_t r0 = static_cast<int64_t>(blockIdx.y) * chunk;
+    const int64_t r1 = r0 + chunk < n ? r0 + chunk : n;
     const double* y[SP_VECS];
 #pragma unroll
     for (int v = 0; v < SP_VECS; ++v) y[v] = Y + static_cast<size_t>(min(j0 + v, nvec - 1)) * n;
     double acc[RHS][SP_VECS] = {};
 #pragma unroll 2
-    for (int r = r0 + threadIdx.x; r < r1; r += 256) {
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
         const double s = WEIGHT ? P[r] * sqrt(D[r]) : 1.0;
         const double w0 = WEIGHT ? s * x0[r] : x0[r];
         const double w1 = RHS > 1 ? (WEIGHT ? s * x1[r] : x1[r]) : 0.0;
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(256) void k_cdc_tensor(const double* __restrict__ Y
     double acc[CDC_MAX];
 #pragma unroll
     for (int l = 0; l < CDC_MAX; ++l) acc[l] = 0.0;
-    for (int r = threadIdx.x; r < n; r += 256) {
+    for (int64_t r = threadIdx.x; r < n; r += 256) {
         const double w = Y[static_cast<size_t>(j) * n + r] * Y[static_cast<size_t>(k) * n + r] / (P[r] * sqrt(D[r]));
 #pragma unroll
         for (int l = 0; l < CDC_MAX; ++l)
@@ -415,9 +417,9 @@ struct RowChunks {
 
 RowChunks row_chunks(int n, int nvec)
 {
-    const int want = std::max(1, std::min({64, n / 512, n / nvec}));
-    const int rows = (n + want - 1) / want;
-    return {rows, (n + rows - 1) / rows};
+    const int64_t want = std::max(1, std::min({64, n / 512, n / nvec}));
+    const int64_t rows = (n + want - 1) / want;
+    return {static_cast<int>(rows), static_cast<int>((n + rows - 1) / rows)};
 }
 
 // split of the Lanczos projections over rows: chunks of at least 8192 rows,
@@ -716,7 +718,7 @@ int kvb_kolmogorov_solve(kvb_ctx ctx, const double* evecs, const double* evals_h
     double* cg = cv.take<double>(l);
     hipStream_t st = ctx->stream;
     const double* Y = evecs + size_t(skip) * nn;
-    const dim3 blk(256), rows_grid((nn + 255) / 256);
+    const dim3 blk(256), rows_grid(static_cast<unsigned>((n + 255) / 256));
     double* lam = ctx->spec_host;
     double* ch = ctx->spec_host + SPEC_MAX;
     for (int j = 0; j < l; ++j) lam[j] = evals_host[skip + j];
@@ -761,7 +763,7 @@ int kvb_carre_du_champ(kvb_ctx ctx, const double* evecs, const double* evals_hos
     int* pj = cv.take<int>(npairs);
     int* pk = cv.take<int>(npairs);
     hipStream_t st = ctx->stream;
-    const dim3 blk(256), rows_grid((nn + 255) / 256), coef_grid((nvec + 3) / 4);
+    const dim3 blk(256), rows_grid(static_cast<unsigned>((n + 255) / 256)), coef_grid((nvec + 3) / 4);
     double* lam = ctx->spec_host;
     for (int j = 0; j < nvec; ++j) lam[j] = evals_host[j];
     const RowChunks rk = row_chunks(nn, nvec);

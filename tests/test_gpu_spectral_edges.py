@@ -58,3 +58,29 @@ def test_spectral_calls_at_chunk_edges(gpu_lib, n, nvec):
     grad, _ = kvb.carre_du_champ(e, P, D, u, v)
     r, s = both(cdc)
     assert bool(((grad - r).abs() <= tol * s).all())
+
+
+def test_solve_at_the_largest_sample_count(gpu_lib):
+    """The last row chunk ends beyond 2^31 rows: its rows count, and no row is read
+    past the end. One constant eigenvector and unit weights, 17 GB an array; every
+    sum is a small whole number."""
+    kvb = gpu_lib
+    n = 2 ** 31 - 32
+    if torch.cuda.mem_get_info()[0] < 100e9:
+        pytest.skip("needs 70 GB of device memory")
+    one = torch.ones(n, device="cuda", dtype=torch.float64)
+    g = torch.zeros(n, device="cuda", dtype=torch.float64)
+    rows = [0, n // 2, n - 40, n - 1]
+    for r, v in zip(rows, (7.0, 4.0, 5.0, 3.0)):
+        g[r] = v
+    f = torch.empty(n, device="cuda", dtype=torch.float64)
+    lam, coef = np.array([-2.0]), np.zeros(1)
+    ctx = kvb.Context()
+    at = [kvb._ptr(t) for t in (one, g, f)]
+    ctx.check(ctx.lib.kvb_kolmogorov_solve(ctx.h, at[0], lam.ctypes.data, 1, 0, at[0], at[0], at[1], n, at[2], None,
+                                           coef.ctypes.data))
+    assert coef[0] == 19.0 * (1.0 / np.sqrt(float(n)))
+    assert [float(f[r]) for r in rows] == [-9.5] * 4
+    ctx.close()
+    del one, g, f
+    torch.cuda.empty_cache()
