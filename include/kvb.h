@@ -156,7 +156,9 @@ int kvb_knn(kvb_ctx ctx, const float* X, int64_t n, int32_t m, int32_t k,
  * distance tiles of the last kvb_knn call on ctx computed: the tiles the
  * spatial scans did not skip by their boxes (direct tiles, curve-ordered
  * matrix-core tiles), every pair when KVB_OPT_CURVE_ORDER is 0, or the routed
- * pairs of the learned search. Synchronises the context stream. */
+ * pairs of the learned search. A pair counts once, also where its score is computed
+ * again (the second pass of the curve-ordered tiles). Synchronises the context
+ * stream. */
 int kvb_knn_pairs(kvb_ctx ctx, double* pairs_host);
 
 /*

@@ -98,3 +98,14 @@ def test_more_tiles_than_notes_equal_scores(gpu_lib, k, margin, mode):
     # corners of a 12-cube, six or so samples at each: 70 at distance 1, 400 at sqrt 2
     X = np.random.default_rng(k).integers(0, 2, (25000, 12)).astype(np.float32)
     check(gpu_lib, X, k, margin, 3, mode, nrows=500)
+
+
+@pytest.mark.parametrize("n,m,mode,every", [(25001, 64, "bf16", True),    # every tile scored by the workgroup scan
+                                            (70001, 12, "f32", False),    # short contractions: tiles out of reach left out
+                                            (25000, 12, "f32", False)])   # the walk beyond its notes
+def test_pairs_count_once(gpu_lib, n, m, mode, every):
+    ctx = gpu_lib.Context()
+    gpu_lib.knn(torch.from_numpy(workloads.gaussian_iid(n, m, seed=m)).cuda(), 64, mode, 32, ctx=ctx)
+    pairs = gpu_lib.knn_pairs(ctx)
+    ctx.close()
+    assert pairs == float(n) * n if every else 0.5 * n * n < pairs <= float(n) * n
