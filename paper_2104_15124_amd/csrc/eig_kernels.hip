@@ -171,7 +171,11 @@ __global__ __launch_bounds__(256) void k_start_vector(uint64_t seed, int n, doub
 // Y[i][r] = sum_c V[c][r] S[c][i] (Ritz vectors), S as S[c * nev + i]. A
 // workgroup forms RITZ_VECS vectors of its rows from one sweep of V (one vector
 // at a time read V nev times: 5.8 ms for 36 vectors at n = 100k and 400
-// columns, 0.31 ms now).
+// columns, 0.31 ms now). Sums past the last vector are formed for nothing, and many
+// sums leave few wavefronts: at 4, 8, 12, 16 and 24 vectors 424, 358, 304, 365 and 495 us
+// there; 10 vectors of 128 columns 51, 50, 65, 79, 104, 25 113, 102, 86, 102, 146; n = 1M, 100
+// columns, 8 vectors 305, 162, 224, 252, 321 and 64 2417, 1327, 1269, 971, 973. Eight
+// and twelve are within 1.4 times the best of them everywhere, the others are not.
 constexpr int RITZ_VECS = 12;
 __global__ __launch_bounds__(256) void k_ritz(const double* __restrict__ V, int64_t ldv, int m,
                                               const double* __restrict__ S, int nev, int n, double* __restrict__ Y)

@@ -35,17 +35,17 @@
 // A list without room for a tile's keys is cut by a lower threshold that at least kp
 // of its keys do not exceed. Lists of kp within 32 of their capacity are sorted instead
 // once full, and take further keys from a buffer in LDS, 32 at a time (k + margin =
-// 256, n = 200k, m = 16: 20.7 to 11.0 ms against a sort per tile; 14.5 by one
-// pass of sorted lists). At the end each list is sorted once.
+// 256, n = 20k, m = 12: 4.1 ms against 17.4 by a sort per tile and 5.1 by one pass of
+// sorted lists; 5-manifold n = 100k 13.6, 35.1 and 19.8). At the end each list is sorted once.
 //
 // A scan that keeps sorted lists while its thresholds fall appends each query's
 // candidates several times over and merges its list some ten times; those
 // merges and appends were two thirds of its time. A wavefront whose box held a
 // few outlying samples walked for most of a launch (141 of 176 ms on the 8M
 // mixture) until boxes were also tested against the single queries (PointTest).
-// Select, before (sorted lists, box tests only) and now: mixture m = 16, n =
-// 8M, FP32 140 -> 78 ms, n = 1M BF16 19.9 -> 10.5; 5-manifold m = 64, n = 1M
-// 242 -> 125; lifted 3-sphere m = 128, n = 4M, k = 128: 125 -> 61.
+// Whole k-NN calls, before (sorted lists, box tests only) and now: mixture m = 16,
+// n = 8M, FP32 144 -> 97 ms, n = 1M BF16 19.9 -> 13.3; 5-manifold m = 64, n = 1M
+// 254 -> 97; lifted 3-sphere m = 128, n = 4M, k = 128: 192 -> 103.
 //
 // Short contractions (SHORT) keep the query fragments and two tiles ahead of
 // the products in registers. Long ones keep the query operand in LDS, and first

@@ -92,6 +92,13 @@ def test_more_tiles_than_notes_coarse(gpu_lib):
         check(gpu_lib, workloads.gaussian_iid(25000, 100, seed=3), 40, margin, 1, nrows=500)
 
 
+def test_every_tile_within_reach_coarse(gpu_lib):
+    # short contractions of one term: the scan skips tiles by true distances
+    X = workloads.gaussian_iid(70001, 40, seed=3)
+    X[::2] *= 0.5
+    check(gpu_lib, X, 40, 32, 1, nrows=200)
+
+
 @pytest.mark.parametrize("mode", ["f32", "bf16"])
 @pytest.mark.parametrize("k,margin", [(40, 0), (64, 32), (96, 32), (128, 32), (224, 32)])
 def test_more_tiles_than_notes_equal_scores(gpu_lib, k, margin, mode):
